@@ -1451,6 +1451,10 @@ kcm_status kcm_chain_free(kcm_chain *c)
                 break;
             }
     }
+    // a table of kcm_step_noalloc that holds the chain matches no later call: a
+    // new chain may get this handle's address with another device block
+    for (auto &d : g_noalloc)
+        if (std::find(d.chains, d.chains + d.n_chains, c) != d.chains + d.n_chains) d.n_chains = 0;
     delete c;
     return KCM_OK;
 }

@@ -72,3 +72,20 @@ def test_noalloc_rejects_more_chains_than_its_table_holds():
         assert kcm.kcm_step_noalloc([c], 1)[0] == kcm.KCM_OK
     finally:
         c.free()
+
+
+def test_noalloc_table_forgets_freed_chains():
+    """A chain built after another one was freed, at whatever handle address,
+    is stepped from its own device block: equal to kcm_step bit for bit."""
+    p = params(kcm.KCM_FP64)
+    for k, m in enumerate((7, 19, 11, 30)):
+        seq, th = synth.sequence(m, 90 + k), synth.random_dihedrals(m, 90 + k)
+        a, b = kcm.Chain(seq, TYPES, p, theta0=th), kcm.Chain(seq, TYPES, p, theta0=th)
+        print(f"case=noalloc-free m={m}", flush=True)
+        kcm.kcm_step([a], 2)
+        kcm.kcm_step_noalloc([b], 2)
+        sa, sb = a.state(), b.state()
+        for key in sa:
+            assert np.array_equal(sa[key], sb[key]), key
+        a.free()
+        b.free()
