@@ -190,7 +190,7 @@ std::vector<V3> sample_directions(int n_orb)
 // device block layout
 // ---------------------------------------------------------------------------
 struct Layout {
-    size_t desc, stats, grid, theta, dtheta, tau, mc_theta, mask, joint0, jcur, xform, xform_loc, blk_xf, tmax_part, bad_part;
+    size_t desc, stats, grid, theta, dtheta, tau, mc_theta, mask, joint0, jcur, xform_loc, blk_xf, tmax_part, bad_part;
     size_t r0, r, aparam, g0, qfix;
     size_t cell_key, cell_count, cell_start, cell_local, scan_part, bbox_part, wrench_part, s_r, s_p, s_tmp, s_idx;
     size_t f_pair, f_cav;
@@ -215,7 +215,7 @@ Layout make_layout(int m, int n_orb, int side_chains)
     l.njb_bb = (l.J + JOINT_BLOCK - 1) / JOINT_BLOCK;
     l.njb = l.njb_bb + (l.n_chi + JOINT_BLOCK - 1) / JOINT_BLOCK;
     l.N = (int)sample_directions(n_orb).size();
-    l.cap = std::max(8192, 8 * l.n);
+    l.cap = cell_capacity(l.n);
     size_t off = 0;
     auto take = [&](size_t bytes) {
         off = (off + 255) & ~size_t(255);
@@ -223,7 +223,7 @@ Layout make_layout(int m, int n_orb, int side_chains)
         off += bytes;
         return o;
     };
-    const size_t n = l.n, J = l.J, L = l.L, N = l.N, cap = l.cap;
+    const size_t n = l.n, J = l.J, N = l.N, cap = l.cap;
     l.desc = take(sizeof(ChainDev));
     l.stats = take(sizeof(ChainStats));
     l.grid = take(sizeof(Grid));
@@ -235,7 +235,6 @@ Layout make_layout(int m, int n_orb, int side_chains)
     l.mask = take(Jt);
     l.joint0 = take(64 * J);
     l.jcur = take(64 * J);
-    l.xform = take(96 * L);
     l.xform_loc = take(96 * J);
     l.blk_xf = take(96 * (size_t)l.njb_bb);
     l.tmax_part = take(8 * (size_t)l.njb);
@@ -338,22 +337,42 @@ struct TimedIter {
     hipEvent_t it0, f0, f1, it1;
 };
 
+// The form of the batch's iterations (the results are the same).  One
+// workgroup per chain replaces eight launches of about 4.5 us by one: of
+// 15 us for chains of at most 256 atoms, and about 20 us more for each 768
+// atoms of the longest.  Measured, a whole iteration in mixed precision,
+// one workgroup against nine launches: one chain of 150 atoms 40 against 63
+// us, of 1,000 atoms 55 against 69, of 2,000 73 against 75, of 3,000 89
+// against 79.  With chains for half of the 256 CUs the workgroups run side by
+// side and win at every length they can hold: 128 chains of 6,400 atoms 2,913
+// against 2,954 us; 32 of them lose, 855 against 785.
+constexpr int CHAIN_ATOMS_ALWAYS = 1536, CHAIN_MANY = 128;
+void set_form(Batch &b, int max_atoms)
+{
+    b.max_atoms = max_atoms;
+    b.fused = max_atoms <= CHAIN_ATOMS_ALWAYS || (b.n_chains >= CHAIN_MANY && max_atoms <= CHAIN_ATOMS) ? 1 : 0;
+}
+
 // One iteration; with ti, events bracket the iteration and the force kernel.
 hipError_t launch_iteration(const Batch &bt, int prec, hipStream_t stream, const TimedIter *ti = nullptr)
 {
     hipError_t e;
     if (ti && (e = hipEventRecord(ti->it0, stream)) != hipSuccess) return e;
-    if ((e = launch_tau(bt, stream)) != hipSuccess) return e;
-    if ((e = launch_stepfk(bt, MODE_ITER, stream)) != hipSuccess) return e;
-    if ((e = launch_place(bt, MODE_ITER, stream)) != hipSuccess) return e;
-    if ((e = launch_cellkey(bt, stream)) != hipSuccess) return e;
-    if ((e = launch_cellscan(bt, stream)) != hipSuccess) return e;
-    if ((e = launch_scatter(bt, stream)) != hipSuccess) return e;
-    if ((e = launch_rank(bt, stream)) != hipSuccess) return e;
+    if (bt.fused) {
+        if ((e = launch_chain(bt, MODE_ITER, stream)) != hipSuccess) return e;
+    } else {
+        if ((e = launch_tau(bt, stream)) != hipSuccess) return e;
+        if ((e = launch_stepfk(bt, MODE_ITER, stream)) != hipSuccess) return e;
+        if ((e = launch_place(bt, MODE_ITER, stream)) != hipSuccess) return e;
+        if ((e = launch_cellkey(bt, stream)) != hipSuccess) return e;
+        if ((e = launch_cellscan(bt, stream)) != hipSuccess) return e;
+        if ((e = launch_scatter(bt, stream)) != hipSuccess) return e;
+        if ((e = launch_rank(bt, stream)) != hipSuccess) return e;
+    }
     if (ti && (e = hipEventRecord(ti->f0, stream)) != hipSuccess) return e;
     if ((e = launch_force(bt, prec, g_force_shape, stream)) != hipSuccess) return e;
     if (ti && (e = hipEventRecord(ti->f1, stream)) != hipSuccess) return e;
-    if ((e = launch_wrench(bt, stream)) != hipSuccess) return e;
+    if (!bt.fused && (e = launch_wrench(bt, stream)) != hipSuccess) return e;
     if (ti && (e = hipEventRecord(ti->it1, stream)) != hipSuccess) return e;
     return hipSuccess;
 }
@@ -362,6 +381,7 @@ hipError_t launch_iteration(const Batch &bt, int prec, hipStream_t stream, const
 // (the kernels skip the others).
 hipError_t launch_boot(const Batch &bt, hipStream_t stream)
 {
+    if (bt.fused) return hipSuccess;  // every iteration sizes its own grid
     hipError_t e;
     if ((e = launch_stepfk(bt, MODE_BOOT, stream)) != hipSuccess) return e;
     if ((e = launch_place(bt, MODE_BOOT, stream)) != hipSuccess) return e;
@@ -371,10 +391,17 @@ hipError_t launch_boot(const Batch &bt, hipStream_t stream)
 // The post phase of the last forces of a call.
 hipError_t launch_final(const Batch &bt, hipStream_t stream)
 {
+    if (bt.fused) return launch_chain(bt, MODE_FINAL, stream);
     hipError_t e;
     if ((e = launch_tau(bt, stream)) != hipSuccess) return e;
     if ((e = launch_stepfk(bt, MODE_FINAL, stream)) != hipSuccess) return e;
     return launch_finish(bt, stream);
+}
+
+// Torques and energies of the pending forces, without the step.
+hipError_t launch_torques(const Batch &bt, hipStream_t stream)
+{
+    return bt.fused ? launch_chain(bt, MODE_TAU, stream) : launch_tau(bt, stream);
 }
 
 // Captures `iters` consecutive iterations of the batch as one executable graph.
@@ -472,7 +499,7 @@ kcm_status ensure_table(kcm_chain *const *chains, int n_chains, hipStream_t stre
         int32_t *jblk = reinterpret_cast<int32_t *>(host.data() + jblk_pos);
         int32_t *sblk = reinterpret_cast<int32_t *>(host.data() + scan_pos);
         long long total = 0, blocks = 0, jblocks = 0, sblocks = 0;
-        int max_chunks = 1;
+        int max_chunks = 1, max_atoms = 0;
         for (int i = 0; i < n_chains; ++i) {
             tab[i] = chains[i]->d_desc;
             off[i] = (int32_t)total;
@@ -485,6 +512,7 @@ kcm_status ensure_table(kcm_chain *const *chains, int n_chains, hipStream_t stre
             const int chunks = (chains[i]->h.cap_cells + SCAN_CHUNK - 1) / SCAN_CHUNK;
             sblocks += chunks;
             max_chunks = std::max(max_chunks, chunks);
+            max_atoms = std::max(max_atoms, chains[i]->n);
         }
         if (total > std::numeric_limits<int32_t>::max() || sblocks > std::numeric_limits<int32_t>::max())
             return fail(KCM_E_INVAL, "too many atoms in one call");
@@ -506,6 +534,7 @@ kcm_status ensure_table(kcm_chain *const *chains, int n_chains, hipStream_t stre
         t->batch.total_jblocks = (int)jblocks;
         t->batch.total_scan_blocks = (int)sblocks;
         t->batch.max_scan_chunks = max_chunks;
+        set_form(t->batch, max_atoms);
         t->chains.assign(chains, chains + n_chains);
         if (t->graph) {
             HIP_TRY(hipGraphExecDestroy(t->graph));
@@ -761,7 +790,6 @@ kcm_status kcm_build_chain(const kcm_chain_desc *desc, const kcm_params *params,
     PTR(mask, uint8_t *);
     PTR(joint0, double4 *);
     PTR(jcur, double4 *);
-    PTR(xform, double *);
     PTR(xform_loc, double *);
     PTR(blk_xf, double *);
     PTR(tmax_part, double *);
@@ -1012,7 +1040,7 @@ kcm_status noalloc_table(NoallocDevice &d, kcm_chain *const *chains, int n_chain
     int32_t *jblk = reinterpret_cast<int32_t *>(g_noalloc_table + kNaTab + 2 * kNaOff);
     int32_t *sblk = reinterpret_cast<int32_t *>(g_noalloc_table + kNaTab + 3 * kNaOff);
     long long total = 0, blocks = 0, jblocks = 0, sblocks = 0;
-    int max_chunks = 1;
+    int max_chunks = 1, max_atoms = 0;
     for (int i = 0; i < n_chains; ++i) {
         tab[i] = chains[i]->d_desc;
         off[i] = (int32_t)total;
@@ -1025,6 +1053,7 @@ kcm_status noalloc_table(NoallocDevice &d, kcm_chain *const *chains, int n_chain
         const int chunks = (chains[i]->h.cap_cells + SCAN_CHUNK - 1) / SCAN_CHUNK;
         sblocks += chunks;
         max_chunks = std::max(max_chunks, chunks);
+        max_atoms = std::max(max_atoms, chains[i]->n);
     }
     if (total > std::numeric_limits<int32_t>::max() || sblocks > std::numeric_limits<int32_t>::max())
         return fail(KCM_E_INVAL, "too many atoms in one call");
@@ -1047,6 +1076,7 @@ kcm_status noalloc_table(NoallocDevice &d, kcm_chain *const *chains, int n_chain
     b.total_jblocks = (int)jblocks;
     b.total_scan_blocks = (int)sblocks;
     b.max_scan_chunks = max_chunks;
+    set_form(b, max_atoms);
     for (int i = 0; i < n_chains; ++i) d.chains[i] = chains[i];
     d.n_chains = n_chains;
     d.used = true;
@@ -1196,14 +1226,14 @@ kcm_status kcm_mc_minimize(kcm_chain *const *chains, int32_t n_chains, int32_t n
     // the energy of the current angles: one evaluation, taken as the start
     HIP_TRY(launch_mc_propose(bt, MC_RESET, nullptr, nullptr, 0, stream));
     if ((s = iterate_locked(t, chains, n_chains, 1, prec, stream, true, false)) != KCM_OK) return s;
-    HIP_TRY(launch_tau(bt, stream));
+    HIP_TRY(launch_torques(bt, stream));
     HIP_TRY(launch_mc_decide(bt, MC_INIT, u, n_trials, 0, kT, stream));
     HIP_TRY(launch_mc_apply(bt, stream));
     for (int k = 0; k < n_trials; ++k) {
         // perturb, n_descent steps, and the evaluation of the reached angles
         HIP_TRY(launch_mc_propose(bt, MC_PROPOSE, delta, t->mc_off_dev, k, stream));
         if ((s = iterate_locked(t, chains, n_chains, n_descent + 1, prec, stream, true, false)) != KCM_OK) return s;
-        HIP_TRY(launch_tau(bt, stream));
+        HIP_TRY(launch_torques(bt, stream));
         HIP_TRY(launch_mc_decide(bt, MC_TRIAL, u, n_trials, k, kT, stream));
         HIP_TRY(launch_mc_apply(bt, stream));
     }

@@ -91,7 +91,6 @@ struct ChainDev {
     uint8_t *mask;
     double4 *joint0;     // [J][2]: (u0, 0), (p0, 0) zero-position axis and point
     double4 *jcur;       // [J][2]: current (u, 0), (p, 0)
-    double *xform;       // [L][12] link transforms: R row-major, then t
     double *xform_loc;   // [J][12] product of the joint transforms from the start of j's joint block to j
     double *blk_xf;      // [nJB][12] product of all joint transforms of each joint block
     double *tmax_part;   // [nJB] max |tau| over the masked joints of each joint block
@@ -137,11 +136,22 @@ struct Batch {
     int total_blocks;
     int total_jblocks;
     int total_scan_blocks;
+    int max_atoms;            // atoms of the largest chain
+    int fused;                // 1: the iteration runs as k_chain and the force kernel
     int max_scan_chunks;      // most chunks of one chain (sizes the chunk-offset table in LDS)
 };
 
 // Modes of the step/kinematics and placement kernels.
-enum : int { MODE_ITER = 0, MODE_FINAL = 1, MODE_BOOT = 2 };
+enum : int { MODE_ITER = 0, MODE_FINAL = 1, MODE_BOOT = 2, MODE_TAU = 3 };
+
+// Cells a chain of n atoms holds at most (its grid is coarsened to fit).
+constexpr int cell_capacity(int n) { return 8 * n > 8192 ? 8 * n : 8192; }
+// Largest chain of the one-workgroup form of the iteration (k_chain): its
+// cells and starts fit 16 bits, its link transforms and cell list the LDS.
+constexpr int CHAIN_ATOMS = 6400;
+constexpr int CHAIN_JBLOCKS = (CHAIN_ATOMS / APR * 2 + JOINT_BLOCK - 1) / JOINT_BLOCK;
+constexpr int CHAIN_LDS = 2 * (cell_capacity(CHAIN_ATOMS) + 3 * CHAIN_ATOMS);
+static_assert(cell_capacity(CHAIN_ATOMS) < 65536 && 96 * (CHAIN_ATOMS / APR * 2 + 1) <= CHAIN_LDS, "k_chain's LDS");
 
 // Launchers (kcm_kernels.hip).  One iteration is
 //   tau, stepfk (post phase of the previous forces if pending, then the
@@ -149,6 +159,9 @@ enum : int { MODE_ITER = 0, MODE_FINAL = 1, MODE_BOOT = 2 };
 //   conformation, keys and counts), cellscan, scatter, rank, force, wrench;
 // a call ends with tau, stepfk(MODE_FINAL), finish.  A chain without a grid
 // (new, or new angles) first runs stepfk(MODE_BOOT), place(MODE_BOOT), gridboot.
+// A batch with `fused` set runs each iteration as chain(MODE_ITER), force; a
+// call then ends with chain(MODE_FINAL) and needs no boot.
+hipError_t launch_chain(const Batch &b, int mode, hipStream_t s);
 hipError_t launch_tau(const Batch &b, hipStream_t s);
 hipError_t launch_stepfk(const Batch &b, int mode, hipStream_t s);
 hipError_t launch_gridboot(const Batch &b, hipStream_t s);

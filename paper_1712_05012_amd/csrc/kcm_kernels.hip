@@ -35,6 +35,8 @@
 #include <float.h>
 #include <math.h>
 
+#include <algorithm>
+
 namespace kcm {
 
 constexpr int WAVE = 64;
@@ -43,6 +45,68 @@ constexpr double PI_D = 3.14159265358979323846;
 // FP32 value lies this close to its threshold is decided again in FP64.  The
 // FP32 error of the tested quantity stays below ~5e-6 A for offsets < 16 A.
 constexpr float MIXED_BAND = 4.0e-5f;
+
+// ---------------------------------------------------------------------------
+// moves between the lanes of a wave
+// ---------------------------------------------------------------------------
+// A shuffle is two LDS permutes per double, and one CU's LDS takes about ten
+// cycles for each: the scans and reductions of the chain kernels were bound by
+// them.  The moves below stay in the vector unit where the
+// pattern allows it: shifts by one lane and rotations inside a row of 16 are
+// data-parallel modifiers, swaps of half waves and of rows are single
+// instructions.  They carry the same values to the same lanes.
+template <int CTRL> __device__ __forceinline__ int dpp(int x) { return __builtin_amdgcn_update_dpp(0, x, CTRL, 0xf, 0xf, true); }
+template <int CTRL> __device__ __forceinline__ double dpp(double x)
+{
+    return __hiloint2double(dpp<CTRL>(__double2hiint(x)), dpp<CTRL>(__double2loint(x)));
+}
+constexpr int DPP_WAVE_SHL1 = 0x130, DPP_WAVE_SHR1 = 0x138, DPP_ROW_ROR = 0x120;
+// the lower half of the wave in both halves (UPPER: the upper one), and the
+// even rows of 16 in both rows of each half (UPPER: the odd ones)
+template <bool UPPER> __device__ __forceinline__ int both_halves(int x)
+{
+    return (int)__builtin_amdgcn_permlane32_swap((unsigned)x, (unsigned)x, false, false)[UPPER];
+}
+template <bool UPPER> __device__ __forceinline__ int both_rows(int x)
+{
+    return (int)__builtin_amdgcn_permlane16_swap((unsigned)x, (unsigned)x, false, false)[UPPER];
+}
+template <bool UPPER> __device__ __forceinline__ double both_halves(double x)
+{
+    return __hiloint2double(both_halves<UPPER>(__double2hiint(x)), both_halves<UPPER>(__double2loint(x)));
+}
+template <bool UPPER> __device__ __forceinline__ double both_rows(double x)
+{
+    return __hiloint2double(both_rows<UPPER>(__double2hiint(x)), both_rows<UPPER>(__double2loint(x)));
+}
+// lane l takes the value of lane l - d (lanes below d: anything); d a power of two, known when compiled
+__device__ __forceinline__ double from_below(double x, int d)
+{
+    if (d == 1) return dpp<DPP_WAVE_SHR1>(x);
+    if (d == 2) return dpp<DPP_WAVE_SHR1>(dpp<DPP_WAVE_SHR1>(x));
+    if (d == 32) return both_halves<false>(x);
+    return __shfl_up(x, d, WAVE);
+}
+// lane l takes the value of lane l + d (the last d lanes: anything)
+__device__ __forceinline__ double from_above(double x, int d)
+{
+    if (d == 1) return dpp<DPP_WAVE_SHL1>(x);
+    if (d == 2) return dpp<DPP_WAVE_SHL1>(dpp<DPP_WAVE_SHL1>(x));
+    if (d == 32) return both_halves<true>(x);
+    return __shfl_down(x, d, WAVE);
+}
+// op over the wave in every lane, as the butterfly over lane distances 32, 16,
+// ..., 1 takes it: below 16 the values repeat with the last distance inside a
+// row, so a rotation by half of it brings the partner's
+template <typename T, typename Op> __device__ __forceinline__ T wave_all(T v, Op op)
+{
+    v = op(both_halves<false>(v), both_halves<true>(v));
+    v = op(both_rows<false>(v), both_rows<true>(v));
+    v = op(v, dpp<DPP_ROW_ROR + 8>(v));
+    v = op(v, dpp<DPP_ROW_ROR + 4>(v));
+    v = op(v, dpp<DPP_ROW_ROR + 2>(v));
+    return op(v, dpp<DPP_ROW_ROR + 1>(v));
+}
 
 // ---------------------------------------------------------------------------
 // rigid transforms (rotation R row-major, translation t): x -> R x + t
@@ -75,13 +139,13 @@ __device__ __forceinline__ Xf xf_mul(const Xf &A, const Xf &B)
     return C;
 }
 
-__device__ __forceinline__ Xf xf_shfl_up(const Xf &x, int d)
+__device__ __forceinline__ Xf xf_from_below(const Xf &x, int d)
 {
     Xf y;
 #pragma unroll
-    for (int k = 0; k < 9; ++k) y.r[k] = __shfl_up(x.r[k], d, WAVE);
+    for (int k = 0; k < 9; ++k) y.r[k] = from_below(x.r[k], d);
 #pragma unroll
-    for (int k = 0; k < 3; ++k) y.t[k] = __shfl_up(x.t[k], d, WAVE);
+    for (int k = 0; k < 3; ++k) y.t[k] = from_below(x.t[k], d);
     return y;
 }
 
@@ -114,27 +178,19 @@ __device__ __forceinline__ int link_of_atom(int a)
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ double wave_sum(double v)
 {
-#pragma unroll
-    for (int d = 32; d > 0; d >>= 1) v += __shfl_xor(v, d, WAVE);
-    return v;
+    return wave_all(v, [](double a, double b) { return a + b; });
 }
 __device__ __forceinline__ double wave_max(double v)
 {
-#pragma unroll
-    for (int d = 32; d > 0; d >>= 1) v = fmax(v, __shfl_xor(v, d, WAVE));
-    return v;
+    return wave_all(v, [](double a, double b) { return fmax(a, b); });
 }
 __device__ __forceinline__ double wave_min(double v)
 {
-#pragma unroll
-    for (int d = 32; d > 0; d >>= 1) v = fmin(v, __shfl_xor(v, d, WAVE));
-    return v;
+    return wave_all(v, [](double a, double b) { return fmin(a, b); });
 }
 __device__ __forceinline__ int wave_sum_i(int v)
 {
-#pragma unroll
-    for (int d = 32; d > 0; d >>= 1) v += __shfl_xor(v, d, WAVE);
-    return v;
+    return wave_all(v, [](int a, int b) { return a + b; });
 }
 
 // Sum of K doubles over the block; the result is returned to every thread.
@@ -238,12 +294,10 @@ __device__ __forceinline__ Xf xf_shfl_idx(const Xf &x, int src)
     return y;
 }
 
-// Writes the link transform G_{j+1} and the current axis (u_j, p_j) of joint j.
-__device__ __forceinline__ void fk_emit(const Xf &G, int j, const double4 *__restrict__ joint0, double *__restrict__ xform,
+// The current axis (u_j, p_j) of joint j from the transform G of link j + 1.
+__device__ __forceinline__ void fk_emit(const Xf &G, int j, const double4 &u0, const double4 &p0,
                                         double4 *__restrict__ jcur)
 {
-    xf_store(xform + 12 * (j + 1), G);
-    const double4 u0 = joint0[2 * j], p0 = joint0[2 * j + 1];
     double4 u, p;
     u.x = G.r[0] * u0.x + G.r[1] * u0.y + G.r[2] * u0.z;
     u.y = G.r[3] * u0.x + G.r[4] * u0.y + G.r[5] * u0.z;
@@ -350,6 +404,108 @@ __device__ bool grid_from_parts(const ChainDev *cd, Grid *out, double *s_red, in
     return *s_ok != 0;
 }
 
+// u . (T - p x F) for the wrench S = (F, T) and the joint axis u through p
+__device__ __forceinline__ double axis_torque(const double4 &u, const double4 &p, const double *S)
+{
+    const double mx = S[3] - (p.y * S[2] - p.z * S[1]);
+    const double my = S[4] - (p.z * S[0] - p.x * S[2]);
+    const double mz = S[5] - (p.x * S[1] - p.y * S[0]);
+    return u.x * mx + u.y * my + u.z * mz;
+}
+__device__ __forceinline__ double joint_torque(const ChainDev *cd, int j, const double *S)
+{
+    return axis_torque(cd->jcur[2 * j], cd->jcur[2 * j + 1], S);
+}
+
+// The sum over the wave as a tree of neighbours, ((v0 + v1) + (v2 + v3)) + ...
+__device__ __forceinline__ double wave_tree_sum(double v)
+{
+    constexpr int QUAD_XOR1 = 0xb1, QUAD_XOR2 = 0x4e, ROW_HALF_MIRROR = 0x141, ROW_MIRROR = 0x140;
+    v += dpp<QUAD_XOR1>(v);
+    v += dpp<QUAD_XOR2>(v);
+    v += dpp<ROW_HALF_MIRROR>(v);
+    v += dpp<ROW_MIRROR>(v);
+    v = both_rows<false>(v) + both_rows<true>(v);
+    return both_halves<false>(v) + both_halves<true>(v);
+}
+
+// Wrench (F, r x F), energies and failure flag of atom a at r (zeros past the chain's end).
+__device__ __forceinline__ void atom_wrench(const ChainDev *cd, int a, double4 &r, double (&v)[WPART])
+{
+#pragma unroll
+    for (int k = 0; k < WPART; ++k) v[k] = 0.0;
+    r = make_double4(0, 0, 0, 0);
+    if (a < cd->n_atoms) {
+        const double inv_fix = 1.0 / FIX_SCALE;
+        const double4 fp = cd->f_pair[a];
+        const double Fx = fp.x + (double)cd->f_cav[3 * a] * inv_fix;
+        const double Fy = fp.y + (double)cd->f_cav[3 * a + 1] * inv_fix;
+        const double Fz = fp.z + (double)cd->f_cav[3 * a + 2] * inv_fix;
+        r = cd->r[a];
+        v[0] = Fx; v[1] = Fy; v[2] = Fz;
+        v[3] = r.y * Fz - r.z * Fy; v[4] = r.z * Fx - r.x * Fz; v[5] = r.x * Fy - r.y * Fx;
+        const double4 e = cd->e_atom[a];
+        v[6] = e.x; v[7] = e.y; v[8] = e.z;
+        v[9] = (isfinite(Fx) && isfinite(Fy) && isfinite(Fz)) ? 0.0 : 1.0;
+    }
+}
+
+// Over the wave: entries 0-5 (the wrench) become the inclusive suffix, this
+// atom and every later one; entries 6-9 (energies, flag) the sum, in every
+// lane, in the order in which lane 0 of such a suffix adds.
+__device__ __forceinline__ void wave_suffix(double (&S)[WPART])
+{
+    const int lane = threadIdx.x & (WAVE - 1);
+#pragma unroll
+    for (int d = 1; d < WAVE; d <<= 1) {
+#pragma unroll
+        for (int k = 0; k < 6; ++k) {
+            const double y = from_above(S[k], d);
+            if (lane + d < WAVE) S[k] += y;
+        }
+    }
+#pragma unroll
+    for (int k = 6; k < WPART; ++k) S[k] = wave_tree_sum(S[k]);
+}
+
+// Side-chain torque of the residue whose CB is atom a at r: the whole torque,
+// over HB1..HB3 (atoms a+1 .. a+3), about the CA->CB axis through CA.
+__device__ __forceinline__ double chi_torque(const ChainDev *cd, int a, const double4 &r)
+{
+    const double inv_fix = 1.0 / FIX_SCALE;
+    const double4 ca = cd->r[a - 2];
+    double ux = r.x - ca.x, uy = r.y - ca.y, uz = r.z - ca.z;
+    const double inv = 1.0 / sqrt(ux * ux + uy * uy + uz * uz);
+    ux *= inv; uy *= inv; uz *= inv;
+    double t = 0.0;
+    for (int h = 1; h <= 3; ++h) {
+        const int b = a + h;
+        const double4 fp = cd->f_pair[b], rb = cd->r[b];
+        const double Fx = fp.x + (double)cd->f_cav[3 * b] * inv_fix;
+        const double Fy = fp.y + (double)cd->f_cav[3 * b + 1] * inv_fix;
+        const double Fz = fp.z + (double)cd->f_cav[3 * b + 2] * inv_fix;
+        const double dx = rb.x - ca.x, dy = rb.y - ca.y, dz = rb.z - ca.z;
+        t += ux * (dy * Fz - dz * Fy) + uy * (dz * Fx - dx * Fz) + uz * (dx * Fy - dy * Fx);
+    }
+    return t;
+}
+
+// The compliance step of eq KCM_07 for the largest torque tm: dtheta = scale tau.
+__device__ __forceinline__ double step_scale(const ChainDev *cd, double tm)
+{
+    const double kappa = cd->kappa, smax = cd->max_step;
+    if (cd->step_rule == 1) return tm > 0.0 ? smax / tm : 0.0;
+    if (cd->step_rule == 2) return kappa;
+    return (kappa * tm > smax) ? smax / tm : kappa;
+}
+__device__ __forceinline__ double stepped_angle(double th, double d)
+{
+    double t = th + d;
+    if (t > PI_D) t -= 2.0 * PI_D;
+    if (t <= -PI_D) t += 2.0 * PI_D;
+    return t;
+}
+
 // ---------------------------------------------------------------------------
 // k_tau: joint torques of the pending forces, one thread per joint
 // ---------------------------------------------------------------------------
@@ -413,11 +569,7 @@ __global__ __launch_bounds__(JOINT_BLOCK) void k_tau(Batch bt)
     double tabs = 0.0, bad = 0.0;
     if (j < J) {
         const double *S = s_S[first_atom_of_joint(j) / ATOM_BLOCK - blo];
-        const double4 u = cd->jcur[2 * j], p = cd->jcur[2 * j + 1];
-        const double mx = S[3] - (p.y * S[2] - p.z * S[1]);
-        const double my = S[4] - (p.z * S[0] - p.x * S[2]);
-        const double mz = S[5] - (p.x * S[1] - p.y * S[0]);
-        const double t = cd->tau[j] + (u.x * mx + u.y * my + u.z * mz);
+        const double t = cd->tau[j] + joint_torque(cd, j, S);
         cd->tau[j] = t;
         if (!isfinite(t)) bad = 1.0;
         if (cd->mask[j]) tabs = fabs(t);
@@ -488,19 +640,12 @@ __global__ __launch_bounds__(JOINT_BLOCK) void k_stepfk(Batch bt, int mode)
             }
             return;
         }
-        const double kappa = cd->kappa, smax = cd->max_step;
-        double scale;
-        if (cd->step_rule == 1) scale = tm > 0.0 ? smax / tm : 0.0;
-        else if (cd->step_rule == 2) scale = kappa;
-        else scale = (kappa * tm > smax) ? smax / tm : kappa;
+        const double scale = step_scale(cd, tm);
         if (valid) {
             const double d = cd->mask[j] ? scale * cd->tau[j] : 0.0;
             cd->dtheta[j] = d;
-            double t = th + d;
-            if (t > PI_D) t -= 2.0 * PI_D;
-            if (t <= -PI_D) t += 2.0 * PI_D;
-            th = t;
-            cd->theta[j] = t;
+            th = stepped_angle(th, d);
+            cd->theta[j] = th;
         }
         if (lead) {
             // max |dtheta| over the moving joints is scale * max |tau| exactly
@@ -526,7 +671,7 @@ __global__ __launch_bounds__(JOINT_BLOCK) void k_stepfk(Batch bt, int mode)
     if (valid) x = joint_xf_of(cd->joint0[2 * j], cd->joint0[2 * j + 1], th);
 #pragma unroll
     for (int d = 1; d < WAVE; d <<= 1) {
-        Xf y = xf_shfl_up(x, d);
+        Xf y = xf_from_below(x, d);
         if (lane >= d) x = xf_mul(y, x);
     }
     if (lane == WAVE - 1) xf_store(s_x[w], x);
@@ -538,6 +683,35 @@ __global__ __launch_bounds__(JOINT_BLOCK) void k_stepfk(Batch bt, int mode)
     }
     if (valid) xf_store(cd->xform_loc + 12 * j, x);
     if (tid == min(J - jb * JOINT_BLOCK, JOINT_BLOCK) - 1) xf_store(cd->blk_xf + 12 * jb, x);
+}
+
+// Position of atom a with zero position q under its link transform L.
+__device__ __forceinline__ double4 placed_atom(const ChainDev *cd, int a, double4 q, const double *L)
+{
+    const int res = a / APR, slot = a - res * APR;
+    if (cd->n_chi && slot >= 5 && slot <= 7) {
+        // side-chain joint chi of the residue (dihedral N-CA-CB-HB1, 60
+        // degrees in the zero position): HB1..HB3 turn about CA->CB, here
+        // in the zero-position frame before the link transform
+        const double4 ca = cd->r0[res * APR + 2], cb = cd->r0[res * APR + 4];
+        double ux = cb.x - ca.x, uy = cb.y - ca.y, uz = cb.z - ca.z;
+        const double inv = 1.0 / sqrt(ux * ux + uy * uy + uz * uz);
+        ux *= inv; uy *= inv; uz *= inv;
+        double sn, cs;
+        sincos(cd->theta[cd->n_joints + res] - PI_D / 3.0, &sn, &cs);
+        const double vx = q.x - cb.x, vy = q.y - cb.y, vz = q.z - cb.z;
+        const double dot = ux * vx + uy * vy + uz * vz;
+        const double wx = uy * vz - uz * vy, wy = uz * vx - ux * vz, wz = ux * vy - uy * vx;
+        q.x = cb.x + vx * cs + wx * sn + ux * dot * (1.0 - cs);
+        q.y = cb.y + vy * cs + wy * sn + uy * dot * (1.0 - cs);
+        q.z = cb.z + vz * cs + wz * sn + uz * dot * (1.0 - cs);
+    }
+    double4 r;
+    r.x = L[0] * q.x + L[1] * q.y + L[2] * q.z + L[9];
+    r.y = L[3] * q.x + L[4] * q.y + L[5] * q.z + L[10];
+    r.z = L[6] * q.x + L[7] * q.y + L[8] * q.z + L[11];
+    r.w = 0.0;
+    return r;
 }
 
 // ---------------------------------------------------------------------------
@@ -569,7 +743,7 @@ __global__ __launch_bounds__(ATOM_BLOCK) void k_place(Batch bt, int mode)
             Xf x = (base + lane < jb_hi) ? xf_load(cd->blk_xf + 12 * (base + lane)) : xf_identity();
 #pragma unroll
             for (int d = 1; d < WAVE; d <<= 1) {
-                Xf y = xf_shfl_up(x, d);
+                Xf y = xf_from_below(x, d);
                 if (lane >= d) x = xf_mul(y, x);
             }
             if (base > 0) x = xf_mul(acc, x);
@@ -593,10 +767,7 @@ __global__ __launch_bounds__(ATOM_BLOCK) void k_place(Batch bt, int mode)
         }
         xf_store(s_G[t], G);
         const int fa = first_atom_of_link(l);
-        if (fa >= a0 && fa <= a1) {
-            if (l == 0) xf_store(cd->xform, G);
-            else fk_emit(G, l - 1, cd->joint0, cd->xform, cd->jcur);
-        }
+        if (l > 0 && fa >= a0 && fa <= a1) fk_emit(G, l - 1, cd->joint0[2 * (l - 1)], cd->joint0[2 * (l - 1) + 1], cd->jcur);
     }
     __syncthreads();
 
@@ -604,31 +775,7 @@ __global__ __launch_bounds__(ATOM_BLOCK) void k_place(Batch bt, int mode)
     double lo[3] = {DBL_MAX, DBL_MAX, DBL_MAX}, hi[3] = {-DBL_MAX, -DBL_MAX, -DBL_MAX};
     bool fin = true;
     if (a <= a1) {
-        const double *L = s_G[link_of_atom(a) - l_lo];
-        double4 q = cd->r0[a];
-        const int res = a / APR, slot = a - res * APR;
-        if (cd->n_chi && slot >= 5 && slot <= 7) {
-            // side-chain joint chi of the residue (dihedral N-CA-CB-HB1, 60
-            // degrees in the zero position): HB1..HB3 turn about CA->CB, here
-            // in the zero-position frame before the link transform
-            const double4 ca = cd->r0[res * APR + 2], cb = cd->r0[res * APR + 4];
-            double ux = cb.x - ca.x, uy = cb.y - ca.y, uz = cb.z - ca.z;
-            const double inv = 1.0 / sqrt(ux * ux + uy * uy + uz * uz);
-            ux *= inv; uy *= inv; uz *= inv;
-            double sn, cs;
-            sincos(cd->theta[cd->n_joints + res] - PI_D / 3.0, &sn, &cs);
-            const double vx = q.x - cb.x, vy = q.y - cb.y, vz = q.z - cb.z;
-            const double dot = ux * vx + uy * vy + uz * vz;
-            const double wx = uy * vz - uz * vy, wy = uz * vx - ux * vz, wz = ux * vy - uy * vx;
-            q.x = cb.x + vx * cs + wx * sn + ux * dot * (1.0 - cs);
-            q.y = cb.y + vy * cs + wy * sn + uy * dot * (1.0 - cs);
-            q.z = cb.z + vz * cs + wz * sn + uz * dot * (1.0 - cs);
-        }
-        double4 r;
-        r.x = L[0] * q.x + L[1] * q.y + L[2] * q.z + L[9];
-        r.y = L[3] * q.x + L[4] * q.y + L[5] * q.z + L[10];
-        r.z = L[6] * q.x + L[7] * q.y + L[8] * q.z + L[11];
-        r.w = 0.0;
+        const double4 r = placed_atom(cd, a, cd->r0[a], s_G[link_of_atom(a) - l_lo]);
         cd->r[a] = r;
         fin = isfinite(r.x) && isfinite(r.y) && isfinite(r.z);
         if (mode == MODE_ITER) {
@@ -1127,6 +1274,383 @@ __global__ __launch_bounds__(ATOM_BLOCK) void k_rank(Batch bt)
     const int e = key + 1 < nc ? cd->cell_local[key + 1] + s_off[(key + 1) / SCAN_CHUNK] : s_off[nb];
     // the first atom of each cell returns its count to zero for the next iteration
     if (place_sorted(cd, cd->s_tmp, a, b, e) == 0) cd->cell_count[key] = 0;
+}
+
+// ---------------------------------------------------------------------------
+// k_chain: everything of an iteration but the force kernel, one workgroup per
+// chain, for calls of short or many chains (set_form in kcm_host.cpp)
+// ---------------------------------------------------------------------------
+// The same work as k_wrench, k_tau, k_stepfk, k_place, k_cellkey, k_cellscan,
+// k_scatter and k_rank (and of k_gridboot and k_finish), with the same
+// arithmetic in the same order -- scans and sums in blocks of 256 joints or
+// atoms -- so a chain's results do not depend on which form a call takes.
+// What those kernels hand over through memory and a launch boundary stays in
+// LDS and registers here: link transforms, torques, cell counts (16 bits
+// each: at most CHAIN_ATOMS atoms) and the scatter.  Order within a call:
+// MODE_ITER applies the forces of the iteration before it, if they are
+// pending, and prepares the force kernel's inputs; MODE_FINAL applies the last
+// ones and ends the call; MODE_TAU leaves torques and energies only.
+// The conditions that end the kernel early are the same for all threads, so
+// every barrier is reached by all of them.
+// What bounds it is latency: of about 34,500 cycles for a chain of 150 atoms
+// the wrenches with the wait for the last forces take 7,000, the transform
+// scan 5,500, the grid 2,600, the sorted arrays 2,800; with LDS permutes for
+// every lane move it took 39,200.  15.3 us in place of 47 us for the eight
+// kernels it replaces, 43 us with them in one graph.  Workgroups of 768
+// threads at most: 1,024 would leave 128 registers and spill 80.
+template <int NT, bool ONE>
+__global__ __launch_bounds__(NT) void k_chain(Batch bt, int mode)
+{
+    static_assert(JOINT_BLOCK == ATOM_BLOCK && NT % ATOM_BLOCK == 0, "blocks of one size");
+    constexpr int NW = NT / WAVE, WPB = ATOM_BLOCK / WAVE;  // waves, waves per block
+    extern __shared__ __align__(16) unsigned char s_dyn[];
+    __shared__ double s_red[NW][12];
+    __shared__ double s_blk[CHAIN_JBLOCKS][12], s_carry[CHAIN_JBLOCKS][12];
+    __shared__ double s_tm[NW];
+    __shared__ int s_bad[NW], s_scan[NW];
+    __shared__ int s_flag;
+    __shared__ Grid s_g;
+
+    ChainDev *cd = bt.table[blockIdx.x];
+    ChainStats *st = cd->stats;
+    const int tid = threadIdx.x, lane = tid & (WAVE - 1), w = tid / WAVE;
+    const int grp = tid / ATOM_BLOCK, gt = tid & (ATOM_BLOCK - 1), w0 = w & ~(WPB - 1);  // block in the pass, its first wave
+    const bool lead = tid == 0;
+    const int n = cd->n_atoms, J = cd->n_joints, n_chi = cd->n_chi;
+    const int nblk = (n + ATOM_BLOCK - 1) / ATOM_BLOCK, njb = cd->n_bb_blocks;
+    // flags and limits, read by every thread before any of them is written
+    const bool active = st->active, pending = active && st->pending_post, fresh = st->need_grid;
+    const bool grid_bad = st->grid_bad;
+    const double tol = st->tol;
+    const int64_t it1 = st->iterations + 1, it_limit = st->iter_limit;
+    const int overflow = st->nbr_overflow;
+    int go = st->run;
+    // a thread with one atom and one joint takes what it needs of them now, all
+    // loads in flight together, and keeps it
+    double4 r0_1 = {}, ap_1 = {}, u0_1 = {}, p0_1 = {}, uc_1 = {}, pc_1 = {};
+    double th_1 = 0.0;
+    bool free_1 = false;
+    if (ONE) {
+        if (tid < n) {
+            r0_1 = cd->r0[tid];
+            ap_1 = cd->aparam[tid];
+        }
+        if (tid < J) {
+            u0_1 = cd->joint0[2 * tid];
+            p0_1 = cd->joint0[2 * tid + 1];
+            uc_1 = cd->jcur[2 * tid];
+            pc_1 = cd->jcur[2 * tid + 1];
+        }
+        if (tid < J + n_chi) {
+            th_1 = cd->theta[tid];
+            free_1 = cd->mask[tid];
+        }
+    }
+    __syncthreads();
+    if (mode == MODE_TAU && !pending) return;
+    if (!active) {
+        if (lead) {
+            st->pending_post = 0;
+            if (mode == MODE_FINAL) st->active = running(st);
+        }
+        return;
+    }
+
+    double tm = 0.0;
+    if (pending) {
+        // wrenches and torques: s_tau[j] first holds the part of tau_j from the
+        // atom block of j's first downstream atom, s_part the block sums
+        double *s_tau = reinterpret_cast<double *>(s_dyn);
+        double(*s_part)[WPART] = reinterpret_cast<double(*)[WPART]>(s_tau + J + n_chi);
+        for (int lb0 = 0; lb0 < nblk; lb0 += NT / ATOM_BLOCK) {
+            const int lb = lb0 + grp, a = lb * ATOM_BLOCK + gt;
+            double4 r;
+            double S[WPART];
+            atom_wrench(cd, a, r, S);
+            wave_suffix(S);
+            if (!ONE) __syncthreads();  // the last pass has read s_red
+            if (lane == 0)
+#pragma unroll
+                for (int k = 0; k < WPART; ++k) s_red[w][k] = S[k];
+            __syncthreads();
+#pragma unroll
+            for (int k = 0; k < 6; ++k) {
+                double t = 0.0;
+                for (int i = w + 1; i < w0 + WPB; ++i) t += s_red[i][k];
+                S[k] += t;
+            }
+            if (a < n) {
+                const int res = a / APR, slot = a - res * APR;
+                if (slot == 4 && n_chi) s_tau[J + res] = chi_torque(cd, a, r);
+                if (slot == 2 || slot == 8) {
+                    const int j = 2 * res + (slot == 8 ? 1 : 0);
+                    s_tau[j] = joint_torque(cd, j, S);
+                }
+            }
+            if (gt < WPART && lb < nblk) {
+                double t = 0.0;
+#pragma unroll
+                for (int i = 0; i < WPB; ++i) t += s_red[w0 + i][gt];
+                s_part[lb][gt] = t;
+            }
+        }
+        __syncthreads();
+        int bad = 0;
+        for (int j0 = 0; j0 < J; j0 += NT) {
+            const int j = j0 + tid, jlo = j - gt;
+            if (jlo + (w - w0) * WAVE < J) {  // the wave holds a joint
+                const int jhi = min(J, jlo + JOINT_BLOCK) - 1, bhi = first_atom_of_joint(jhi) / ATOM_BLOCK;
+                // wrench of the atom blocks after bhi, then of those down to j's
+                double S[6] = {0, 0, 0, 0, 0, 0};
+                if (bhi + 1 < nblk) {
+                    static_assert(CHAIN_ATOMS <= ATOM_BLOCK * WAVE, "later blocks fit one wave");
+                    const int b = bhi + 1 + lane;
+#pragma unroll
+                    for (int k = 0; k < 6; ++k) S[k] = wave_sum(b < nblk ? s_part[b][k] : 0.0);
+                }
+                if (j < J) {
+                    for (int b = bhi; b > first_atom_of_joint(j) / ATOM_BLOCK; --b)
+#pragma unroll
+                        for (int k = 0; k < 6; ++k) S[k] += s_part[b][k];
+                    const double t = s_tau[j] + (ONE ? axis_torque(uc_1, pc_1, S) : joint_torque(cd, j, S));
+                    s_tau[j] = t;
+                    cd->tau[j] = t;
+                    if (!isfinite(t)) bad = 1;
+                    if (ONE ? free_1 : cd->mask[j]) tm = fmax(tm, fabs(t));
+                }
+            }
+        }
+        for (int j = tid; j < J + n_chi; j += NT) {
+            if (j < J) continue;
+            const double t = s_tau[j];
+            cd->tau[j] = t;
+            if (!isfinite(t)) bad = 1;
+            if (ONE ? free_1 : cd->mask[j]) tm = fmax(tm, fabs(t));
+        }
+        tm = wave_max(tm);
+        if (lane == 0) s_tm[w] = tm;
+        bad = __any(bad);
+        if (w == 0) {
+            // energies and the non-finite force flag of the pending forces
+            double E[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) E[k] = wave_sum(lane < nblk ? s_part[lane][6 + k] : 0.0);
+            if (lead) {
+                st->e_elec = E[0];
+                st->e_vdw = E[1];
+                st->e_cav = E[2];
+                st->post_bad = E[3] > 0.0 ? 1 : 0;
+            }
+            bad = bad || E[3] > 0.0;
+        }
+        if (lane == 0) s_bad[w] = bad;
+        __syncthreads();
+        if (mode == MODE_TAU) return;
+        bad = 0;
+#pragma unroll
+        for (int i = 0; i < NW; ++i) {
+            tm = fmax(tm, s_tm[i]);
+            bad |= s_bad[i];
+        }
+        if (bad) {
+            if (lead) {
+                st->status = -4;
+                st->run = 0;
+                st->pending_post = 0;
+                st->active = 0;
+            }
+            return;
+        }
+        const double scale = step_scale(cd, tm), mxd = scale * tm;
+        for (int j = tid; j < J + n_chi; j += NT) {
+            const double d = (ONE ? free_1 : cd->mask[j]) ? scale * s_tau[j] : 0.0;
+            cd->dtheta[j] = d;
+            th_1 = stepped_angle(ONE ? th_1 : cd->theta[j], d);
+            cd->theta[j] = th_1;
+        }
+        const bool conv = tol > 0.0 && mxd < tol;
+        go = !conv && it1 < it_limit;
+        if (lead) {
+            st->max_tau = tm;
+            st->max_dtheta = mxd;
+            st->iterations = it1;
+            if (overflow) st->status = -6;
+            if (conv) st->converged = 1;
+            st->run = go;
+        }
+    } else if (mode == MODE_ITER) {
+        go = 1;
+        if (lead) st->run = 1;
+    }
+    const bool on = go && !grid_bad;
+    if (mode == MODE_FINAL || !on) {
+        if (lead) {
+            st->pending_post = 0;
+            st->active = on;
+        }
+        return;
+    }
+    __syncthreads();  // s_tau is read, the angles are written
+
+    // forward kinematics: s_G[j + 1] = T_jlo o ... o T_j inside each joint
+    // block, then the products of the earlier blocks in front
+    double(*s_G)[12] = reinterpret_cast<double(*)[12]>(s_dyn);
+    for (int j0 = 0; j0 < J; j0 += NT) {
+        const int j = j0 + tid, jb = j / JOINT_BLOCK;
+        const bool holds = j - lane < J;  // the wave holds a joint
+        Xf x = xf_identity();
+        if (holds) {
+            if (j < J) {
+                if (!ONE) {
+                    u0_1 = cd->joint0[2 * j];
+                    p0_1 = cd->joint0[2 * j + 1];
+                    th_1 = cd->theta[j];
+                }
+                x = joint_xf_of(u0_1, p0_1, th_1);
+            }
+#pragma unroll
+            for (int d = 1; d < WAVE; d <<= 1) {
+                Xf y = xf_from_below(x, d);
+                if (lane >= d) x = xf_mul(y, x);
+            }
+            if (lane == WAVE - 1) xf_store(s_red[w], x);
+        }
+        __syncthreads();
+        if (holds) {
+            if (w > w0) {
+                Xf pre = xf_load(s_red[w0]);
+                for (int i = w0 + 1; i < w; ++i) pre = xf_mul(pre, xf_load(s_red[i]));
+                x = xf_mul(pre, x);
+            }
+            if (j < J) xf_store(s_G[j + 1], x);
+            if (j == min(J, (jb + 1) * JOINT_BLOCK) - 1) xf_store(s_blk[jb], x);
+        }
+        if (!ONE) __syncthreads();
+    }
+    __syncthreads();
+    if (w == 0) {
+        if (lane == 0) xf_store(s_carry[0], xf_identity());
+        if (njb > 1) {
+            Xf x = lane < njb - 1 ? xf_load(s_blk[lane]) : xf_identity();
+            static_assert(CHAIN_JBLOCKS <= 8, "carries of at most eight blocks");
+#pragma unroll
+            for (int d = 1; d < 8; d <<= 1) {
+                Xf y = xf_from_below(x, d);
+                if (lane >= d) x = xf_mul(y, x);
+            }
+            if (lane < njb - 1) xf_store(s_carry[lane + 1], x);
+        }
+    }
+    if (lead) xf_store(s_G[0], xf_identity());
+    __syncthreads();
+    for (int j = tid; j < J; j += NT) {
+        const Xf G = xf_mul(xf_load(s_carry[j / JOINT_BLOCK]), xf_load(s_G[j + 1]));
+        xf_store(s_G[j + 1], G);
+        fk_emit(G, j, ONE ? u0_1 : cd->joint0[2 * j], ONE ? p0_1 : cd->joint0[2 * j + 1], cd->jcur);
+    }
+    __syncthreads();
+
+    // positions and bounding box
+    double lo[3] = {DBL_MAX, DBL_MAX, DBL_MAX}, hi[3] = {-DBL_MAX, -DBL_MAX, -DBL_MAX};
+    bool fin = true;
+    double4 r1 = make_double4(0, 0, 0, 0);
+    for (int a = tid; a < n; a += NT) {
+        const double4 r = placed_atom(cd, a, ONE ? r0_1 : cd->r0[a], s_G[link_of_atom(a)]);
+        cd->r[a] = r;
+        if (ONE) r1 = r;
+        cd->f_cav[3 * a] = 0;
+        cd->f_cav[3 * a + 1] = 0;
+        cd->f_cav[3 * a + 2] = 0;
+        fin = fin && isfinite(r.x) && isfinite(r.y) && isfinite(r.z);
+        lo[0] = fmin(lo[0], r.x); lo[1] = fmin(lo[1], r.y); lo[2] = fmin(lo[2], r.z);
+        hi[0] = fmax(hi[0], r.x); hi[1] = fmax(hi[1], r.y); hi[2] = fmax(hi[2], r.z);
+    }
+#pragma unroll
+    for (int k = 0; k < 3; ++k) { lo[k] = wave_min(lo[k]); hi[k] = wave_max(hi[k]); }
+    fin = !__any(!fin);
+    if (lane == 0) {
+#pragma unroll
+        for (int k = 0; k < 3; ++k) { s_red[w][k] = lo[k]; s_red[w][3 + k] = hi[k]; }
+        s_bad[w] = fin ? 0 : 1;
+    }
+    __syncthreads();
+    if (lead) {
+        bool ok = true;
+        for (int i = 0; i < NW; ++i) {
+#pragma unroll
+            for (int k = 0; k < 3; ++k) { lo[k] = fmin(lo[k], s_red[i][k]); hi[k] = fmax(hi[k], s_red[i][3 + k]); }
+            ok = ok && !s_bad[i];
+        }
+        const Grid g = size_grid(cd, lo, hi, &ok);
+        s_flag = ok;
+        if (ok) {
+            s_g = g;
+            *cd->grid = g;
+        } else {
+            // a conformation that never had a grid stops the chain before its
+            // first iteration
+            st->status = -4;
+            if (fresh) st->run = 0;
+            else st->grid_bad = 1;
+            st->pending_post = 0;
+            st->active = 0;
+        }
+        st->need_grid = 0;
+    }
+    __syncthreads();
+    if (!s_flag) return;
+
+    // cell list: counts and starts two to a word
+    const int nc = s_g.n_cells, nword = (nc + 1) / 2;
+    unsigned *s_cell = reinterpret_cast<unsigned *>(s_dyn);
+    unsigned short *s_ids = reinterpret_cast<unsigned short *>(s_cell + cd->cap_cells / 2);
+    unsigned short *s_key = s_ids + n, *s_arr = s_key + n;  // unless each thread keeps its one atom's
+    for (int i = tid; i < nword; i += NT) s_cell[i] = 0;
+    __syncthreads();
+    int key1 = 0, arr1 = 0;
+    for (int a = tid; a < n; a += NT) {
+        const int key = cell_of(s_g, ONE ? r1 : cd->r[a]), sh = 16 * (key & 1);
+        const int arr = (int)((atomicAdd(&s_cell[key >> 1], 1u << sh) >> sh) & 0xffffu);
+        if (ONE) {
+            key1 = key;
+            arr1 = arr;
+        } else {
+            s_key[a] = (unsigned short)key;
+            s_arr[a] = (unsigned short)arr;
+        }
+    }
+    __syncthreads();
+    {
+        const int per = (nword + NT - 1) / NT, i0 = min(tid * per, nword), i1 = min(i0 + per, nword);
+        int sum = 0, total = 0;
+        for (int i = i0; i < i1; ++i) sum += (int)(s_cell[i] & 0xffffu) + (int)(s_cell[i] >> 16);
+        int run = block_excl_scan(sum, s_scan, &total);
+        for (int i = i0; i < i1; ++i) {
+            const unsigned v = s_cell[i];
+            s_cell[i] = (unsigned)run | ((unsigned)(run + (int)(v & 0xffffu)) << 16);
+            run += (int)(v & 0xffffu) + (int)(v >> 16);
+        }
+    }
+    __syncthreads();
+    auto start_of = [&](int c) -> int { return c < nc ? (int)((s_cell[c >> 1] >> (16 * (c & 1))) & 0xffffu) : n; };
+    for (int c = tid; c <= nc; c += NT) cd->cell_start[c] = start_of(c);
+    for (int a = tid; a < n; a += NT) s_ids[start_of(ONE ? key1 : s_key[a]) + (ONE ? arr1 : s_arr[a])] = (unsigned short)a;
+    __syncthreads();
+    for (int a = tid; a < n; a += NT) {
+        // the stable slot: the members of the cell with a smaller index before it
+        const int key = ONE ? key1 : s_key[a], b = start_of(key), e = start_of(key + 1);
+        int pos = b;
+        for (int s = b; s < e; ++s) pos += s_ids[s] < a ? 1 : 0;
+        const double4 r = ONE ? r1 : cd->r[a];
+        cd->s_idx[pos] = a;
+        cd->s_r[pos] = make_double4(r.x, r.y, r.z, __longlong_as_double((long long)a | ((long long)(a / APR) << 32)));
+        cd->s_p[pos] = ONE ? ap_1 : cd->aparam[a];
+    }
+    if (lead) {
+        // the force kernel follows: its forces await the next post phase
+        st->active = 1;
+        st->pending_post = 1;
+    }
 }
 
 // Loads, stores and atomics through a pointer of unknown address space are
@@ -2175,33 +2699,10 @@ __global__ __launch_bounds__(ATOM_BLOCK) void k_wrench(Batch bt)
     __shared__ double s_w[ATOM_BLOCK / WAVE][WPART];
     const int a = lb * ATOM_BLOCK + threadIdx.x;
     const int lane = threadIdx.x & (WAVE - 1), w = threadIdx.x / WAVE, nw = ATOM_BLOCK / WAVE;
-    double v[WPART] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-    double4 r = make_double4(0, 0, 0, 0);
-    if (a < cd->n_atoms) {
-        const double inv_fix = 1.0 / FIX_SCALE;
-        const double4 fp = cd->f_pair[a];
-        const double Fx = fp.x + (double)cd->f_cav[3 * a] * inv_fix;
-        const double Fy = fp.y + (double)cd->f_cav[3 * a + 1] * inv_fix;
-        const double Fz = fp.z + (double)cd->f_cav[3 * a + 2] * inv_fix;
-        r = cd->r[a];
-        v[0] = Fx; v[1] = Fy; v[2] = Fz;
-        v[3] = r.y * Fz - r.z * Fy; v[4] = r.z * Fx - r.x * Fz; v[5] = r.x * Fy - r.y * Fx;
-        const double4 e = cd->e_atom[a];
-        v[6] = e.x; v[7] = e.y; v[8] = e.z;
-        v[9] = (isfinite(Fx) && isfinite(Fy) && isfinite(Fz)) ? 0.0 : 1.0;
-    }
-    // inclusive suffix over the workgroup: this atom and every later one
+    double4 r;
     double S[WPART];
-#pragma unroll
-    for (int k = 0; k < WPART; ++k) S[k] = v[k];
-#pragma unroll
-    for (int d = 1; d < WAVE; d <<= 1) {
-#pragma unroll
-        for (int k = 0; k < WPART; ++k) {
-            const double y = __shfl_down(S[k], d, WAVE);
-            if (lane + d < WAVE) S[k] += y;
-        }
-    }
+    atom_wrench(cd, a, r, S);
+    wave_suffix(S);
     if (lane == 0)
         for (int k = 0; k < WPART; ++k) s_w[w][k] = S[k];
     __syncthreads();
@@ -2213,33 +2714,10 @@ __global__ __launch_bounds__(ATOM_BLOCK) void k_wrench(Batch bt)
     }
     if (a < cd->n_atoms) {
         const int res = a / APR, slot = a - res * APR;
-        if (slot == 4 && cd->n_chi) {
-            // side-chain joint of the residue: its whole torque, over HB1..HB3
-            // (atoms a+1 .. a+3), about the CA->CB axis through CA
-            const double inv_fix = 1.0 / FIX_SCALE;
-            const double4 ca = cd->r[a - 2];
-            double ux = r.x - ca.x, uy = r.y - ca.y, uz = r.z - ca.z;
-            const double inv = 1.0 / sqrt(ux * ux + uy * uy + uz * uz);
-            ux *= inv; uy *= inv; uz *= inv;
-            double t = 0.0;
-            for (int h = 1; h <= 3; ++h) {
-                const int b = a + h;
-                const double4 fp = cd->f_pair[b], rb = cd->r[b];
-                const double Fx = fp.x + (double)cd->f_cav[3 * b] * inv_fix;
-                const double Fy = fp.y + (double)cd->f_cav[3 * b + 1] * inv_fix;
-                const double Fz = fp.z + (double)cd->f_cav[3 * b + 2] * inv_fix;
-                const double dx = rb.x - ca.x, dy = rb.y - ca.y, dz = rb.z - ca.z;
-                t += ux * (dy * Fz - dz * Fy) + uy * (dz * Fx - dx * Fz) + uz * (dx * Fy - dy * Fx);
-            }
-            cd->tau[cd->n_joints + res] = t;
-        }
+        if (slot == 4 && cd->n_chi) cd->tau[cd->n_joints + res] = chi_torque(cd, a, r);
         if (slot == 2 || slot == 8) {
             const int j = 2 * res + (slot == 8 ? 1 : 0);
-            const double4 u = cd->jcur[2 * j], p = cd->jcur[2 * j + 1];
-            const double mx = S[3] - (p.y * S[2] - p.z * S[1]);
-            const double my = S[4] - (p.z * S[0] - p.x * S[2]);
-            const double mz = S[5] - (p.x * S[1] - p.y * S[0]);
-            cd->tau[j] = u.x * mx + u.y * my + u.z * mz;
+            cd->tau[j] = joint_torque(cd, j, S);
         }
     }
     if (threadIdx.x < WPART) {
@@ -2257,6 +2735,30 @@ hipError_t launch_tau(const Batch &b, hipStream_t s)
     if (b.total_jblocks <= 0) return hipSuccess;
     hipLaunchKernelGGL(k_tau, dim3(b.total_jblocks), dim3(JOINT_BLOCK), 0, s, b);
     return hipGetLastError();
+}
+
+template <int NT, bool ONE>
+static hipError_t launch_chain_form(const Batch &b, int mode, hipStream_t s)
+{
+    // the larger of the link transforms and the cell list
+    const int n = b.max_atoms, links = 2 * (n / APR) + 1;
+    const size_t lds = std::max(sizeof(double) * 12 * links, sizeof(uint16_t) * (size_t)(cell_capacity(n) + (ONE ? 1 : 3) * n));
+    if (lds > 65536) {
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_chain<NT, ONE>),
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, CHAIN_LDS);
+        if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL((k_chain<NT, ONE>), dim3(b.n_chains), dim3(NT), lds, s, b, mode);
+    return hipGetLastError();
+}
+
+hipError_t launch_chain(const Batch &b, int mode, hipStream_t s)
+{
+    if (b.n_chains <= 0) return hipSuccess;
+    if (b.max_atoms <= 256) return launch_chain_form<256, true>(b, mode, s);
+    if (b.max_atoms <= 512) return launch_chain_form<512, true>(b, mode, s);
+    if (b.max_atoms <= 768) return launch_chain_form<768, true>(b, mode, s);
+    return launch_chain_form<768, false>(b, mode, s);
 }
 
 hipError_t launch_stepfk(const Batch &b, int mode, hipStream_t s)
