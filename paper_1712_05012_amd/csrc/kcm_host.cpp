@@ -225,8 +225,8 @@ Layout make_layout(int m, int n_orb, int side_chains)
     };
     const size_t n = l.n, J = l.J, N = l.N, cap = l.cap;
     l.desc = take(sizeof(ChainDev));
-    l.stats = take(sizeof(ChainStats));
-    l.grid = take(sizeof(Grid));
+    l.stats = take(sizeof(ChainStats));  // STATS_OFFSET
+    l.grid = take(sizeof(Grid));         // GRID_OFFSET
     const size_t Jt = l.Jt;
     l.theta = take(8 * Jt);
     l.dtheta = take(8 * Jt);
@@ -481,7 +481,14 @@ kcm_status ensure_table(kcm_chain *const *chains, int n_chains, hipStream_t stre
         const size_t blk_pos = off_pos + ints;
         const size_t jblk_pos = blk_pos + ints;
         const size_t scan_pos = jblk_pos + ints;
-        const size_t need = scan_pos + sizeof(int32_t) * (n_chains + 1);
+        // the map of atoms to chains: groups of 16 atoms, larger ones where that
+        // would take more than 16,384 entries
+        long long atoms = 0;
+        for (int i = 0; i < n_chains; ++i) atoms += chains[i]->n;
+        int shift = 4;
+        while ((atoms >> shift) > 16384) ++shift;
+        const size_t map_pos = scan_pos + ints, n_map = (size_t)(atoms >> shift) + 1;
+        const size_t need = map_pos + sizeof(int32_t) * n_map;
         if (need > t->cap) {
             if (t->dev) {
                 HIP_TRY(hipStreamSynchronize(stream));
@@ -520,9 +527,16 @@ kcm_status ensure_table(kcm_chain *const *chains, int n_chains, hipStream_t stre
         blk[n_chains] = (int32_t)blocks;
         jblk[n_chains] = (int32_t)jblocks;
         sblk[n_chains] = (int32_t)sblocks;
+        int32_t *map = reinterpret_cast<int32_t *>(host.data() + map_pos);
+        for (size_t k = 0, c = 0; k < n_map; ++k) {
+            while (c + 1 < (size_t)n_chains && off[c + 1] <= (long long)(k << shift)) ++c;
+            map[k] = (int32_t)c;
+        }
         HIP_TRY(hipMemcpyAsync(t->dev, host.data(), need, hipMemcpyHostToDevice, stream));
         HIP_TRY(hipStreamSynchronize(stream));
         unsigned char *d = static_cast<unsigned char *>(t->dev);
+        t->batch.atom_chain = reinterpret_cast<const int32_t *>(d + map_pos);
+        t->batch.atom_chain_shift = shift;
         t->batch.table = reinterpret_cast<ChainDev *const *>(d);
         t->batch.atom_off = reinterpret_cast<const int32_t *>(d + off_pos);
         t->batch.blk_off = reinterpret_cast<const int32_t *>(d + blk_pos);
@@ -678,6 +692,7 @@ kcm_status kcm_build_chain(const kcm_chain_desc *desc, const kcm_params *params,
     if (!dev_mem || (reinterpret_cast<uintptr_t>(dev_mem) & 255)) return fail(KCM_E_INVAL, "dev_mem must be 256-byte aligned");
     const int m = desc->n_res;
     const Layout l = make_layout(m, params->n_orbits, desc->side_chains);
+    if (l.desc != 0 || l.stats != STATS_OFFSET || l.grid != GRID_OFFSET) return fail(KCM_E_STATE, "layout of flags and grid");
     if (bytes < l.total) return fail(KCM_E_NOMEM, "device block smaller than kcm_chain_bytes");
     if (!device_readable(dev_mem)) return fail(KCM_E_INVAL, "dev_mem must be device memory");
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);

@@ -120,6 +120,10 @@ struct ChainDev {
     ChainStats *stats;
 };
 
+// Where a chain's flags and grid lie behind its descriptor.
+constexpr int STATS_OFFSET = (sizeof(ChainDev) + 255) / 256 * 256;
+constexpr int GRID_OFFSET = STATS_OFFSET + (sizeof(ChainStats) + 255) / 256 * 256;
+
 // The chains of one call.  table: device array of device descriptors;
 // atom_off / blk_off / jblk_off: device arrays [n_chains+1] of cumulative atom
 // counts, of cumulative per-atom workgroup counts (ATOM_BLOCK atoms per
@@ -131,6 +135,10 @@ struct Batch {
     const int32_t *blk_off;
     const int32_t *jblk_off;
     const int32_t *scan_off;  // cumulative count of SCAN_CHUNK-cell chunks of the chains' capacities
+    // chain of atom i << atom_chain_shift of the launch, or null (the force
+    // kernel then searches atom_off)
+    const int32_t *atom_chain;
+    int atom_chain_shift;
     int n_chains;
     int total_atoms;
     int total_blocks;

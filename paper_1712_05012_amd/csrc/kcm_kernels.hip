@@ -96,6 +96,9 @@ __device__ __forceinline__ double from_above(double x, int d)
     if (d == 32) return both_halves<true>(x);
     return __shfl_down(x, d, WAVE);
 }
+// the lanes where p holds (from the compare's own mask, where the library's
+// ballot goes through a 0/1 register and a second compare)
+__device__ __forceinline__ unsigned long long ballot(bool p) { return __builtin_amdgcn_ballot_w64(p); }
 // op over the wave in every lane, as the butterfly over lane distances 32, 16,
 // ..., 1 takes it: below 16 the values repeat with the last distance inside a
 // row, so a rotation by half of it brings the partner's
@@ -1217,6 +1220,20 @@ __device__ void chunk_offsets(const ChainDev *cd, int nc, int *s_off, int *s_int
     __syncthreads();
 }
 
+// Parameters of an atom as the cell-ordered array s_p holds them: (q, R,
+// sqrt(eps), R_off) in FP64, or, for a chain of the mixed form, the first three
+// as the FP32 values its pair terms use in the first 16 bytes.  Either way
+// R_off is the last double.
+__device__ __forceinline__ double4 sorted_param(const ChainDev *cd, double4 p)
+{
+    if (cd->precision == 1) {
+        p.x = __hiloint2double(__float_as_int((float)p.y), __float_as_int((float)p.x));
+        p.y = __hiloint2double(0, __float_as_int((float)p.z));
+        p.z = 0.0;
+    }
+    return p;
+}
+
 // Slot of atom a in the cell-ordered arrays: the counting-sort scatter placed
 // the atoms of a cell in the order of their count atomics; the stable slot is
 // the number of atoms of the cell with a smaller index, so everything
@@ -1239,7 +1256,7 @@ __device__ __forceinline__ int place_sorted(const ChainDev *cd, const int *ids, 
     const double4 r = cd->r[a];
     cd->s_idx[pos] = a;
     cd->s_r[pos] = make_double4(r.x, r.y, r.z, __longlong_as_double((long long)a | ((long long)(a / APR) << 32)));
-    cd->s_p[pos] = cd->aparam[a];
+    cd->s_p[pos] = sorted_param(cd, cd->aparam[a]);
     return rank;
 }
 
@@ -1705,7 +1722,7 @@ __global__ __launch_bounds__(NT) void k_chain(Batch bt, int mode)
         const double4 r = ONE ? r1 : cd->r[a];
         cd->s_idx[pos] = a;
         cd->s_r[pos] = make_double4(r.x, r.y, r.z, __longlong_as_double((long long)a | ((long long)(a / APR) << 32)));
-        cd->s_p[pos] = ONE ? ap_1 : cd->aparam[a];
+        cd->s_p[pos] = sorted_param(cd, ONE ? ap_1 : cd->aparam[a]);
     }
     if (lead) {
         // the force kernel follows: its forces await the next post phase
@@ -1745,6 +1762,24 @@ struct NbrEntry {
     Real ax, ay, az, c0;
 };
 
+// One atom's parameters from s_p, at a byte offset.
+template <typename Real>
+struct AtomPar {
+    Real q, R, se;
+    double roff;
+};
+template <typename Real> __device__ __forceinline__ AtomPar<Real> load_par(gptr<const char> sp, unsigned ob);
+template <> __device__ __forceinline__ AtomPar<float> load_par<float>(gptr<const char> sp, unsigned ob)
+{
+    const float4 f = *(const gptr<const float4>)(sp + ob);
+    return {f.x, f.y, f.z, *(const gptr<const double>)(sp + ob + 24)};
+}
+template <> __device__ __forceinline__ AtomPar<double> load_par<double>(gptr<const char> sp, unsigned ob)
+{
+    const double4 p = *(const gptr<const double4>)(sp + ob);
+    return {p.x, p.y, p.z, p.w};
+}
+
 // Squared distance and cap threshold of a candidate, with the fused steps
 // written out: every path and launch shape that takes them rounds alike.
 __device__ __forceinline__ double dist2(double dx, double dy, double dz)
@@ -1767,7 +1802,7 @@ constexpr int SPL = 4;                              // samples per lane in one p
 // Neighbours whose cap on the offset sphere is large (cosine of its angular
 // radius, c0/|a|, below CAP_SPLIT) lead the list: step 1 then reaches two
 // overlappers for every sample of a slot early and stops there.
-constexpr double CAP_SPLIT = 0.6;
+constexpr float CAP_SPLIT = 0.6f;
 // Launch shapes of the force kernel (kcm_set_force_variant): candidates each
 // lane loads per trip of the candidate loop (CPT), the neighbours step 1
 // reads as one block before it checks the slots' saturation (SATB), and the
@@ -1914,7 +1949,7 @@ __device__ __noinline__ PairSums pair_terms_fp64(CDev cd, int si, int off, int r
 {
     const int lane = threadIdx.x & (WAVE - 1);
     const double4 ri = glob(cd->s_r)[si];
-    const double4 pa = glob(cd->s_p)[si];
+    const double4 pa = glob(cd->aparam)[(int)__double_as_longlong(ri.w)];
     const double cut2 = cd->cutoff * cd->cutoff;
     const bool do_elec = terms & 1, do_vdw = terms & 2;
     PairSums out = {{0.0, 0.0, 0.0}, {0.0, 0.0}};
@@ -1932,10 +1967,10 @@ __device__ __noinline__ PairSums pair_terms_fp64(CDev cd, int si, int off, int r
         const bool ok = k < T && sj != si;
         if (k >= T) sj = si;
         const double4 rj = glob(cd->s_r)[sj];
-        const double4 pj = glob(cd->s_p)[sj];
         const double ddx = rj.x - ri.x, ddy = rj.y - ri.y, ddz = rj.z - ri.z;
         const double d2 = dist2(ddx, ddy, ddz);
         if (!(ok && d2 <= cut2)) continue;
+        const double4 pj = glob(cd->aparam)[(int)__double_as_longlong(rj.w)];
         const long long wj = __double_as_longlong(rj.w);
         const int aj = (int)wj, res_j = (int)(wj >> 32), dres = res_j - res_i;
         double we = do_elec ? 1.0 : 0.0, wv = do_vdw ? 1.0 : 0.0;
@@ -2025,7 +2060,7 @@ __device__ __noinline__ ChunkedSasa sasa_chunked(CDev cd, const ChunkArgs c, Nbr
             const double d2 = dist2(ddx, ddy, ddz);
             const double lim = a.roff_i + pj.w + a.dr;
             const bool in_cav = valid && d2 <= lim * lim;
-            const unsigned long long m = __ballot(in_cav);
+            const unsigned long long m = ballot(in_cav);
             if (in_cav) {
                 const int pos = nb + count_below(m) - lo;
                 if (pos >= 0 && pos < len) {
@@ -2079,7 +2114,7 @@ __device__ __noinline__ ChunkedSasa sasa_chunked(CDev cd, const ChunkArgs c, Nbr
                 if (MIXED) {
                     // a test within the band of its threshold: the whole wave
                     // recounts that sample in FP64, one lane per neighbour
-                    unsigned long long bm = __ballot(kb + lane + WAVE * i < a.N && amin[i] <= (Real)MIXED_BAND);
+                    unsigned long long bm = ballot(kb + lane + WAVE * i < a.N && amin[i] <= (Real)MIXED_BAND);
                     while (bm) {
                         const int l = __ffsll((long long)bm) - 1;
                         bm &= bm - 1;
@@ -2129,7 +2164,7 @@ __device__ __noinline__ ChunkedSasa sasa_chunked(CDev cd, const ChunkArgs c, Nbr
                     }
                 }
                 // exposed samples: one lane per neighbour, the samples broadcast
-                const unsigned long long em0 = __ballot(valid && cnt[i] == 0);
+                const unsigned long long em0 = ballot(valid && cnt[i] == 0);
                 if (!em0) continue;
                 for (int v = 0; WAVE * v < len; ++v) {
                     const int u = lane + WAVE * v;
@@ -2196,15 +2231,36 @@ __global__ __launch_bounds__(WAVE, sizeof(Real) == 4 ? 6 : 4) void k_force(Batch
         const int x = blockIdx.x % N_XCD, k = blockIdx.x / N_XCD;
         atom = x * nq + min(x, nr) + k;
     }
-    const int c = find_block_owner(bt.atom_off, bt.n_chains, atom);
+    // the atom's chain: from the map of the batch, the chain of the first atom
+    // of each group and a step per chain border in it (two dependent loads
+    // where a binary search over 256 chains takes nine)
+    int c = 0;
+    if (bt.n_chains > 1) {
+        if (bt.atom_chain) {
+            c = bt.atom_chain[atom >> bt.atom_chain_shift];
+            while (bt.atom_off[c + 1] <= atom) ++c;
+        } else {
+            c = find_block_owner(bt.atom_off, bt.n_chains, atom);
+        }
+    }
     const CDev cd = glob(glob(bt.table)[c]);
-    if (!running(cd->stats)) return;
     const int si = atom - bt.atom_off[c];
     const int lane = threadIdx.x;
 
-    const Grid g = *glob(cd->grid);
-    const double4 ri = glob(cd->s_r)[si];
-    const double4 pi = glob(cd->s_p)[si];
+    // flags and grid lie at fixed places behind the descriptor, and their loads
+    // are issued with those of its pointers: the empty asm uses all of them
+    // before the first branch (the compiler otherwise moves each behind it,
+    // one wait after the other)
+    const gptr<const ChainStats> st = (gptr<const ChainStats>)((gptr<const char>)cd + STATS_OFFSET);
+    const Grid g = *(gptr<const Grid>)((gptr<const char>)cd + GRID_OFFSET);
+    int run = st->run;
+    const int bad = st->grid_bad;
+    const gptr<const char> sr = (gptr<const char>)glob(cd->s_r), sp = (gptr<const char>)glob(cd->s_p);
+    asm("" : "+s"(run) : "s"(bad), "s"(sr), "s"(sp), "s"(si), "s"(g.origin[0]), "s"(g.origin[1]), "s"(g.origin[2]),
+                 "s"(g.cell), "s"(g.inv_cell), "s"(g.reach_len), "s"(g.dims[0]), "s"(g.dims[1]), "s"(g.dims[2]), "s"(g.reach));
+    if (!run || bad) return;
+    const double4 ri = *(const gptr<const double4>)(sr + (unsigned)si * (unsigned)sizeof(double4));
+    const AtomPar<Real> pi = load_par<Real>(sp, (unsigned)si * (unsigned)sizeof(double4));
     const int ai = (int)__double_as_longlong(ri.w);
     const int dxn = g.dims[0], dyn = g.dims[1], dzn = g.dims[2];
     // the atom's cell, by the expression that sorted it (no key decoding)
@@ -2264,12 +2320,12 @@ __global__ __launch_bounds__(WAVE, sizeof(Real) == 4 ? 6 : 4) void k_force(Batch
     const bool do_elec = terms & 1, do_vdw = terms & 2, do_cav = terms & 4;
     const bool do_pair = do_elec || do_vdw;
     const double cut2 = cd->cutoff * cd->cutoff;
-    const double roff_i = pi.w;
+    const double roff_i = pi.roff;
     const double inv_2roff = 0.5 / roff_i;
     const double dr = cd->delta_r;
     const int res_i = ai / APR, slot_i = ai - res_i * APR;
     const Real coul = (Real)cd->coulomb;
-    const Real qi = (Real)pi.x, Ri = (Real)pi.y, sei = (Real)pi.z;
+    const Real qi = pi.q, Ri = pi.R, sei = pi.se;
 
     // Bond class of each atom of residues res_i - 1 .. res_i + 1 relative to
     // atom i, two bits per atom (0 none, 1 1-2, 2 1-3, 3 1-4), and the pair
@@ -2282,28 +2338,32 @@ __global__ __launch_bounds__(WAVE, sizeof(Real) == 4 ? 6 : 4) void k_force(Batch
     __builtin_amdgcn_wave_barrier();
 
     // Sorted atom of candidate kw + lane, one window of 64 candidates at a
-    // time, windows in increasing order.  Each non-empty row starting inside
-    // the window leaves (its first candidate number, rbase) at that position
-    // of an LDS table; a candidate's row is the last start at or before it,
-    // read from the wave's mask of starts, or else the row running on from
-    // the previous window.  The table lives in the event array, which is
-    // free until the candidates are done; an entry left by an earlier window
-    // never matches, since it holds that window's candidate number.
-    int2 *s_head = reinterpret_cast<int2 *>(s_ev01);
-    s_head[lane] = make_int2(-1, 0);
-    int carry = 0;
+    // time, windows in increasing order.  The non-empty rows' bases move to the
+    // leading lanes, and one bit per candidate says where a row starts, 32 to a
+    // lane for MAP_SPAN candidates (the bits are set in the event array, free
+    // until the candidates are done).  A window's two words then tell every lane
+    // how many rows have started up to its candidate, and the last of them is
+    // its row: 10 vector instructions a window and one LDS permute.
+    constexpr int MAP_SPAN = 32 * WAVE;
+    const unsigned long long full = ballot(cnt > 0);
+    const int row_base = __builtin_amdgcn_ds_permute(4 * (cnt > 0 ? count_below(full) : WAVE - 1), rbase);
+    unsigned starts = 0;  // this lane's word of start bits
+    int started = 0;      // rows that start before the window
     auto window_atom = [&](int kw) -> int {
-        if (cnt > 0 && off >= kw && off < kw + WAVE) s_head[off - kw] = make_int2(off, rbase);
-        __builtin_amdgcn_wave_barrier();
-        const int2 h = s_head[lane];
-        // the last start at or below this lane: its bit moved to the top
-        const unsigned long long m = __ballot(h.x == kw + lane) << (63 - lane);
-        const int p = m ? lane - __clzll((long long)m) : lane;
-        const int rb = __shfl(h.y, p, WAVE);
-        const int base = m ? rb : carry;
-        carry = __builtin_amdgcn_readlane(base, WAVE - 1);
-        __builtin_amdgcn_wave_barrier();
-        return base + kw + lane;
+        const int w = (kw & (MAP_SPAN - 1)) >> 5;
+        if (w == 0) {
+            s_ev01[lane] = 0;
+            __builtin_amdgcn_wave_barrier();
+            if (cnt > 0 && (unsigned)(off - kw) < (unsigned)MAP_SPAN) atomicOr(&s_ev01[(off - kw) >> 5], 1u << (off & 31));
+            __builtin_amdgcn_wave_barrier();
+            starts = s_ev01[lane];
+        }
+        const unsigned lo = __builtin_amdgcn_readlane(starts, w), hi = __builtin_amdgcn_readlane(starts, w + 1);
+        // rows started at or below this lane: bit 0, then those at bits 1 .. lane
+        const unsigned long long m = ((unsigned long long)hi << 32 | lo) >> 1;
+        const int p = (int)__builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, started + (int)(lo & 1) - 1));
+        started += __popc(lo) + __popc(hi);
+        return __builtin_amdgcn_ds_bpermute(4 * p, row_base) + kw + lane;
     };
 
     Real fx = 0, fy = 0, fz = 0;
@@ -2312,7 +2372,7 @@ __global__ __launch_bounds__(WAVE, sizeof(Real) == 4 ? 6 : 4) void k_force(Batch
     // one candidate: pair terms into (fx, fy, fz, ee, evw); a solvation
     // neighbour with a large cap is appended at the front of the list, any
     // other at its back (growing down from MAX_NBR - 1), in lane order
-    auto visit = [&](bool valid, const double4 &rj, const double4 &pj) {
+    auto visit = [&](bool valid, const double4 &rj, const AtomPar<Real> &pj) {
         // contraction off, the fused steps written out: the loop bodies of
         // all launch shapes round alike
 #pragma clang fp contract(off)
@@ -2329,11 +2389,11 @@ __global__ __launch_bounds__(WAVE, sizeof(Real) == 4 ? 6 : 4) void k_force(Batch
                 // mixed form: hardware reciprocal (1 ulp), far inside the force tolerance
                 const Real inv2 = MIXED ? (Real)__builtin_amdgcn_rcpf((float)d2) : (Real)1 / (Real)d2;
                 // eq 02 with eps = k_d d: E = (C/k_d) q_i q_j / d^2
-                const Real eel = we * coul * qi * (Real)pj.x * inv2;
+                const Real eel = we * coul * qi * pj.q * inv2;
                 // eq 03: E = eps_ij [(D/d)^12 - 2 (D/d)^6], D = R_i + R_j, eps_ij = sqrt(eps_i eps_j)
-                const Real D = Ri + (Real)pj.y;
+                const Real D = Ri + pj.R;
                 const Real s2 = D * D * inv2, s6 = s2 * s2 * s2, s12 = s6 * s6;
-                const Real eij = sei * (Real)pj.z;
+                const Real eij = sei * pj.se;
                 const Real elj = wv * eij * fma((Real)-2, s6, s12);
                 // |F|/d along r_i - r_j: 2 E_elec/d^2 + 12 eps (s12 - s6)/d^2
                 const Real fsc = fma((Real)2, eel, (Real)12 * wv * eij * (s12 - s6)) * inv2;
@@ -2347,13 +2407,15 @@ __global__ __launch_bounds__(WAVE, sizeof(Real) == 4 ? 6 : 4) void k_force(Batch
         bool in_cav = false, front = false;
         double c0 = 0.0;
         if (do_cav) {
-            const double Rj = pj.w;
+            const double Rj = pj.roff;
             const double lim = roff_i + Rj + dr;
             in_cav = valid && d2 <= lim * lim;
             c0 = cap_c0(roff_i, d2, Rj, inv_2roff);
-            front = c0 < 0.0 || c0 * c0 < (CAP_SPLIT * CAP_SPLIT) * d2;
+            // c0 < CAP_SPLIT |a|; FP32 will do, the list's order does not change results
+            const float cf = (float)c0;
+            front = cf * fabsf(cf) < (CAP_SPLIT * CAP_SPLIT) * (float)d2;
         }
-        const unsigned long long mf = __ballot(in_cav && front), mb = __ballot(in_cav && !front);
+        const unsigned long long mf = ballot(in_cav && front), mb = ballot(in_cav && !front);
         const int cf = __popcll(mf), cb = __popcll(mb);
         // past the list's capacity nothing more is written: the atom then
         // takes the chunked path, which enumerates its neighbours again
@@ -2373,7 +2435,6 @@ __global__ __launch_bounds__(WAVE, sizeof(Real) == 4 ? 6 : 4) void k_force(Batch
     // CPT candidates per lane per trip, every load issued before any is used.
     // Loads take 32-bit byte offsets from the chain's arrays (n < 2^26 atoms
     // of 32 bytes).
-    const gptr<const char> sr = (gptr<const char>)glob(cd->s_r), sp = (gptr<const char>)glob(cd->s_p);
     // The sorted atoms of the next trip are found while this trip's loads are
     // in flight.
     int sj[CPT];
@@ -2387,13 +2448,14 @@ __global__ __launch_bounds__(WAVE, sizeof(Real) == 4 ? 6 : 4) void k_force(Batch
     if (T > 0) map_trip(0);
     for (int kb = 0; kb < T; kb += CPT * WAVE) {
         bool ok[CPT];
-        double4 rj[CPT], pj[CPT];
+        double4 rj[CPT];
+        AtomPar<Real> pj[CPT];
 #pragma unroll
         for (int q = 0; q < CPT; ++q) {
             ok[q] = sj[q] != si;
             const unsigned ob = (unsigned)sj[q] * (unsigned)sizeof(double4);
             rj[q] = *(const gptr<const double4>)(sr + ob);
-            pj[q] = *(const gptr<const double4>)(sp + ob);
+            pj[q] = load_par<Real>(sp, ob);
         }
         if (kb + CPT * WAVE < T) map_trip(kb + CPT * WAVE);
 #pragma unroll
@@ -2544,7 +2606,7 @@ __global__ __launch_bounds__(WAVE, sizeof(Real) == 4 ? 6 : 4) void k_force(Batch
                             for (int q = 0; q < SAT_CHECK; ++q) blk += (t[q] >= (Real)0) ? 32 + q : 0;
                         }
                         acc[i] = mad_u24(blk >> 5, kmul, acc[i] + blk);
-                        if (__ballot(acc[i] < (2 << ACC_SHIFT))) next |= 1 << i;
+                        if (ballot(acc[i] < (2 << ACC_SHIFT))) next |= 1 << i;
                     }
                     livem = next;
                 };
@@ -2564,7 +2626,7 @@ __global__ __launch_bounds__(WAVE, sizeof(Real) == 4 ? 6 : 4) void k_force(Batch
                         const bool valid = kb + kl < N;
                         const bool band = MIXED && amin[i] <= (Real)MIXED_BAND;
                         const bool keep = valid && (acc[i] < (2 << ACC_SHIFT) || band);
-                        const unsigned long long m = __ballot(keep);
+                        const unsigned long long m = ballot(keep);
                         if (keep) s_stage[pos + count_below(m)] = acc[i] | (kl << STAGE_K) | (band ? 1 << 30 : 0);
                         if (valid && !keep) ++ncov;
                         pos += __popcll(m);
@@ -2585,7 +2647,7 @@ __global__ __launch_bounds__(WAVE, sizeof(Real) == 4 ? 6 : 4) void k_force(Batch
                             if (w >> 30) amin[i] = (Real)0;
                             load_q<Real>(cd, kb + ((w >> STAGE_K) & 255), Qx[i], Qy[i], Qz[i]);
                         }
-                        if (__ballot(acc[i] < (2 << ACC_SHIFT))) next |= 1 << i;
+                        if (ballot(acc[i] < (2 << ACC_SHIFT))) next |= 1 << i;
                     }
                     livem = __builtin_amdgcn_readfirstlane(next);
                 }
@@ -2616,7 +2678,7 @@ __global__ __launch_bounds__(WAVE, sizeof(Real) == 4 ? 6 : 4) void k_force(Batch
                     if (MIXED) {
                         // a test within the band of its threshold: the whole wave
                         // recounts that sample in FP64, one lane per neighbour
-                        unsigned long long bm = __ballot(valid && amin[i] <= (Real)MIXED_BAND);
+                        unsigned long long bm = ballot(valid && amin[i] <= (Real)MIXED_BAND);
                         while (bm) {
                             const int l = __ffsll((long long)bm) - 1;
                             bm &= bm - 1;
@@ -2656,7 +2718,7 @@ __global__ __launch_bounds__(WAVE, sizeof(Real) == 4 ? 6 : 4) void k_force(Batch
                     if (valid && C >= 1) ++ncov;
                     // step 2 for the exposed samples of this slot: one lane per
                     // neighbour, the samples broadcast from their lanes
-                    const unsigned long long em0 = __ballot(valid && C == 0);
+                    const unsigned long long em0 = ballot(valid && C == 0);
                     if (em0) {
 #pragma unroll
                         for (int v = 0; v < NSLOT; ++v) {
