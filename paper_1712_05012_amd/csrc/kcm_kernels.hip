@@ -112,6 +112,19 @@ template <typename T, typename Op> __device__ __forceinline__ T wave_all(T v, Op
     return op(v, dpp<DPP_ROW_ROR + 1>(v));
 }
 
+// inclusive prefix sum over the wave: inside rows of 16, then the last lane of
+// each row into the next, then of the lower half into the upper
+__device__ __forceinline__ int wave_scan_i(int x)
+{
+    x += dpp<DPP_ROW_SHR + 1>(x);
+    x += dpp<DPP_ROW_SHR + 2>(x);
+    x += dpp<DPP_ROW_SHR + 4>(x);
+    x += dpp<DPP_ROW_SHR + 8>(x);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);
+    return x;
+}
+
 // Several sums at once: where a butterfly adds the two halves of one value in
 // all lanes, the halves of two values are exchanged first and one add serves
 // both.  Each value's sum is the one wave_all gives, in the lanes named.
@@ -296,12 +309,7 @@ __device__ double block_max(double v, double *scratch)
 __device__ int block_excl_scan(int v, int *scratch, int *total)
 {
     const int lane = threadIdx.x & (WAVE - 1), w = threadIdx.x / WAVE, nw = blockDim.x / WAVE;
-    int x = v;
-#pragma unroll
-    for (int d = 1; d < WAVE; d <<= 1) {
-        int y = __shfl_up(x, d, WAVE);
-        if (lane >= d) x += y;
-    }
+    const int x = wave_scan_i(v);
     __syncthreads();
     if (lane == WAVE - 1) scratch[w] = x;
     __syncthreads();
@@ -2264,7 +2272,9 @@ __global__ __launch_bounds__(WAVE, sizeof(Real) == 4 ? 6 : 4) void k_force(Batch
     const int ai = (int)__double_as_longlong(ri.w);
     const int dxn = g.dims[0], dyn = g.dims[1], dzn = g.dims[2];
     // the atom's cell, by the expression that sorted it (no key decoding)
-    const int cx = min(max((int)floor((ri.x - g.origin[0]) * g.inv_cell), 0), dxn - 1);
+    const double ux = (ri.x - g.origin[0]) * g.inv_cell, fx0 = floor(ux);
+    const int cx0 = (int)fx0;
+    const int cx = min(max(cx0, 0), dxn - 1);
     const int cy = min(max((int)floor((ri.y - g.origin[1]) * g.inv_cell), 0), dyn - 1);
     const int cz = min(max((int)floor((ri.z - g.origin[2]) * g.inv_cell), 0), dzn - 1);
     const int R = g.reach, side = 2 * R + 1, nrows = side * side;
@@ -2278,41 +2288,37 @@ __global__ __launch_bounds__(WAVE, sizeof(Real) == 4 ? 6 : 4) void k_force(Batch
     // run keeps only the cells that can hold an atom within reach of atom i:
     // a row whose y-z slab is farther than the reach is empty, and the x run
     // covers [x_i - ext, x_i + ext] with ext^2 = reach^2 - (y-z distance)^2.
-    // Border cells reach to infinity outward (atoms outside the grid are
-    // clamped into them); the pad on the reach absorbs rounding.
+    // The pad on the reach absorbs rounding.
     int beg = 0, cnt = 0;
-    if (lane < nrows) {
+    {
         const int y = cy + row_y - R, z = cz + row_z - R;
-        if (y >= 0 && y < dyn && z >= 0 && z < dzn) {
-            const double reach = g.reach_len + 1e-6;
-            const double ylo = y == 0 ? -DBL_MAX : g.origin[1] + y * g.cell;
-            const double yhi = y == dyn - 1 ? DBL_MAX : g.origin[1] + (y + 1) * g.cell;
-            const double zlo = z == 0 ? -DBL_MAX : g.origin[2] + z * g.cell;
-            const double zhi = z == dzn - 1 ? DBL_MAX : g.origin[2] + (z + 1) * g.cell;
-            const double gy = fmax(0.0, fmax(ylo - ri.y, ri.y - yhi));
-            const double gz = fmax(0.0, fmax(zlo - ri.z, ri.z - zhi));
-            const double rest = reach * reach - gy * gy - gz * gz;
-            if (rest >= 0.0) {
-                const double ext = sqrt(rest);
-                const int xa = (int)floor((ri.x - ext - g.origin[0]) * g.inv_cell);
-                const int xb = (int)floor((ri.x + ext - g.origin[0]) * g.inv_cell);
-                const int xl = max(max(0, cx - R), min(xa, dxn - 1));
-                const int xh = min(min(dxn - 1, cx + R), max(xb, 0));
-                if (xl <= xh) {
-                    const int base = (z * dyn + y) * dxn;
-                    beg = glob(cd->cell_start)[base + xl];
-                    cnt = glob(cd->cell_start)[base + xh + 1] - beg;
-                }
-            }
+        // distance to the slab: to its near edge, nothing in the atom's own row
+        const double ey = g.origin[1] + (y + (row_y < R ? 1 : 0)) * g.cell, ez = g.origin[2] + (z + (row_z < R ? 1 : 0)) * g.cell;
+        const double gy = row_y == R ? 0.0 : ey - ri.y, gz = row_z == R ? 0.0 : ez - ri.z;
+        const double reach = g.reach_len + 1e-6, rest = reach * reach - gy * gy - gz * gz;
+        const bool row = lane < nrows && (unsigned)y < (unsigned)dyn && (unsigned)z < (unsigned)dzn && rest >= 0.0;
+        // the run's ends in cells from the atom's own, in FP32 unless one lies
+        // so near a border that FP64 might put it on the other side
+        const float f = (float)(ux - fx0), e = __builtin_amdgcn_sqrtf((float)rest) * (float)g.inv_cell;
+        const float lo = f - e, hi = f + e;
+        constexpr float NEAR = 1e-4f;
+        const bool tie = fminf(fabsf(lo - rintf(lo)), fabsf(hi - rintf(hi))) < NEAR;
+        int xa = cx0 + (int)floorf(lo), xb = cx0 + (int)floorf(hi);
+        if (ballot(row && tie)) {
+            const double ext = sqrt(rest);
+            xa = (int)floor((ri.x - ext - g.origin[0]) * g.inv_cell);
+            xb = (int)floor((ri.x + ext - g.origin[0]) * g.inv_cell);
+        }
+        const int xl = max(max(0, cx - R), min(xa, dxn - 1));
+        const int xh = min(min(dxn - 1, cx + R), max(xb, 0));
+        if (row && xl <= xh) {
+            const int base = (z * dyn + y) * dxn;
+            beg = glob(cd->cell_start)[base + xl];
+            cnt = glob(cd->cell_start)[base + xh + 1] - beg;
         }
     }
-    int off = cnt;
-#pragma unroll
-    for (int d = 1; d < WAVE; d <<= 1) {
-        const int y = __shfl_up(off, d, WAVE);
-        if (lane >= d) off += y;
-    }
-    const int T = __shfl(off, WAVE - 1, WAVE);
+    int off = wave_scan_i(cnt);
+    const int T = __builtin_amdgcn_readlane(off, WAVE - 1);
     off -= cnt;                   // first candidate number of this row
     const int rbase = beg - off;  // candidate number k of row t is sorted atom rbase_t + k
 
