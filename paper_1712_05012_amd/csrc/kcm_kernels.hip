@@ -1844,11 +1844,20 @@ static_assert(WAVE * SPL <= 256 && STAGE_K + 8 < 31, "staged sample field");
 static_assert(MAX_NBR * (MAX_NBR - 1) / 2 < (1 << ACC_SHIFT), "slot sum must stay below the count field");
 static_assert(MAX_NBR * 2 < (1 << (31 - ACC_SHIFT)), "count field must not overflow");
 static_assert((2 * MAX_REACH + 1) * (2 * MAX_REACH + 1) <= WAVE, "stencil rows must fit one wave");
-// Net events of one neighbour and axis lie in [-N, N] with N < 2^15 samples:
-// axes 0 and 1 share a word as two halves biased by 2^15 (no carry or borrow
-// crosses the halves), axis 2 has a word of its own.
-constexpr int EV_BIAS = 0x8000;
-constexpr int EV_INIT = EV_BIAS | (EV_BIAS << 16);
+// Net events of one neighbour and axis from one pass of at most 256 samples lie
+// in [-256, 256]: the three axes share a word as ten-bit fields biased by 512
+// (no carry or borrow leaves a field), scattered after each pass.  One word
+// instead of two keeps the mixed form's LDS within five of the 1,280-byte
+// granules it is allotted in, 24 waves to a CU: with 6,720 bytes it was six
+// granules and 21 waves, the 256-chain batch 2,419 us against 2,289.
+constexpr int EV_BITS = 10, EV_BIAS = 1 << (EV_BITS - 1), EV_MASK = (1 << EV_BITS) - 1;
+constexpr unsigned EV_INIT = EV_BIAS | EV_BIAS << EV_BITS | EV_BIAS << (2 * EV_BITS);
+static_assert(WAVE * SPL < EV_BIAS, "events of a pass fit their field");
+__device__ __forceinline__ int ev_of(unsigned w, int axis) { return (int)(w >> (EV_BITS * axis) & EV_MASK) - EV_BIAS; }
+__device__ __forceinline__ unsigned ev_word(int e0, int e1, int e2)
+{
+    return (unsigned)e0 + ((unsigned)e1 << EV_BITS) + ((unsigned)e2 << (2 * EV_BITS));
+}
 
 __device__ __forceinline__ float bcast(float x, int l)
 {
@@ -2023,7 +2032,7 @@ struct ChunkArgs {
 };
 template <typename Real>
 __device__ __noinline__ ChunkedSasa sasa_chunked(CDev cd, const ChunkArgs c, NbrEntry<Real> *s_nbr,
-                                                 int *s_nbr_a, unsigned *s_ev01, int *s_ev2)
+                                                 int *s_nbr_a, unsigned *s_ev)
 {
     constexpr bool MIXED = sizeof(Real) == 4;
     const int lane = threadIdx.x & (WAVE - 1);
@@ -2148,8 +2157,7 @@ __device__ __noinline__ ChunkedSasa sasa_chunked(CDev cd, const ChunkArgs c, Nbr
             __syncthreads();
             enum_window(lo, len);
             for (int u = lane; u < len; u += WAVE) {
-                s_ev01[u] = EV_INIT;
-                s_ev2[u] = 0;
+                s_ev[u] = EV_INIT;
             }
             __syncthreads();
 #pragma unroll
@@ -2164,11 +2172,10 @@ __device__ __noinline__ ChunkedSasa sasa_chunked(CDev cd, const ChunkArgs c, Nbr
                     const Real base = Qx[i] * e.ax + Qy[i] * e.ay + Qz[i] * e.az - e.c0 - kq;
                     const Real span = drr + k1 * fmax(fabs(e.ax), fmax(fabs(e.ay), fabs(e.az)));
                     if (base - span <= guard) {
-                        unsigned inc01 = 0;
-                        if (!test_cover<Real, MIXED>(base + drr * Qx[i] - k1 * e.ax, cd, a.ri, a.roff_i, k, aj, 0)) inc01 += 1u;
-                        if (!test_cover<Real, MIXED>(base + drr * Qy[i] - k1 * e.ay, cd, a.ri, a.roff_i, k, aj, 1)) inc01 += 1u << 16;
-                        if (inc01) atomicAdd(&s_ev01[u], inc01);
-                        if (!test_cover<Real, MIXED>(base + drr * Qz[i] - k1 * e.az, cd, a.ri, a.roff_i, k, aj, 2)) atomicAdd(&s_ev2[u], 1);
+                        const int n0 = !test_cover<Real, MIXED>(base + drr * Qx[i] - k1 * e.ax, cd, a.ri, a.roff_i, k, aj, 0);
+                        const int n1 = !test_cover<Real, MIXED>(base + drr * Qy[i] - k1 * e.ay, cd, a.ri, a.roff_i, k, aj, 1);
+                        const int n2 = !test_cover<Real, MIXED>(base + drr * Qz[i] - k1 * e.az, cd, a.ri, a.roff_i, k, aj, 2);
+                        if (n0 | n1 | n2) atomicAdd(&s_ev[u], ev_word(n0, n1, n2));
                     }
                 }
                 // exposed samples: one lane per neighbour, the samples broadcast
@@ -2194,18 +2201,15 @@ __device__ __noinline__ ChunkedSasa sasa_chunked(CDev cd, const ChunkArgs c, Nbr
                             if (test_cover<Real, MIXED>(base + drr * qz - k1 * e.az, cd, a.ri, a.roff_i, kx, aj, 2)) --d2;
                         }
                     }
-                    const unsigned dec01 = (unsigned)d0 + ((unsigned)d1 << 16);
-                    if (own && dec01) atomicAdd(&s_ev01[u], dec01);
-                    if (own && d2) atomicAdd(&s_ev2[u], d2);
+                    if (own && (d0 | d1 | d2)) atomicAdd(&s_ev[u], ev_word(d0, d1, d2));
                 }
             }
             __syncthreads();
             // eq F_cav_patch: atom i gains G0_i ev / (N dr) per axis, neighbour j the opposite
             for (int u = lane; u < len; u += WAVE) {
-                const unsigned w01 = s_ev01[u];
-                const int e0 = (int)(w01 & 0xffffu) - EV_BIAS, e1 = (int)(w01 >> 16) - EV_BIAS, e2 = s_ev2[u];
+                const unsigned w = s_ev[u];
                 const int aj = s_nbr_a[u];
-                const int ev[3] = {e0, e1, e2};
+                const int ev[3] = {ev_of(w, 0), ev_of(w, 1), ev_of(w, 2)};
 #pragma unroll
                 for (int x = 0; x < 3; ++x) {
                     if (!ev[x]) continue;
@@ -2218,11 +2222,11 @@ __device__ __noinline__ ChunkedSasa sasa_chunked(CDev cd, const ChunkArgs c, Nbr
     return out;
 }
 
-// Mixed form: six waves per SIMD (80 registers, the 6,720-byte LDS list), which
+// Mixed form: six waves per SIMD (80 registers, 5,760 bytes of LDS), which
 // hides the latency of the candidate loads and LDS reads better than four
-// waves with room to spare (3.06 against 3.39 ms on the 256-chain batch);
-// seven spill in the hot loops.  The FP64 form: four (127 registers; its
-// 10,560-byte list allows 15 waves per CU).
+// waves with room to spare (3.06 against 3.39 ms on the 256-chain batch when
+// measured, with a longer list); seven spill in the hot loops.  The FP64 form:
+// four (127 registers; its 9,600 bytes allow 16 waves per CU).
 template <typename Real, int CPT, int SAT_CHECK, bool XCD>
 __global__ __launch_bounds__(WAVE, sizeof(Real) == 4 ? 6 : 4) void k_force(Batch bt)
 {
@@ -2230,8 +2234,7 @@ __global__ __launch_bounds__(WAVE, sizeof(Real) == 4 ? 6 : 4) void k_force(Batch
     constexpr bool MIXED = sizeof(Real) == 4;
     __shared__ NbrEntry<Real> s_nbr[MAX_NBR];
     __shared__ int s_nbr_a[MAX_NBR];
-    __shared__ __align__(8) unsigned s_ev01[MAX_NBR];  // net events of each neighbour, axes 0 and 1 (biased halves)
-    __shared__ int s_ev2[MAX_NBR];                     // and axis 2
+    __shared__ __align__(8) unsigned s_ev[MAX_NBR];  // net events of each neighbour in this pass
 
     int atom = blockIdx.x;
     if (XCD) {
@@ -2339,7 +2342,7 @@ __global__ __launch_bounds__(WAVE, sizeof(Real) == 4 ? 6 : 4) void k_force(Batch
     // below in the event array (free until the candidates are done).
     const unsigned long long cls_word = cd->cls_word[slot_i];
     const int skip_cls = MIXED ? cd->skip_cls32 : cd->skip_cls64;  // bit c: class c adds nothing
-    Real *s_wtab = reinterpret_cast<Real *>(s_ev01 + 2 * WAVE);
+    Real *s_wtab = reinterpret_cast<Real *>(s_ev + 2 * WAVE);
     if (lane < 8) s_wtab[lane] = MIXED ? (Real)cd->wtab32[lane] : (Real)cd->wtab64[lane];
     __builtin_amdgcn_wave_barrier();
 
@@ -2358,11 +2361,11 @@ __global__ __launch_bounds__(WAVE, sizeof(Real) == 4 ? 6 : 4) void k_force(Batch
     auto window_atom = [&](int kw) -> int {
         const int w = (kw & (MAP_SPAN - 1)) >> 5;
         if (w == 0) {
-            s_ev01[lane] = 0;
+            s_ev[lane] = 0;
             __builtin_amdgcn_wave_barrier();
-            if (cnt > 0 && (unsigned)(off - kw) < (unsigned)MAP_SPAN) atomicOr(&s_ev01[(off - kw) >> 5], 1u << (off & 31));
+            if (cnt > 0 && (unsigned)(off - kw) < (unsigned)MAP_SPAN) atomicOr(&s_ev[(off - kw) >> 5], 1u << (off & 31));
             __builtin_amdgcn_wave_barrier();
-            starts = s_ev01[lane];
+            starts = s_ev[lane];
         }
         const unsigned lo = __builtin_amdgcn_readlane(starts, w), hi = __builtin_amdgcn_readlane(starts, w + 1);
         // rows started at or below this lane: bit 0, then those at bits 1 .. lane
@@ -2514,7 +2517,7 @@ __global__ __launch_bounds__(WAVE, sizeof(Real) == 4 ? 6 : 4) void k_force(Batch
         if (nn > MAX_NBR) {
             // more neighbours than the LDS list holds: chunks, out of line
             const ChunkArgs ca = {si, off, rbase, nrows, T, nn};
-            const ChunkedSasa cs = sasa_chunked<Real>(cd, ca, s_nbr, s_nbr_a, s_ev01, s_ev2);
+            const ChunkedSasa cs = sasa_chunked<Real>(cd, ca, s_nbr, s_nbr_a, s_ev);
             ncov = cs.ncov;
             own0 = cs.own[0];
             own1 = cs.own[1];
@@ -2549,13 +2552,10 @@ __global__ __launch_bounds__(WAVE, sizeof(Real) == 4 ? 6 : 4) void k_force(Batch
                 }
                 __syncthreads();
             }
-            for (int u = lane; u < nnc; u += WAVE) {
-                s_ev01[u] = EV_INIT;
-                s_ev2[u] = 0;
-            }
-            __syncthreads();
             const int nlist = __builtin_amdgcn_readfirstlane(nnc);
             for (int kb = 0; kb < N; kb += WAVE * SPL) {
+                for (int u = lane; u < nnc; u += WAVE) s_ev[u] = EV_INIT;
+                __syncthreads();
                 // step 1: coverage counts of SPL samples per lane
                 Real Qx[SPL], Qy[SPL], Qz[SPL], amin[SPL];
                 int acc[SPL];
@@ -2716,9 +2716,7 @@ __global__ __launch_bounds__(WAVE, sizeof(Real) == 4 ? 6 : 4) void k_force(Batch
                                 n1 += redo((float)v1, cd, ri, roff_i, k, aj, 1);
                                 n2 += redo((float)v2, cd, ri, roff_i, k, aj, 2);
                             }
-                            const unsigned inc01 = (unsigned)n0 + ((unsigned)n1 << 16);
-                            if (inc01) atomicAdd(&s_ev01[u], inc01);
-                            if (n2) atomicAdd(&s_ev2[u], 1);
+                            if (n0 | n1 | n2) atomicAdd(&s_ev[u], ev_word(n0, n1, n2));
                         }
                     }
                     if (valid && C >= 1) ++ncov;
@@ -2765,28 +2763,25 @@ __global__ __launch_bounds__(WAVE, sizeof(Real) == 4 ? 6 : 4) void k_force(Batch
                             }
                             // the lane owns neighbour u here, but critical samples of
                             // other lanes add to the same words: keep atomics
-                            const unsigned dec01 = (unsigned)d0 + ((unsigned)d1 << 16);
-                            if (dec01) atomicAdd(&s_ev01[u], dec01);
-                            if (d2) atomicAdd(&s_ev2[u], d2);
+                            if (d0 | d1 | d2) atomicAdd(&s_ev[u], ev_word(d0, d1, d2));
                         }
                     }
                 }
-            }
-            __syncthreads();
-
-            // eq F_cav_patch: atom i gains G0_i ev / (N dr) per axis, neighbour j the opposite
-            const long long qf = glob(cd->qfix)[ai];
-            for (int u = lane; u < nnc; u += WAVE) {
-                const unsigned w01 = s_ev01[u];
-                const int e0 = (int)(w01 & 0xffffu) - EV_BIAS, e1 = (int)(w01 >> 16) - EV_BIAS, e2 = s_ev2[u];
-                if (!(e0 | e1 | e2)) continue;
-                const int aj = s_nbr_a[u];
-                own0 += e0;
-                own1 += e1;
-                own2 += e2;
-                if (e0) fix_add(&glob(cd->f_cav)[3 * aj + 0], (-(long long)e0 * qf));
-                if (e1) fix_add(&glob(cd->f_cav)[3 * aj + 1], (-(long long)e1 * qf));
-                if (e2) fix_add(&glob(cd->f_cav)[3 * aj + 2], (-(long long)e2 * qf));
+                __syncthreads();
+                // eq F_cav_patch: atom i gains G0_i ev / (N dr) per axis, neighbour j the opposite
+                const long long qf = glob(cd->qfix)[ai];
+                for (int u = lane; u < nnc; u += WAVE) {
+                    const unsigned w = s_ev[u];
+                    if (w == EV_INIT) continue;
+                    const int e0 = ev_of(w, 0), e1 = ev_of(w, 1), e2 = ev_of(w, 2), aj = s_nbr_a[u];
+                    own0 += e0;
+                    own1 += e1;
+                    own2 += e2;
+                    if (e0) fix_add(&glob(cd->f_cav)[3 * aj + 0], (-(long long)e0 * qf));
+                    if (e1) fix_add(&glob(cd->f_cav)[3 * aj + 1], (-(long long)e1 * qf));
+                    if (e2) fix_add(&glob(cd->f_cav)[3 * aj + 2], (-(long long)e2 * qf));
+                }
+                __syncthreads();
             }
         }
         __syncthreads();
