@@ -1825,7 +1825,6 @@ struct ForceShape {
 };
 constexpr ForceShape FORCE_SHAPES[] = {{2, 4, false}, {1, 4, false}, {1, 4, true}, {2, 4, true}};
 constexpr int N_XCD = 8;
-constexpr int NSLOT = (MAX_NBR + WAVE - 1) / WAVE;  // neighbours per lane in step 2
 // Step-1 count of a sample: acc = (covering neighbours << ACC_SHIFT) + (sum of
 // their slots), so acc >> ACC_SHIFT == 1 leaves the single overlapper in the
 // low bits; slots below MAX_NBR keep the slot sum below 2^ACC_SHIFT.
@@ -1928,18 +1927,11 @@ __device__ __forceinline__ bool test_cover(Real v, CDev cd, const double4 &ri, d
 // The three displaced tests of one (sample, neighbour) pair are decided in
 // the form's precision first; the mixed form then takes every test inside the
 // band again in FP64, the three behind one branch.  band3: is any of them in
-// the band; redo: the FP32 decision minus the FP64 one for a test in the band
-// (0 outside it), the correction to a count of covered tests.
+// the band.
 __device__ __forceinline__ bool band3(float v0, float v1, float v2)
 {
     return fminf(fabsf(v0), fminf(fabsf(v1), fabsf(v2))) <= MIXED_BAND;
 }
-__device__ __forceinline__ int redo(float v, CDev cd, const double4 &ri, double roff_i, int k, int aj, int s)
-{
-    if (fabsf(v) > MIXED_BAND) return 0;
-    return (v >= 0.0f ? 1 : 0) - (cover_exact(cd, ri, roff_i, k, aj, s) ? 1 : 0);
-}
-
 template <typename Real>
 __device__ __forceinline__ void load_q(CDev cd, int k, Real &x, Real &y, Real &z)
 {
@@ -2235,6 +2227,7 @@ __global__ __launch_bounds__(WAVE, sizeof(Real) == 4 ? 6 : 4) void k_force(Batch
     __shared__ NbrEntry<Real> s_nbr[MAX_NBR];
     __shared__ int s_nbr_a[MAX_NBR];
     __shared__ __align__(8) unsigned s_ev[MAX_NBR];  // net events of each neighbour in this pass
+    __shared__ unsigned s_pair[2 * WAVE];            // (sample, neighbour) pairs that await their displaced tests
 
     int atom = blockIdx.x;
     if (XCD) {
@@ -2523,38 +2516,31 @@ __global__ __launch_bounds__(WAVE, sizeof(Real) == 4 ? 6 : 4) void k_force(Batch
             own1 = cs.own[1];
             own2 = cs.own[2];
         } else {
-            // the back part of the list, [MAX_NBR - nback, MAX_NBR), moves
-            // down to [nfront, nnc): the list is then contiguous, large caps
-            // first.  Each source lies at or above its destination, and a
-            // chunk's reads are done before its writes.
+            // The list lies in two parts, large caps from 0 up and the others
+            // from MAX_NBR - 1 down.  The front is filled up to a multiple of
+            // SAT_CHECK from the lower end of the back, so that no block of
+            // step 1 straddles the gap; neighbour u of the list then is entry
+            // u below nf and u + gap from there on.
             const int nb_back = __builtin_amdgcn_readfirstlane(nback);
-            const int nf = __builtin_amdgcn_readfirstlane(nfront);
-            for (int c = 0; c < nb_back; c += WAVE) {
-                const int v = c + lane;
-                // component by component, so that the entry stays in registers
-                Real ex = 0, ey = 0, ez = 0, ec = 0;
-                int a = 0;
-                if (v < nb_back) {
-                    const int src = MAX_NBR - nb_back + v;
-                    ex = s_nbr[src].ax;
-                    ey = s_nbr[src].ay;
-                    ez = s_nbr[src].az;
-                    ec = s_nbr[src].c0;
-                    a = s_nbr_a[src];
+            int nf = __builtin_amdgcn_readfirstlane(nfront);
+            {
+                const int fill = min(-nf & (SAT_CHECK - 1), nb_back), src = MAX_NBR - nb_back + lane;
+                if (lane < fill) {
+                    // component by component, so that the entry stays in registers
+                    const Real ex = s_nbr[src].ax, ey = s_nbr[src].ay, ez = s_nbr[src].az, ec = s_nbr[src].c0;
+                    const int a = s_nbr_a[src];
+                    s_nbr[nf + lane].ax = ex;
+                    s_nbr[nf + lane].ay = ey;
+                    s_nbr[nf + lane].az = ez;
+                    s_nbr[nf + lane].c0 = ec;
+                    s_nbr_a[nf + lane] = a;
                 }
-                __syncthreads();
-                if (v < nb_back) {
-                    s_nbr[nf + v].ax = ex;
-                    s_nbr[nf + v].ay = ey;
-                    s_nbr[nf + v].az = ez;
-                    s_nbr[nf + v].c0 = ec;
-                    s_nbr_a[nf + v] = a;
-                }
-                __syncthreads();
+                nf += fill;
             }
-            const int nlist = __builtin_amdgcn_readfirstlane(nnc);
+            const int nlist = __builtin_amdgcn_readfirstlane(nnc), gap = MAX_NBR - nlist;
+            auto entry_of = [&](int u) -> int { return u < nf ? u : u + gap; };
             for (int kb = 0; kb < N; kb += WAVE * SPL) {
-                for (int u = lane; u < nnc; u += WAVE) s_ev[u] = EV_INIT;
+                for (int u = lane; u < nlist; u += WAVE) s_ev[entry_of(u)] = EV_INIT;
                 __syncthreads();
                 // step 1: coverage counts of SPL samples per lane
                 Real Qx[SPL], Qy[SPL], Qz[SPL], amin[SPL];
@@ -2583,7 +2569,8 @@ __global__ __launch_bounds__(WAVE, sizeof(Real) == 4 ? 6 : 4) void k_force(Batch
                     if (kb + WAVE * i < N) livem |= 1 << i;
                 }
                 // one block of SAT_CHECK neighbours from u for the live slots
-                auto block = [&](int u) {
+                auto block = [&](int ul) {
+                    const int u = entry_of(ul);
                     NbrEntry<Real> e[SAT_CHECK];
 #pragma unroll
                     for (int q = 0; q < SAT_CHECK; ++q) e[q] = s_nbr[u + q];
@@ -2619,9 +2606,8 @@ __global__ __launch_bounds__(WAVE, sizeof(Real) == 4 ? 6 : 4) void k_force(Batch
                 // kept < 0: slot i of lane l holds sample kb + l + WAVE i;
                 // else the first `kept` staged samples fill the slots in order
                 int kept = -1;
-                const bool can_stage = (nnc * (int)sizeof(NbrEntry<Real>) + WAVE * SPL * (int)sizeof(int)) <=
-                                       MAX_NBR * (int)sizeof(NbrEntry<Real>);
-                int *s_stage = reinterpret_cast<int *>(s_nbr + nnc);
+                const bool can_stage = gap * (int)sizeof(NbrEntry<Real>) >= WAVE * SPL * (int)sizeof(int);
+                int *s_stage = reinterpret_cast<int *>(s_nbr + nf);
                 int u = 0;
                 for (; livem && u < COMPACT_AT && u + SAT_CHECK <= nlist; u += SAT_CHECK) block(u);
                 if (livem && u == COMPACT_AT && u + SAT_CHECK <= nlist && can_stage) {
@@ -2661,8 +2647,9 @@ __global__ __launch_bounds__(WAVE, sizeof(Real) == 4 ? 6 : 4) void k_force(Batch
                 if (!livem) u = nlist;
                 const int lm = __builtin_amdgcn_readfirstlane(livem);
                 for (; u < nlist; ++u) {
-                    const NbrEntry<Real> e = s_nbr[u];
-                    const int inc = (1 << ACC_SHIFT) + u;
+                    const int ue = entry_of(u);
+                    const NbrEntry<Real> e = s_nbr[ue];
+                    const int inc = (1 << ACC_SHIFT) + ue;
 #pragma unroll
                     for (int i = 0; i < SPL; ++i) {
                         if (!((lm >> i) & 1)) continue;
@@ -2671,12 +2658,46 @@ __global__ __launch_bounds__(WAVE, sizeof(Real) == 4 ? 6 : 4) void k_force(Batch
                         if (MIXED) amin[i] = fmin(amin[i], fabs(t));
                     }
                 }
-                // sample of lane l in slot i
-                auto sample_of = [&](int i, int l) -> int {
-                    if (kept < 0) return kb + l + WAVE * i;
-                    int p = l + WAVE * i;
-                    asm volatile("" : "+v"(p));  // computed at the (rare) use, not kept from the pass start
-                    return kb + ((s_stage[p] >> STAGE_K) & 255);
+                // sample in slot place p (lane + WAVE slot)
+                auto sample_at = [&](int p) -> int { return kb + (kept < 0 ? p : (s_stage[p] >> STAGE_K) & 255); };
+                // Displaced tests, one (sample, neighbour) pair per lane: a
+                // critically overlapped sample with its overlapper (the
+                // events are the copies that no longer cover it), an exposed
+                // one with a neighbour whose copies may reach it (the events
+                // are those that do).  Pairs collect in a queue and are taken
+                // when they fill the wave, and at the end of the pass.
+                int nq = 0;
+                auto take_pairs = [&](int n, int from) {
+                    if (lane < n) {
+                        const unsigned w = s_pair[from + lane];
+                        const int u = w & 255, k = sample_at((w >> 8) & 255);
+                        const bool crit = w >> 16;
+                        const NbrEntry<Real> e = s_nbr[u];
+                        Real qx, qy, qz;
+                        load_q<Real>(cd, k, qx, qy, qz);
+                        const Real base = fma(qz, e.az, fma(qy, e.ay, fma(qx, e.ax, -(e.c0 + kq))));
+                        const Real v0 = fma(-k1, e.ax, fma(drr, qx, base));
+                        const Real v1 = fma(-k1, e.ay, fma(drr, qy, base));
+                        const Real v2 = fma(-k1, e.az, fma(drr, qz, base));
+                        int h0 = v0 >= (Real)0, h1 = v1 >= (Real)0, h2 = v2 >= (Real)0;
+                        if (MIXED && band3((float)v0, (float)v1, (float)v2)) {
+                            const int aj = s_nbr_a[u];
+                            if (fabsf((float)v0) <= MIXED_BAND) h0 = cover_exact(cd, ri, roff_i, k, aj, 0);
+                            if (fabsf((float)v1) <= MIXED_BAND) h1 = cover_exact(cd, ri, roff_i, k, aj, 1);
+                            if (fabsf((float)v2) <= MIXED_BAND) h2 = cover_exact(cd, ri, roff_i, k, aj, 2);
+                        }
+                        const unsigned ev = (crit ? ev_word(1, 1, 1) : 0u) - ev_word(h0, h1, h2);
+                        if (ev) atomicAdd(&s_ev[u], ev);
+                    }
+                };
+                auto push_pairs = [&](bool mine, unsigned long long m, unsigned word) {
+                    if (mine) s_pair[nq + count_below(m)] = word;
+                    nq += __popcll(m);
+                    __builtin_amdgcn_wave_barrier();
+                    if (nq >= WAVE) {
+                        nq -= WAVE;
+                        take_pairs(WAVE, nq);
+                    }
                 };
 #pragma unroll
                 for (int i = 0; i < SPL; ++i) {
@@ -2688,89 +2709,53 @@ __global__ __launch_bounds__(WAVE, sizeof(Real) == 4 ? 6 : 4) void k_force(Batch
                         while (bm) {
                             const int l = __ffsll((long long)bm) - 1;
                             bm &= bm - 1;
-                            const int kl = sample_of(i, l);
+                            const int kl = sample_at(l + WAVE * i);
                             int part = 0;
-                            for (int u = lane; u < nnc; u += WAVE)
-                                if (cover_exact(cd, ri, roff_i, kl, s_nbr_a[u], -1)) part += (1 << ACC_SHIFT) + u;
+                            for (int u = lane; u < nlist; u += WAVE) {
+                                const int ue = entry_of(u);
+                                if (cover_exact(cd, ri, roff_i, kl, s_nbr_a[ue], -1)) part += (1 << ACC_SHIFT) + ue;
+                            }
                             part = wave_sum_i(part);
                             if (lane == l) acc[i] = part;
                         }
                     }
                     const int C = acc[i] >> ACC_SHIFT;
-                    if (valid && C == 1) {
-                        // critically overlapped: only the overlapper's shifted copies can expose it
-                        const int k = sample_of(i, lane);
-                        const int u = acc[i] & ((1 << ACC_SHIFT) - 1);
-                        const NbrEntry<Real> e = s_nbr[u];
-                        const int aj = s_nbr_a[u];
-                        const Real base = Qx[i] * e.ax + Qy[i] * e.ay + Qz[i] * e.az - e.c0 - kq;
-                        const Real span = drr + k1 * fmax(fabs(e.ax), fmax(fabs(e.ay), fabs(e.az)));
-                        if (base - span <= guard) {
-                            // events: the shifted copies that no longer cover the sample
-                            const Real v0 = base + drr * Qx[i] - k1 * e.ax;
-                            const Real v1 = base + drr * Qy[i] - k1 * e.ay;
-                            const Real v2 = base + drr * Qz[i] - k1 * e.az;
-                            int n0 = v0 < (Real)0, n1 = v1 < (Real)0, n2 = v2 < (Real)0;
-                            if (MIXED && band3((float)v0, (float)v1, (float)v2)) {
-                                n0 += redo((float)v0, cd, ri, roff_i, k, aj, 0);
-                                n1 += redo((float)v1, cd, ri, roff_i, k, aj, 1);
-                                n2 += redo((float)v2, cd, ri, roff_i, k, aj, 2);
-                            }
-                            if (n0 | n1 | n2) atomicAdd(&s_ev[u], ev_word(n0, n1, n2));
-                        }
-                    }
                     if (valid && C >= 1) ++ncov;
-                    // step 2 for the exposed samples of this slot: one lane per
-                    // neighbour, the samples broadcast from their lanes
+                    int p = lane + WAVE * i;
+                    asm volatile("" : "+v"(p));  // computed here, not kept from the pass start
+                    const bool crit = valid && C == 1;
+                    const unsigned long long cm = ballot(crit);
+                    if (cm) push_pairs(crit, cm, (unsigned)(acc[i] & ((1 << ACC_SHIFT) - 1)) | (unsigned)p << 8 | 1u << 16);
+                    // exposed samples: one lane per neighbour, the samples
+                    // broadcast from their lanes
                     const unsigned long long em0 = ballot(valid && C == 0);
                     if (em0) {
-#pragma unroll
-                        for (int v = 0; v < NSLOT; ++v) {
-                            if (WAVE * v >= nnc) break;
-                            int u = lane + WAVE * v;
-                            // opaque to hoisting: recomputed per pass, not kept (and spilled) across them
-                            asm volatile("" : "+v"(u));
-                            const bool own = u < nnc;
-                            const NbrEntry<Real> e = s_nbr[own ? u : 0];
-                            const int aj = s_nbr_a[own ? u : 0];
-                            const Real lim = -(drr + k1 * fmax(fabs(e.ax), fmax(fabs(e.ay), fabs(e.az)))) - guard;
-                            // the neighbour's constants: base = q . a - (c0 + kq),
-                            // copy d tests base + drr q_d - k1 a_d
-                            Real cb = e.c0 + kq, sx = k1 * e.ax, sy = k1 * e.ay, sz = k1 * e.az;
-                            asm volatile("" : "+v"(sx), "+v"(sy), "+v"(sz));  // kept, not recomputed per sample
-                            int d0 = 0, d1 = 0, d2 = 0;
+#pragma unroll 1
+                        for (int u0 = 0; u0 < nlist; u0 += WAVE) {
+                            const bool own = u0 + lane < nlist;
+                            const int u = own ? entry_of(u0 + lane) : 0;
+                            const NbrEntry<Real> e = s_nbr[u];
+                            // below lim no axis reaches the sample
+                            const Real lim = own ? -(drr + k1 * fmax(fabs(e.ax), fmax(fabs(e.ay), fabs(e.az)))) - guard : (Real)1e30;
+                            const Real cb = -(e.c0 + kq);
                             unsigned long long em = em0;
                             while (em) {
                                 const int l = __ffsll((long long)em) - 1;
                                 em &= em - 1;
                                 const Real qx = bcast(Qx[i], l), qy = bcast(Qy[i], l), qz = bcast(Qz[i], l);
-                                const Real base = fma(qz, e.az, fma(qy, e.ay, qx * e.ax)) - cb;
-                                if (own && base >= lim) {
-                                    // events: the shifted copies that now cover the sample
-                                    const Real v0 = fma(drr, qx, base) - sx;
-                                    const Real v1 = fma(drr, qy, base) - sy;
-                                    const Real v2 = fma(drr, qz, base) - sz;
-                                    d0 -= v0 >= (Real)0;
-                                    d1 -= v1 >= (Real)0;
-                                    d2 -= v2 >= (Real)0;
-                                    if (MIXED && band3((float)v0, (float)v1, (float)v2)) {
-                                        const int kx = sample_of(i, l);
-                                        d0 += redo((float)v0, cd, ri, roff_i, kx, aj, 0);
-                                        d1 += redo((float)v1, cd, ri, roff_i, kx, aj, 1);
-                                        d2 += redo((float)v2, cd, ri, roff_i, kx, aj, 2);
-                                    }
-                                }
+                                const bool near = fma(qz, e.az, fma(qy, e.ay, fma(qx, e.ax, cb))) >= lim;
+                                const unsigned long long m = ballot(near);
+                                if (m) push_pairs(near, m, (unsigned)u | (unsigned)(l + WAVE * i) << 8);
                             }
-                            // the lane owns neighbour u here, but critical samples of
-                            // other lanes add to the same words: keep atomics
-                            if (d0 | d1 | d2) atomicAdd(&s_ev[u], ev_word(d0, d1, d2));
                         }
                     }
                 }
+                take_pairs(nq, 0);
                 __syncthreads();
                 // eq F_cav_patch: atom i gains G0_i ev / (N dr) per axis, neighbour j the opposite
                 const long long qf = glob(cd->qfix)[ai];
-                for (int u = lane; u < nnc; u += WAVE) {
+                for (int ul = lane; ul < nlist; ul += WAVE) {
+                    const int u = entry_of(ul);
                     const unsigned w = s_ev[u];
                     if (w == EV_INIT) continue;
                     const int e0 = ev_of(w, 0), e1 = ev_of(w, 1), e2 = ev_of(w, 2), aj = s_nbr_a[u];
