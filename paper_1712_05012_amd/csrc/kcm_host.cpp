@@ -138,10 +138,9 @@ void bond_class_masks(uint32_t m12[APR], uint32_t m13[APR], uint32_t m14[APR])
 // precisions, taken exactly as the force kernel applies them: the term flag
 // (1 or 0) times the class factor.
 template <typename Real>
-static int class_weights(const ChainDev &h, Real *tab)
+static void class_weights(const ChainDev &h, Real *tab)
 {
     const Real we0 = (h.terms & KCM_TERM_ELEC) ? (Real)1 : (Real)0, wv0 = (h.terms & KCM_TERM_VDW) ? (Real)1 : (Real)0;
-    int skip = 0;
     for (int c = 0; c < 4; ++c) {
         Real we = we0, wv = wv0;
         if (c == 1) { we = 0; wv = 0; }
@@ -149,9 +148,7 @@ static int class_weights(const ChainDev &h, Real *tab)
         else if (c == 3) { we *= (Real)h.w14e; wv *= (Real)h.w14v; }
         tab[2 * c] = we;
         tab[2 * c + 1] = wv;
-        if (we == (Real)0 && wv == (Real)0) skip |= 1 << c;
     }
-    return skip;
 }
 
 void bond_class_table(ChainDev &h)
@@ -165,8 +162,8 @@ void bond_class_table(ChainDev &h)
         }
         h.cls_word[s] = w;
     }
-    h.skip_cls32 = class_weights<float>(h, h.wtab32);
-    h.skip_cls64 = class_weights<double>(h, h.wtab64);
+    class_weights<float>(h, h.wtab32);
+    class_weights<double>(h, h.wtab64);
 }
 
 // Polar geodesic samples (Sec. 3.4): n_orb orbits at polar angles pi (o + 1/2) / n_orb,
@@ -259,8 +256,10 @@ Layout make_layout(int m, int n_orb, int side_chains)
     l.f_pair = take(32 * n);
     l.f_cav = take(24 * n);
     l.e_atom = take(32 * n);
-    l.q64 = take(32 * N);
-    l.q32 = take(16 * N);
+    // sample tables in whole passes of the force kernel (the rest stays zero)
+    const size_t Npad = (N + SAMPLE_PASS - 1) / SAMPLE_PASS * SAMPLE_PASS;
+    l.q64 = take(32 * Npad);
+    l.q32 = take(16 * Npad);
     l.total = (off + 255) & ~size_t(255);
     return l;
 }

@@ -17,6 +17,7 @@ constexpr int SCAN_MAX_CHUNKS = 16384; // chunks per chain the scatter's offset 
 constexpr int JOINT_BLOCK = 256;     // joints per workgroup of the torque / step / kinematics kernels
 constexpr int MAX_NBR = KCM_NBR_CHUNK; // solvation neighbours of one atom kept in LDS (the list, its atoms
                                       // and its events, 5,760 bytes in the mixed form, let 24 waves share a CU)
+constexpr int SAMPLE_PASS = 256;     // offset-sphere samples the force kernel takes at a time
 constexpr int MAX_REACH = 3;         // cell-stencil half width the force kernel supports (cells >= reach/3)
 constexpr double FIX_SCALE = 4294967296.0;  // fixed-point units per kcal/mol/A (2^32)
 constexpr int WPART = 10;            // doubles per wrench partial: F(3), T(3), E(3), flag
@@ -79,12 +80,10 @@ struct ChainDev {
     uint32_t pad_masks[2];
     // the same classes as one word per slot: two bits at bit 2 ((dres+1)*10 + slot_j),
     // 0 none, 1 1-2, 2 1-3, 3 1-4 (m12 before m13 before m14); the (elec, vdw)
-    // pair weights of each class in FP32 and FP64, and bit c set when both
-    // weights of class c are zero
+    // pair weights of each class in FP32 and FP64
     uint64_t cls_word[APR];
     float wtab32[8];
     double wtab64[8];
-    int32_t skip_cls32, skip_cls64;
 
     double *theta, *dtheta, *tau;
     double *mc_theta;    // [2][J]: accepted, then lowest angles of Monte Carlo minimization
@@ -114,8 +113,8 @@ struct ChainDev {
     double4 *f_pair;     // [n] Coulomb + LJ force
     long long *f_cav;    // [3n] solvation force, fixed point
     double4 *e_atom;     // [n] (elec, vdw, cav, exposed samples) per atom
-    double4 *q64;        // [N] unit sample directions
-    float4 *q32;         // [N]
+    double4 *q64;        // [N, rounded up to SAMPLE_PASS] unit sample directions, then zeros
+    float4 *q32;         // [likewise]
     Grid *grid;          // grid of the current iteration
     ChainStats *stats;
 };

@@ -1806,7 +1806,7 @@ __device__ __forceinline__ double cap_c0(double roff_i, double d2, double rj, do
     return fma(-rj, rj, fma(roff_i, roff_i, d2)) * inv_2roff;
 }
 
-constexpr int SPL = 4;                              // samples per lane in one pass: passes of 256 samples
+constexpr int SPL = SAMPLE_PASS / WAVE;             // samples per lane in one pass
 // Neighbours whose cap on the offset sphere is large (cosine of its angular
 // radius, c0/|a|, below CAP_SPLIT) lead the list: step 1 then reaches two
 // overlappers for every sample of a slot early and stops there.
@@ -2226,8 +2226,9 @@ __global__ __launch_bounds__(WAVE, sizeof(Real) == 4 ? 6 : 4) void k_force(Batch
     constexpr bool MIXED = sizeof(Real) == 4;
     __shared__ NbrEntry<Real> s_nbr[MAX_NBR];
     __shared__ int s_nbr_a[MAX_NBR];
-    __shared__ __align__(8) unsigned s_ev[MAX_NBR];  // net events of each neighbour in this pass
-    __shared__ unsigned s_pair[2 * WAVE];            // (sample, neighbour) pairs that await their displaced tests
+    __shared__ __align__(16) unsigned s_word[MAX_NBR + 2 * WAVE];
+    unsigned *const s_ev = s_word;                 // net events of each neighbour in this pass
+    unsigned *const s_pair = s_word + MAX_NBR;     // (sample, neighbour) pairs that await their displaced tests
 
     int atom = blockIdx.x;
     if (XCD) {
@@ -2329,14 +2330,24 @@ __global__ __launch_bounds__(WAVE, sizeof(Real) == 4 ? 6 : 4) void k_force(Batch
     const Real coul = (Real)cd->coulomb;
     const Real qi = pi.q, Ri = pi.R, sei = pi.se;
 
-    // Bond class of each atom of residues res_i - 1 .. res_i + 1 relative to
-    // atom i, two bits per atom (0 none, 1 1-2, 2 1-3, 3 1-4), and the pair
-    // weights (elec, vdw) of each class, copied to LDS after the window table
-    // below in the event array (free until the candidates are done).
+    // Pair weights of each atom of residues res_i - 1 .. res_i + 1 relative to
+    // atom i, and of any other atom in the last entry: (elec weight x coul x
+    // q_i, vdw weight, 12 x vdw weight), from the bond classes (two bits per
+    // atom: 0 none, 1 1-2, 2 1-3, 3 1-4).  They lie behind the start bits below
+    // (the words are free until the candidates are done).  A class of weight zero adds zeros: its
+    // atoms lie at the fixed distances of bonds and bond angles.
     const unsigned long long cls_word = cd->cls_word[slot_i];
-    const int skip_cls = MIXED ? cd->skip_cls32 : cd->skip_cls64;  // bit c: class c adds nothing
-    Real *s_wtab = reinterpret_cast<Real *>(s_ev + 2 * WAVE);
-    if (lane < 8) s_wtab[lane] = MIXED ? (Real)cd->wtab32[lane] : (Real)cd->wtab64[lane];
+    struct __align__(16) PairWeights {
+        Real el, vdw, vdw12, pad;
+    };
+    PairWeights *s_wtab = reinterpret_cast<PairWeights *>(s_word + WAVE);
+    static_assert(sizeof(unsigned) * WAVE + sizeof(PairWeights) * (3 * APR + 1) <= sizeof(s_word), "start bits and weights");
+    if (lane <= 3 * APR) {
+        const int cls = lane < 3 * APR ? (int)(cls_word >> (2 * lane)) & 3 : 0;
+        const Real we = MIXED ? (Real)cd->wtab32[2 * cls] : (Real)cd->wtab64[2 * cls];
+        const Real wv = MIXED ? (Real)cd->wtab32[2 * cls + 1] : (Real)cd->wtab64[2 * cls + 1];
+        s_wtab[lane] = {we * coul * qi, wv, (Real)12 * wv, (Real)0};
+    }
     __builtin_amdgcn_wave_barrier();
 
     // Sorted atom of candidate kw + lane, one window of 64 candidates at a
@@ -2383,28 +2394,24 @@ __global__ __launch_bounds__(WAVE, sizeof(Real) == 4 ? 6 : 4) void k_force(Batch
         const int aj = (int)__double_as_longlong(rj.w);
         if (valid && do_pair && d2 <= cut2) {
             // (dres + 1) APR + slot_j, in [0, 3 APR) iff |dres| <= 1
-            const int idx = aj - APR * res_i + APR;
-            const int cls = (unsigned)idx < 3u * APR ? (int)((cls_word >> (2 * idx)) & 3) : 0;
-            if (!((skip_cls >> cls) & 1)) {
-                const Real we = s_wtab[2 * cls], wv = s_wtab[2 * cls + 1];
-                const Real rx = (Real)ddx, ry = (Real)ddy, rz = (Real)ddz;
-                // mixed form: hardware reciprocal (1 ulp), far inside the force tolerance
-                const Real inv2 = MIXED ? (Real)__builtin_amdgcn_rcpf((float)d2) : (Real)1 / (Real)d2;
-                // eq 02 with eps = k_d d: E = (C/k_d) q_i q_j / d^2
-                const Real eel = we * coul * qi * pj.q * inv2;
-                // eq 03: E = eps_ij [(D/d)^12 - 2 (D/d)^6], D = R_i + R_j, eps_ij = sqrt(eps_i eps_j)
-                const Real D = Ri + pj.R;
-                const Real s2 = D * D * inv2, s6 = s2 * s2 * s2, s12 = s6 * s6;
-                const Real eij = sei * pj.se;
-                const Real elj = wv * eij * fma((Real)-2, s6, s12);
-                // |F|/d along r_i - r_j: 2 E_elec/d^2 + 12 eps (s12 - s6)/d^2
-                const Real fsc = fma((Real)2, eel, (Real)12 * wv * eij * (s12 - s6)) * inv2;
-                fx = fma(-fsc, rx, fx);
-                fy = fma(-fsc, ry, fy);
-                fz = fma(-fsc, rz, fz);
-                ee += (double)eel;
-                evw += (double)elj;
-            }
+            const PairWeights wt = s_wtab[min((unsigned)(aj - APR * res_i + APR), 3u * APR)];
+            const Real rx = (Real)ddx, ry = (Real)ddy, rz = (Real)ddz;
+            // mixed form: hardware reciprocal (1 ulp), far inside the force tolerance
+            const Real inv2 = MIXED ? (Real)__builtin_amdgcn_rcpf((float)d2) : (Real)1 / (Real)d2;
+            // eq 02 with eps = k_d d: E = (C/k_d) q_i q_j / d^2
+            const Real eel = wt.el * pj.q * inv2;
+            // eq 03: E = eps_ij [(D/d)^12 - 2 (D/d)^6], D = R_i + R_j, eps_ij = sqrt(eps_i eps_j)
+            const Real D = Ri + pj.R;
+            const Real s2 = D * D * inv2, s6 = s2 * s2 * s2, s12 = s6 * s6;
+            const Real eij = sei * pj.se;
+            const Real elj = wt.vdw * eij * fma((Real)-2, s6, s12);
+            // |F|/d along r_i - r_j: 2 E_elec/d^2 + 12 eps (s12 - s6)/d^2
+            const Real fsc = fma((Real)2, eel, wt.vdw12 * eij * (s12 - s6)) * inv2;
+            fx = fma(-fsc, rx, fx);
+            fy = fma(-fsc, ry, fy);
+            fz = fma(-fsc, rz, fz);
+            ee += (double)eel;
+            evw += (double)elj;
         }
         bool in_cav = false, front = false;
         double c0 = 0.0;
@@ -2547,9 +2554,8 @@ __global__ __launch_bounds__(WAVE, sizeof(Real) == 4 ? 6 : 4) void k_force(Batch
                 int acc[SPL];
 #pragma unroll
                 for (int i = 0; i < SPL; ++i) {
-                    const int k = kb + lane + WAVE * i;
-                    Qx[i] = Qy[i] = Qz[i] = (Real)0;
-                    if (k < N) load_q<Real>(cd, k, Qx[i], Qy[i], Qz[i]);
+                    // (the tables are padded to whole passes)
+                    load_q<Real>(cd, kb + lane + WAVE * i, Qx[i], Qy[i], Qz[i]);
                     acc[i] = 0;
                     amin[i] = (Real)1e30;
                 }
@@ -2628,6 +2634,7 @@ __global__ __launch_bounds__(WAVE, sizeof(Real) == 4 ? 6 : 4) void k_force(Batch
                     int next = 0;
 #pragma unroll
                     for (int i = 0; i < SPL; ++i) {
+                        if (WAVE * i >= kept) break;  // nothing reads the slots past the staged samples
                         int p = lane + WAVE * i;
                         asm volatile("" : "+v"(p));  // recomputed here, not kept (and spilled) from the pass start
                         acc[i] = 2 << ACC_SHIFT;
@@ -2701,7 +2708,9 @@ __global__ __launch_bounds__(WAVE, sizeof(Real) == 4 ? 6 : 4) void k_force(Batch
                 };
 #pragma unroll
                 for (int i = 0; i < SPL; ++i) {
-                    const bool valid = kept < 0 ? kb + lane + WAVE * i < N : lane + WAVE * i < kept;
+                    const int held = kept < 0 ? N - kb : kept;  // places that hold a sample
+                    if (WAVE * i >= held) break;
+                    const bool valid = lane + WAVE * i < held;
                     if (MIXED) {
                         // a test within the band of its threshold: the whole wave
                         // recounts that sample in FP64, one lane per neighbour
