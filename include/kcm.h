@@ -323,11 +323,12 @@ kcm_status kcm_set_timing(int every);
 kcm_status kcm_set_graphs(int iterations);
 
 /* Launch shape of the force kernel (process-wide), for the autotuner:
- * 0 (default): each lane loads two candidates per trip of the candidate loop,
- * and step 1 reads the solvation neighbours in blocks of 4 before it checks
- * which sample slots are done; 1: one candidate per trip, blocks of 4;
- * 2: as 1, and 3: as 0, with the atoms handed to the 8 XCDs in contiguous
- * eighths (XCD-aware order).  Every shape gives identical
+ * 0 (default): each lane loads one candidate per trip of the candidate loop,
+ * step 1 reads the solvation neighbours in blocks of 4 before it checks which
+ * sample slots are done, and the atoms go to the 8 XCDs in chunks of 256 in
+ * turn; 1: as 0, with the atoms in plain order; 2: as 0, with the atoms handed
+ * to the XCDs in contiguous eighths; 3: as 0, with two candidates per trip.
+ * Every shape gives identical
  * results (the same visiting order and decisions).  Graphs captured in
  * another shape are captured again.  KCM_E_INVAL unless
  * 0 <= variant < KCM_FORCE_VARIANTS. */

@@ -1814,16 +1814,23 @@ constexpr float CAP_SPLIT = 0.6f;
 // Launch shapes of the force kernel (kcm_set_force_variant): candidates each
 // lane loads per trip of the candidate loop (CPT), the neighbours step 1
 // reads as one block before it checks the slots' saturation (SATB), and the
-// order of the atoms over the workgroups: cell order, or XCD-aware (the
-// workgroups go to the 8 XCDs in turn; XCD x takes the x-th contiguous eighth
-// of the cell-ordered atoms, so that its L2 serves one region of space).
+// order of the atoms over the workgroups, which go to the 8 XCDs in turn: cell
+// order; XCD-aware by chunks (each XCD takes chunks of XCD_CHUNK consecutive
+// cell-ordered atoms in turn, so that its L2 serves a few regions of space and
+// all XCDs see the same mix of atoms); or XCD-aware by eighths (XCD x takes the
+// x-th contiguous eighth).  Force kernel in shapes 0 to 3: 256-chain batch
+// 2,140, 2,180, 2,175, 2,197 us; 10,000-residue globule 301, 303, 307, 314; 256
+// short chains in vacuum (FP64) 41.9, 46.7, 40.7, 41; sixteen chains of unequal
+// density 171, 174, 215, 220 (one eighth holds most of the work).
 // Every shape visits the candidates and appends the neighbours in the same
 // order, and takes the same decisions: the results are the same bit for bit.
+enum XcdOrder { CELL_ORDER, XCD_CHUNKS, XCD_EIGHTHS };
 struct ForceShape {
     int cpt, satb;
-    bool xcd;
+    XcdOrder order;
 };
-constexpr ForceShape FORCE_SHAPES[] = {{2, 4, false}, {1, 4, false}, {1, 4, true}, {2, 4, true}};
+constexpr ForceShape FORCE_SHAPES[] = {{1, 4, XCD_CHUNKS}, {1, 4, CELL_ORDER}, {1, 4, XCD_EIGHTHS}, {2, 4, XCD_CHUNKS}};
+constexpr int XCD_CHUNK = 256;
 constexpr int N_XCD = 8;
 // Step-1 count of a sample: acc = (covering neighbours << ACC_SHIFT) + (sum of
 // their slots), so acc >> ACC_SHIFT == 1 leaves the single overlapper in the
@@ -2219,7 +2226,7 @@ __device__ __noinline__ ChunkedSasa sasa_chunked(CDev cd, const ChunkArgs c, Nbr
 // waves with room to spare (3.06 against 3.39 ms on the 256-chain batch when
 // measured, with a longer list); seven spill in the hot loops.  The FP64 form:
 // four (127 registers; its 9,600 bytes allow 16 waves per CU).
-template <typename Real, int CPT, int SAT_CHECK, bool XCD>
+template <typename Real, int CPT, int SAT_CHECK, XcdOrder ORDER>
 __global__ __launch_bounds__(WAVE, sizeof(Real) == 4 ? 6 : 4) void k_force(Batch bt)
 {
     static_assert(SAT_CHECK * (SAT_CHECK - 1) / 2 < 32 && 32 + SAT_CHECK <= 64, "block code of step 1");
@@ -2231,10 +2238,14 @@ __global__ __launch_bounds__(WAVE, sizeof(Real) == 4 ? 6 : 4) void k_force(Batch
     unsigned *const s_pair = s_word + MAX_NBR;     // (sample, neighbour) pairs that await their displaced tests
 
     int atom = blockIdx.x;
-    if (XCD) {
-        const int nq = bt.total_atoms / N_XCD, nr = bt.total_atoms % N_XCD;
+    if (ORDER != CELL_ORDER) {
         const int x = blockIdx.x % N_XCD, k = blockIdx.x / N_XCD;
-        atom = x * nq + min(x, nr) + k;
+        if (ORDER == XCD_EIGHTHS) {
+            const int nq = bt.total_atoms / N_XCD, nr = bt.total_atoms % N_XCD;
+            atom = x * nq + min(x, nr) + k;
+        } else if (atom < bt.total_atoms / (N_XCD * XCD_CHUNK) * (N_XCD * XCD_CHUNK)) {
+            atom = (k / XCD_CHUNK * N_XCD + x) * XCD_CHUNK + k % XCD_CHUNK;  // the last part stays in cell order
+        }
     }
     // the atom's chain: from the map of the batch, the chain of the first atom
     // of each group and a step per chain border in it (two dependent loads
@@ -2997,7 +3008,7 @@ template <int V>
 void launch_force_shape(const Batch &b, int precision, hipStream_t s)
 {
     constexpr int C = FORCE_SHAPES[V].cpt, S = FORCE_SHAPES[V].satb;
-    constexpr bool X = FORCE_SHAPES[V].xcd;
+    constexpr XcdOrder X = FORCE_SHAPES[V].order;
     if (precision == 1)
         hipLaunchKernelGGL((k_force<float, C, S, X>), dim3(b.total_atoms), dim3(WAVE), 0, s, b);
     else
