@@ -22,11 +22,14 @@
  *    owned by the caller: kcm_build_chain lays a chain out inside the block it
  *    is given and never frees it.  The one exception is per-call bookkeeping:
  *    kcm_step, kcm_fold, kcm_mc_minimize and kcm_set_theta_batch keep, per
- *    (device, stream), a device table of the chain set (descriptor pointers
- *    and four offset arrays, about 24 bytes per chain), the gathered per-chain
- *    records (device and pinned host) and the captured HIP graphs; these are
- *    allocated when a larger set first arrives, reused while the set is
- *    unchanged (graphs are dropped when one of their chains is freed) and
+ *    (device, stream), device tables of the last four chain sets (descriptor
+ *    pointers, offset arrays and a map of atoms to chains, about 28 bytes per
+ *    chain and up to 128 KiB), each with the per-chain records (pinned host
+ *    memory) and the captured HIP graphs; these are allocated when a set first
+ *    arrives, reused while it comes back (graphs are dropped when one of their
+ *    chains is freed) and kept until the process ends.  kcm_get_state and
+ *    kcm_mc_best_theta share up to four pinned buffers of 1 MiB, allocated when
+ *    first needed and
  *    kept until the process ends.  kcm_step_noalloc takes the same
  *    bookkeeping from static device memory and allocates nothing.
  *    Host-side handles are owned by the library (kcm_chain_free).  hip_stream
@@ -318,8 +321,9 @@ kcm_status kcm_set_timing(int every);
  * captures that many consecutive iterations of a call's chains as one HIP
  * graph (on a private stream, once per batch composition and depth) and
  * replays it on hip_stream, with single-iteration replays for the rest of a
- * call; iterations = 0 launches the kernels directly.  Every mode gives
- * identical results.  KCM_E_INVAL unless 0 <= iterations <= 64. */
+ * call; iterations = 0 launches the kernels directly.  Calls of short or many
+ * chains, whose iterations are two launches, are always launched directly.
+ * Every mode gives identical results.  KCM_E_INVAL unless 0 <= iterations <= 64. */
 kcm_status kcm_set_graphs(int iterations);
 
 /* Launch shape of the force kernel (process-wide), for the autotuner:

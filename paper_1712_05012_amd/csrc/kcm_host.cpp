@@ -10,6 +10,7 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
+#include <deque>
 #include <limits>
 #include <mutex>
 #include <string>
@@ -286,8 +287,10 @@ kcm_status check_inputs(const kcm_chain_desc *d, const kcm_params *p)
 }
 
 // ---------------------------------------------------------------------------
-// batch tables: per (device, stream) a device array of chain descriptors and
-// the cumulative atom offsets the force kernel maps its workgroups with
+// batch tables: per (device, stream) and chain set a device array of chain
+// descriptors and the cumulative atom offsets the force kernel maps its
+// workgroups with; a stream keeps its last kTablesPerStream sets, so that a
+// program that steps a few sets in turn uploads and captures each once
 // ---------------------------------------------------------------------------
 struct Table {
     int device = -1;
@@ -300,15 +303,19 @@ struct Table {
     int graph_prec = -1;
     hipGraphExec_t graph_n = nullptr;  // graph_n_depth iterations in one graph
     int graph_n_prec = -1, graph_n_depth = 0;
-    ChainStats *stats_dev = nullptr;   // [stats_cap] the batch's records, gathered on the device
-    ChainStats *stats_host = nullptr;  // [stats_cap] pinned host copy of them
+    ChainStats *stats_host = nullptr;  // [stats_cap] pinned: the batch's records, written by the gather kernel
     int stats_cap = 0;
-    int64_t *mc_off_dev = nullptr;     // [mc_off_cap] per-chain offsets into a Monte Carlo call's perturbations
+    int64_t *mc_off_dev = nullptr;     // [mc_off_cap] per-chain offsets into a call's angles or perturbations
     int mc_off_cap = 0;
+    int64_t mc_off_per = -1;           // what they were made for, per joint (-1: another chain set)
+    uint64_t last_use = 0;
 };
+constexpr int kTablesPerStream = 4;
 
 std::mutex g_mu;
-std::vector<Table> g_tables;
+std::deque<Table> g_tables;
+uint64_t g_table_clock = 0;
+uint64_t g_check_mark = 0;              // check_chains: the current call's mark
 int g_graphs = 1;                       // iterations per captured graph (0: direct launches)
 int g_force_shape = 0;                  // launch shape of the force kernel (kcm_set_force_variant)
 constexpr int kMaxGraphDepth = 64;
@@ -455,6 +462,7 @@ struct kcm_chain {
     int njb;             // joint blocks (backbone blocks, then side-chain blocks)
     std::vector<unsigned char> staging;  // host source of the build copies
     bool boot = true;    // the conformation has no grid yet (built, or new angles)
+    uint64_t mark = 0;   // the last call that checked it (check_chains)
 };
 
 namespace {
@@ -463,18 +471,33 @@ kcm_status ensure_table(kcm_chain *const *chains, int n_chains, hipStream_t stre
 {
     int dev = 0;
     HIP_TRY(hipGetDevice(&dev));
-    Table *t = nullptr;
-    for (auto &x : g_tables)
-        if (x.device == dev && x.stream == stream) t = &x;
-    if (!t) {
+    // the stream's table of this chain set, else its least recently used one
+    // (a set with a freed chain was cleared and counts as never used)
+    Table *t = nullptr, *oldest = nullptr;
+    int held = 0;
+    for (auto &x : g_tables) {
+        if (x.device != dev || x.stream != stream) continue;
+        ++held;
+        if ((int)x.chains.size() == n_chains && std::equal(chains, chains + n_chains, x.chains.begin())) {
+            t = &x;
+            break;
+        }
+        const uint64_t age = x.chains.empty() ? 0 : x.last_use;
+        if (!oldest || age < (oldest->chains.empty() ? 0 : oldest->last_use)) oldest = &x;
+    }
+    const bool same = t != nullptr;
+    if (!t && (held < kTablesPerStream && !(oldest && oldest->chains.empty()))) {
         g_tables.emplace_back();
         t = &g_tables.back();
         t->device = dev;
         t->stream = stream;
+    } else if (!t) {
+        t = oldest;
     }
-    bool same = (int)t->chains.size() == n_chains;
-    for (int i = 0; same && i < n_chains; ++i) same = t->chains[i] == chains[i];
+    t->last_use = ++g_table_clock;
     if (!same) {
+        t->chains.clear();  // until the new set is in place
+        t->mc_off_per = -1;
         const size_t ints = ((sizeof(int32_t) * (n_chains + 1) + 255) & ~size_t(255));
         const size_t off_pos = (sizeof(ChainDev *) * n_chains + 255) & ~size_t(255);
         const size_t blk_pos = off_pos + ints;
@@ -570,28 +593,106 @@ kcm_status write_field(T *dev_field, T value, hipStream_t s)
     return KCM_OK;
 }
 
-// The records of every chain of the table's batch, read back with one gather
-// kernel and one copy.  Synchronises the stream.
+// Waits until the stream's last kernel has stored seq to the n pinned flags:
+// polls for a while (a hundred microseconds at most; the end of a stream's work
+// is seen some five microseconds sooner so), then synchronises the stream.
+kcm_status wait_flags(const unsigned *flags, int n, unsigned seq, hipStream_t stream)
+{
+    auto here = [&] {
+        for (int i = 0; i < n; ++i)
+            if (__atomic_load_n(flags + i, __ATOMIC_ACQUIRE) != seq) return false;
+        return true;
+    };
+    const auto t0 = std::chrono::steady_clock::now();
+    for (int i = 1; !here(); ++i)
+        if (i % 64 == 0 && std::chrono::steady_clock::now() - t0 > std::chrono::microseconds(100)) {
+            HIP_TRY(hipStreamSynchronize(stream));
+            if (!here()) return fail(KCM_E_DEVICE, "a copy to the host did not complete");
+            break;
+        }
+    return KCM_OK;
+}
+
+// The records of every chain of the table's batch: one gather kernel writes
+// them to pinned host memory, and a flag after them where one workgroup does it
+// (up to kFlagChains chains).  Synchronises the stream.
+constexpr int kFlagChains = 256;
 kcm_status gather_stats(Table *t, hipStream_t stream, std::vector<ChainStats> &out)
 {
     const int n = t->batch.n_chains;
     if (n > t->stats_cap) {
         HIP_TRY(hipStreamSynchronize(stream));
-        if (t->stats_dev) HIP_TRY(hipFree(t->stats_dev));
         if (t->stats_host) HIP_TRY(hipHostFree(t->stats_host));
-        t->stats_dev = nullptr;
         t->stats_host = nullptr;
         t->stats_cap = 0;
         const int cap = std::max(2 * n, 64);
-        HIP_TRY(hipMalloc(&t->stats_dev, sizeof(ChainStats) * cap));
-        HIP_TRY(hipHostMalloc(&t->stats_host, sizeof(ChainStats) * cap, hipHostMallocDefault));
+        // one record more, for the flag
+        HIP_TRY(hipHostMalloc(&t->stats_host, sizeof(ChainStats) * (cap + 1), hipHostMallocDefault));
+        std::memset(t->stats_host + cap, 0, sizeof(ChainStats));
         t->stats_cap = cap;
     }
-    HIP_TRY(launch_stats_gather(t->batch, t->stats_dev, stream));
-    HIP_TRY(hipMemcpyAsync(t->stats_host, t->stats_dev, sizeof(ChainStats) * n, hipMemcpyDeviceToHost, stream));
-    HIP_TRY(hipStreamSynchronize(stream));
+    if (n <= kFlagChains) {
+        unsigned *flag = reinterpret_cast<unsigned *>(t->stats_host + t->stats_cap);
+        const unsigned seq = *flag + 1;
+        HIP_TRY(launch_stats_gather(t->batch, t->stats_host, flag, seq, stream));
+        if (kcm_status s = wait_flags(flag, 1, seq, stream); s != KCM_OK) return s;
+    } else {
+        HIP_TRY(launch_stats_gather(t->batch, t->stats_host, nullptr, 0, stream));
+        HIP_TRY(hipStreamSynchronize(stream));
+    }
     out.assign(t->stats_host, t->stats_host + n);
     return KCM_OK;
+}
+
+// Host reads of a chain's arrays go through a pinned box that one kernel on the
+// caller's stream fills: the angles of a short chain 8 us after an idle stream,
+// where a copy to pageable memory takes 20.  A box serves one call at a time;
+// a call that finds none free (or reads more than a box holds, or from another
+// device than the current one) synchronises and copies instead.
+constexpr size_t kBoxBytes = 1 << 20;
+struct Box {
+    std::mutex mu;
+    unsigned char *mem = nullptr;  // kBoxBytes, then the flags; kept until the process ends
+    unsigned seq = 0;
+};
+Box g_boxes[4];
+
+// The parts in order, each where its dst says; true when they have been read
+// (or *st says why not), false when the caller has to copy.
+bool box_read(const kcm_chain *c, const BoxRead &what, double *const (&dst)[BOX_PARTS], hipStream_t stream, kcm_status *st)
+{
+    *st = KCM_OK;
+    int64_t total = 0;
+    for (int k = 0; k < what.n_parts; ++k) total += what.n[k];
+    if (total == 0) return true;
+    int dev = -1;
+    if ((size_t)total * 8 > kBoxBytes || hipGetDevice(&dev) != hipSuccess || dev != c->device) return false;
+    for (Box &b : g_boxes) {
+        std::unique_lock<std::mutex> lock(b.mu, std::try_to_lock);
+        if (!lock.owns_lock()) continue;
+        if (!b.mem) {
+            void *p = nullptr;
+            if (hipHostMalloc(&p, kBoxBytes + 256, hipHostMallocPortable) != hipSuccess) {
+                (void)hipGetLastError();
+                return false;
+            }
+            b.mem = static_cast<unsigned char *>(p);
+            std::memset(b.mem + kBoxBytes, 0, 256);
+        }
+        const int blocks = (int)std::min<int64_t>(BOX_BLOCKS, (total + 4095) / 4096);
+        unsigned *flags = reinterpret_cast<unsigned *>(b.mem + kBoxBytes);
+        if (launch_box_read(what, reinterpret_cast<double *>(b.mem), flags, ++b.seq, blocks, stream) != hipSuccess) {
+            (void)hipGetLastError();
+            return false;
+        }
+        *st = wait_flags(flags, blocks, b.seq, stream);
+        if (*st == KCM_OK) {
+            const double *at = reinterpret_cast<const double *>(b.mem);
+            for (int k = 0; k < what.n_parts; at += what.n[k++]) std::memcpy(dst[k], at, 8 * (size_t)what.n[k]);
+        }
+        return true;
+    }
+    return false;
 }
 
 // Whether kernels may read p: device, managed or pinned host memory known to
@@ -611,6 +712,8 @@ bool device_readable(const void *p)
 kcm_status upload_joint_offsets(Table *t, kcm_chain *const *chains, int n_chains, int64_t per_joint,
                                 hipStream_t stream)
 {
+    if (t->mc_off_per == per_joint) return KCM_OK;  // of this chain set already
+    t->mc_off_per = -1;
     if (n_chains + 1 > t->mc_off_cap) {
         HIP_TRY(hipStreamSynchronize(stream));
         if (t->mc_off_dev) HIP_TRY(hipFree(t->mc_off_dev));
@@ -625,9 +728,11 @@ kcm_status upload_joint_offsets(Table *t, kcm_chain *const *chains, int n_chains
     HIP_TRY(hipMemcpyAsync(t->mc_off_dev, off.data(), sizeof(int64_t) * (n_chains + 1), hipMemcpyHostToDevice,
                            stream));
     HIP_TRY(hipStreamSynchronize(stream));
+    t->mc_off_per = per_joint;
     return KCM_OK;
 }
 
+// (with g_mu held: a chain met twice carries the call's mark already)
 kcm_status check_chains(kcm_chain *const *chains, int n_chains, int *precision)
 {
     if (!chains || n_chains < 1) return fail(KCM_E_INVAL, "no chains");
@@ -638,10 +743,11 @@ kcm_status check_chains(kcm_chain *const *chains, int n_chains, int *precision)
         if (chains[i]->device != dev) return fail(KCM_E_INVAL, "chain lives on another device");
         if (chains[i]->h.precision != chains[0]->h.precision) return fail(KCM_E_INVAL, "chains of one call must share precision");
     }
-    std::vector<const kcm_chain *> sorted(chains, chains + n_chains);
-    std::sort(sorted.begin(), sorted.end());
-    if (std::adjacent_find(sorted.begin(), sorted.end()) != sorted.end())
-        return fail(KCM_E_INVAL, "a chain appears twice in one call");
+    ++g_check_mark;
+    for (int i = 0; i < n_chains; ++i) {
+        if (chains[i]->mark == g_check_mark) return fail(KCM_E_INVAL, "a chain appears twice in one call");
+        chains[i]->mark = g_check_mark;
+    }
     *precision = chains[0]->h.precision;
     return KCM_OK;
 }
@@ -878,7 +984,9 @@ kcm_status iterate_locked(Table *t, kcm_chain *const *chains, int n_chains, int 
                           bool boot_all, bool final)
 {
     const Batch &bt = t->batch;
-    const int depth = g_graphs;
+    // two launches an iteration need no graph: queueing them takes the host less
+    // time than the GPU takes for them, and capture costs a new set 150 us
+    const int depth = bt.fused ? 0 : g_graphs;
     // a captured graph holds the precision's kernels in the current force shape
     const int key = prec + 16 * g_force_shape;
     if (depth > 0 && n_iter > 0 && (!t->graph || t->graph_prec != key)) {
@@ -958,10 +1066,10 @@ kcm_status kcm_step(kcm_chain *const *chains, int n_chains, int n_iter, void *hi
 {
     if (n_iter < 0) return fail(KCM_E_INVAL, "n_iter < 0");
     int prec = 0;
-    kcm_status s = check_chains(chains, n_chains, &prec);
-    if (s != KCM_OK) return s;
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     std::lock_guard<std::mutex> lock(g_mu);
+    kcm_status s = check_chains(chains, n_chains, &prec);
+    if (s != KCM_OK) return s;
     std::vector<ChainStats> st;
     s = step_locked(chains, n_chains, n_iter, prec, stream, reports ? &st : nullptr);
     if (s != KCM_OK || !reports) return s;
@@ -1150,7 +1258,7 @@ kcm_status kcm_step_noalloc(kcm_chain *const *chains, int n_chains, int n_iter, 
     }
     if (!reports) return KCM_OK;
     ChainStats *dst = reinterpret_cast<ChainStats *>(d->ptr + kNaTable);
-    if ((e = launch_stats_gather(bt, dst, stream)) != hipSuccess ||
+    if ((e = launch_stats_gather(bt, dst, nullptr, 0, stream)) != hipSuccess ||
         (e = hipMemcpyAsync(g_noalloc_stats, dst, sizeof(ChainStats) * n_chains, hipMemcpyDeviceToHost, stream)) !=
             hipSuccess ||
         (e = hipStreamSynchronize(stream)) != hipSuccess)
@@ -1177,11 +1285,11 @@ kcm_status kcm_fold(kcm_chain *const *chains, int n_chains, double tol_dtheta, i
                     void *hip_stream, kcm_fold_result *results)
 {
     int prec = 0;
+    hipStream_t stream = static_cast<hipStream_t>(hip_stream);
+    std::lock_guard<std::mutex> lock(g_mu);
     kcm_status s = check_chains(chains, n_chains, &prec);
     if (s != KCM_OK) return s;
     if (max_iter < 0 || check_every < 1) return fail(KCM_E_INVAL, "max_iter < 0 or check_every < 1");
-    hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-    std::lock_guard<std::mutex> lock(g_mu);
     const auto t0 = std::chrono::steady_clock::now();
     Table *t = nullptr;
     if ((s = ensure_table(chains, n_chains, stream, &t)) != KCM_OK) return s;
@@ -1223,6 +1331,7 @@ kcm_status kcm_mc_minimize(kcm_chain *const *chains, int32_t n_chains, int32_t n
                            const double *delta, const double *u, void *hip_stream, kcm_mc_result *results)
 {
     int prec = 0;
+    std::lock_guard<std::mutex> lock(g_mu);
     kcm_status s = check_chains(chains, n_chains, &prec);
     if (s != KCM_OK) return s;
     if (n_trials < 0 || n_descent < 0) return fail(KCM_E_INVAL, "n_trials < 0 or n_descent < 0");
@@ -1231,7 +1340,6 @@ kcm_status kcm_mc_minimize(kcm_chain *const *chains, int32_t n_chains, int32_t n
     if (n_trials > 0 && (!device_readable(delta) || !device_readable(u)))
         return fail(KCM_E_INVAL, "delta and u must be device memory");
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-    std::lock_guard<std::mutex> lock(g_mu);
     Table *t = nullptr;
     if ((s = ensure_table(chains, n_chains, stream, &t)) != KCM_OK) return s;
     // per-chain offsets of the perturbations: chain c's [n_trials][J_c] block
@@ -1277,6 +1385,10 @@ kcm_status kcm_mc_best_theta(const kcm_chain *c, void *hip_stream, double *theta
 {
     if (!c || !theta) return fail(KCM_E_INVAL, "null chain or theta");
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
+    BoxRead what{};
+    what.add(c->h.mc_theta + c->J, c->J);
+    kcm_status st = KCM_OK;
+    if (box_read(c, what, {theta}, s, &st)) return st;
     HIP_TRY(hipMemcpyAsync(theta, c->h.mc_theta + c->J, 8 * (size_t)c->J, hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
     return KCM_OK;
@@ -1287,6 +1399,15 @@ kcm_status kcm_get_state(const kcm_chain *c, void *hip_stream, double *theta, do
 {
     if (!c) return fail(KCM_E_INVAL, "null chain");
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
+    BoxRead what{};
+    double *dst[BOX_PARTS] = {};
+    if (theta) dst[what.add(c->h.theta, c->J)] = theta;
+    if (tau) dst[what.add(c->h.tau, c->J)] = tau;
+    if (dtheta) dst[what.add(c->h.dtheta, c->J)] = dtheta;
+    if (xyz) dst[what.add_atoms(c->h.r, nullptr, c->n)] = xyz;
+    if (force) dst[what.add_atoms(c->h.f_pair, c->h.f_cav, c->n)] = force;
+    kcm_status st = KCM_OK;
+    if (what.n_parts > 0 && box_read(c, what, dst, s, &st)) return st;
     HIP_TRY(hipStreamSynchronize(s));
     if (theta) HIP_TRY(hipMemcpy(theta, c->h.theta, 8 * c->J, hipMemcpyDeviceToHost));
     if (tau) HIP_TRY(hipMemcpy(tau, c->h.tau, 8 * c->J, hipMemcpyDeviceToHost));
@@ -1379,12 +1500,12 @@ kcm_status kcm_set_theta(kcm_chain *c, const double *theta, void *hip_stream)
 kcm_status kcm_set_theta_batch(kcm_chain *const *chains, int32_t n_chains, const double *theta, void *hip_stream)
 {
     int prec = 0;
+    std::lock_guard<std::mutex> lock(g_mu);
     kcm_status s = check_chains(chains, n_chains, &prec);
     if (s != KCM_OK) return s;
     if (!theta) return fail(KCM_E_INVAL, "null theta");
     if (!device_readable(theta)) return fail(KCM_E_INVAL, "theta must be device memory");
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-    std::lock_guard<std::mutex> lock(g_mu);
     Table *t = nullptr;
     if ((s = ensure_table(chains, n_chains, stream, &t)) != KCM_OK) return s;
     if ((s = upload_joint_offsets(t, chains, n_chains, 1, stream)) != KCM_OK) return s;

@@ -190,7 +190,34 @@ hipError_t launch_mc_decide(const Batch &b, int mode, const double *u, int n_tri
                             hipStream_t s);
 hipError_t launch_mc_apply(const Batch &b, hipStream_t s);
 hipError_t launch_set_theta(const Batch &b, const double *theta, const int64_t *theta_off, hipStream_t s);
-hipError_t launch_stats_gather(const Batch &b, ChainStats *out, hipStream_t s);
+// The records of all chains to `out`; with a flag (pinned host memory, as out
+// then is) seq is stored to it when they have arrived.
+hipError_t launch_stats_gather(const Batch &b, ChainStats *out, unsigned *flag, unsigned seq, hipStream_t s);
+// What a host read packs into pinned memory, part after part: n doubles from
+// src; or, for atoms, the x, y, z of n / 3 of them (4 doubles apart at src),
+// with the fixed-point solvation force f_cav added if given.  Workgroup b stores
+// seq to flags[b] when its share has arrived.
+constexpr int BOX_PARTS = 5, BOX_BLOCKS = 16;
+struct BoxRead {
+    const double *src[BOX_PARTS];
+    const long long *f_cav[BOX_PARTS];
+    int64_t n[BOX_PARTS];
+    bool atoms[BOX_PARTS];
+    int n_parts;
+    int add(const double *s, int64_t count)
+    {
+        src[n_parts] = s;
+        n[n_parts] = count;
+        return n_parts++;
+    }
+    int add_atoms(const double4 *s, const long long *cav, int64_t n_atoms)
+    {
+        f_cav[n_parts] = cav;
+        atoms[n_parts] = true;
+        return add(reinterpret_cast<const double *>(s), 3 * n_atoms);
+    }
+};
+hipError_t launch_box_read(const BoxRead &what, double *out, unsigned *flags, unsigned seq, int blocks, hipStream_t s);
 hipError_t launch_fold_control(const Batch &b, int mode, double tol, int64_t max_iter, hipStream_t s);
 
 }  // namespace kcm

@@ -1023,13 +1023,42 @@ __global__ void k_finish(Batch bt)
     st->active = running(st);
 }
 
-// k_stats_gather: the records of every chain of the batch into one array, so
-// that the host reads them back with a single copy.
-__global__ void k_stats_gather(Batch bt, ChainStats *__restrict__ out)
+// Stores seq to a flag in pinned host memory once every store of the workgroup
+// before it has reached the host (one workgroup).
+__device__ __forceinline__ void signal_host(unsigned *flag, unsigned seq)
 {
-    const int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= bt.n_chains) return;
-    out[c] = *bt.table[c]->stats;
+    __threadfence_system();
+    __syncthreads();
+    if (threadIdx.x == 0) __hip_atomic_store(flag, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+// k_stats_gather: the records of every chain of the batch into one array, so
+// that the host reads them back at once.  With a flag one workgroup does it all.
+__global__ __launch_bounds__(1024) void k_stats_gather(Batch bt, ChainStats *__restrict__ out, unsigned *flag, unsigned seq)
+{
+    constexpr int W = sizeof(ChainStats) / sizeof(double);
+    static_assert(W * sizeof(double) == sizeof(ChainStats), "records are whole doubles");
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < (int64_t)W * bt.n_chains; i += (int64_t)gridDim.x * blockDim.x)
+        reinterpret_cast<double *>(out)[i] = reinterpret_cast<const double *>(bt.table[i / W]->stats)[i % W];
+    if (flag) signal_host(flag, seq);
+}
+
+// k_box_read: a host read's values into pinned memory, then the flag of each
+// workgroup's share.
+__global__ __launch_bounds__(1024) void k_box_read(BoxRead what, double *__restrict__ out, unsigned *flags, unsigned seq)
+{
+    const int64_t i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x, step = (int64_t)gridDim.x * blockDim.x;
+    for (int k = 0; k < what.n_parts; ++k) {
+        const double *__restrict__ src = what.src[k];
+        const long long *__restrict__ cav = what.f_cav[k];
+        for (int64_t i = i0; i < what.n[k]; i += step) {
+            double v = src[what.atoms[k] ? i + i / 3 : i];  // x, y, z of every four
+            if (cav) v += (double)cav[i] / FIX_SCALE;
+            out[i] = v;
+        }
+        out += what.n[k];
+    }
+    signal_host(flags + blockIdx.x, seq);
 }
 
 // k_fold_control: FOLD_BEGIN keeps the chain's own stopping rule
@@ -2904,10 +2933,17 @@ hipError_t launch_finish(const Batch &b, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t launch_stats_gather(const Batch &b, ChainStats *out, hipStream_t s)
+hipError_t launch_stats_gather(const Batch &b, ChainStats *out, unsigned *flag, unsigned seq, hipStream_t s)
 {
     if (b.n_chains <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_stats_gather, dim3((b.n_chains + 255) / 256), dim3(256), 0, s, b, out);
+    const int blocks = flag ? 1 : (b.n_chains + 63) / 64;
+    hipLaunchKernelGGL(k_stats_gather, dim3(blocks), dim3(b.n_chains > 16 ? 1024 : 256), 0, s, b, out, flag, seq);
+    return hipGetLastError();
+}
+
+hipError_t launch_box_read(const BoxRead &what, double *out, unsigned *flags, unsigned seq, int blocks, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_box_read, dim3(blocks), dim3(blocks > 1 ? 1024 : 256), 0, s, what, out, flags, seq);
     return hipGetLastError();
 }
 

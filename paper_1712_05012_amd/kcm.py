@@ -8,6 +8,7 @@ from __future__ import annotations
 
 import ctypes as C
 import os
+from array import array
 from dataclasses import dataclass, field
 
 import numpy as np
@@ -205,10 +206,11 @@ def kcm_build_chain(inputs: ChainInputs, params: kcm_params, dev_ptr: int, nbyte
 
 
 def _handles(chains):
-    arr = (C.c_void_p * len(chains))()
-    for i, c in enumerate(chains):
-        arr[i] = c.handle.value if isinstance(c, Chain) else c.value
-    return arr
+    try:
+        ptrs = array("Q", [c._ptr for c in chains])  # Chain objects, not freed
+    except (AttributeError, TypeError):
+        ptrs = array("Q", [c.handle.value if isinstance(c, Chain) else c.value for c in chains])
+    return (C.c_void_p * len(ptrs)).from_buffer(ptrs) if ptrs else (C.c_void_p * 0)()
 
 
 def kcm_step(chains, n_iter: int = 1, stream=None, report=True, check: bool = True):
@@ -296,8 +298,10 @@ def kcm_set_theta_batch(chains, thetas, stream=None):
     if len(thetas) != len(chains):
         raise ValueError("one theta array per chain")
     Js = [c.n_joints if isinstance(c, Chain) else kcm_chain_info(c)[1] for c in chains]
-    if isinstance(thetas, np.ndarray) and thetas.ndim == 2 and all(J == thetas.shape[1] for J in Js):
+    if isinstance(thetas, np.ndarray) and thetas.ndim == 2 and set(Js) == {thetas.shape[1]}:
         flat = np.ascontiguousarray(thetas, dtype=np.float64).reshape(-1)
+    elif Js and all(type(t) is np.ndarray for t in thetas) and [t.shape for t in thetas] == [(J,) for J in Js]:
+        flat = np.concatenate(thetas).astype(np.float64, copy=False)
     else:
         parts = []
         for J, t in zip(Js, thetas):
@@ -321,26 +325,30 @@ def kcm_mc_best_theta(handle, stream=None):
 
 
 def kcm_chain_info(handle):
-    v = [C.c_int32() for _ in range(4)]
-    _check(load_library().kcm_chain_info(handle, *[C.byref(x) for x in v]))
-    return tuple(int(x.value) for x in v)
+    v = (C.c_int32 * 4)()
+    at = C.addressof(v)
+    _check(load_library().kcm_chain_info(handle, at, at + 4, at + 8, at + 12))
+    return tuple(v)
 
 
 def kcm_get_state(handle, stream=None):
     n, J, _, _ = kcm_chain_info(handle)
-    theta, tau, dth = np.zeros(J), np.zeros(J), np.zeros(J)
-    xyz, F = np.zeros((n, 3)), np.zeros((n, 3))
+    theta, tau, dth = np.empty(J), np.empty(J), np.empty(J)
+    xyz, F = np.empty((n, 3)), np.empty((n, 3))
     _check(load_library().kcm_get_state(handle, _stream_handle(stream), _p(theta), _p(xyz), _p(F), _p(tau),
                                         _p(dth)))
     return {"theta": theta, "xyz": xyz, "force": F, "tau": tau, "dtheta": dth}
 
 
+def _theta(handle, n_joints, stream):
+    theta = np.empty(n_joints)
+    _check(load_library().kcm_get_state(handle, _stream_handle(stream), theta.ctypes.data, None, None, None, None))
+    return theta
+
+
 def kcm_get_theta(handle, stream=None):
     """The angles alone (one copy instead of the whole state)."""
-    _, J, _, _ = kcm_chain_info(handle)
-    theta = np.zeros(J)
-    _check(load_library().kcm_get_state(handle, _stream_handle(stream), _p(theta), None, None, None, None))
-    return theta
+    return _theta(handle, kcm_chain_info(handle)[1], stream)
 
 
 def kcm_get_forces(handle, stream=None):
@@ -430,6 +438,7 @@ class Chain:
         ptr = self.block.data_ptr()
         self.offset = (-ptr) % 256
         self.handle = kcm_build_chain(self.inputs, self.params, ptr + self.offset, self.nbytes, stream)
+        self._ptr = self.handle.value
         self.n_atoms, self.n_joints, self.n_samples, self.precision = kcm_chain_info(self.handle)
 
     def step(self, n_iter=1, stream=None):
@@ -439,7 +448,7 @@ class Chain:
         return kcm_get_state(self.handle, stream)
 
     def theta(self, stream=None):
-        return kcm_get_theta(self.handle, stream)
+        return _theta(self.handle, self.n_joints, stream)
 
     def forces(self, stream=None):
         return kcm_get_forces(self.handle, stream)
@@ -459,7 +468,7 @@ class Chain:
     def free(self):
         if self.handle is not None:
             kcm_chain_free(self.handle)
-            self.handle = None
+            self.handle = self._ptr = None
             self.block = None
 
     def __del__(self):
