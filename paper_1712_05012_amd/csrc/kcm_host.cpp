@@ -505,12 +505,19 @@ kcm_status ensure_table(kcm_chain *const *chains, int n_chains, hipStream_t stre
         const size_t scan_pos = jblk_pos + ints;
         // the map of atoms to chains: groups of 16 atoms, larger ones where that
         // would take more than 16,384 entries
-        long long atoms = 0;
-        for (int i = 0; i < n_chains; ++i) atoms += chains[i]->n;
+        long long atoms = 0, n_blk = 0, n_jblk = 0, n_scan = 0;
+        for (int i = 0; i < n_chains; ++i) {
+            atoms += chains[i]->n;
+            n_blk += (chains[i]->n + ATOM_BLOCK - 1) / ATOM_BLOCK;
+            n_jblk += chains[i]->njb;
+            n_scan += (chains[i]->h.cap_cells + SCAN_CHUNK - 1) / SCAN_CHUNK;
+        }
         int shift = 4;
         while ((atoms >> shift) > 16384) ++shift;
         const size_t map_pos = scan_pos + ints, n_map = (size_t)(atoms >> shift) + 1;
-        const size_t need = map_pos + sizeof(int32_t) * n_map;
+        // maps of the other launches' workgroups (unused by the two-launch form)
+        const size_t own_pos = map_pos + sizeof(int32_t) * n_map, n_own = (size_t)(n_blk + n_jblk + n_scan);
+        const size_t need = own_pos + sizeof(int32_t) * n_own;
         if (need > t->cap) {
             if (t->dev) {
                 HIP_TRY(hipStreamSynchronize(stream));
@@ -554,9 +561,19 @@ kcm_status ensure_table(kcm_chain *const *chains, int n_chains, hipStream_t stre
             while (c + 1 < (size_t)n_chains && off[c + 1] <= (long long)(k << shift)) ++c;
             map[k] = (int32_t)c;
         }
+        int32_t *own = reinterpret_cast<int32_t *>(host.data() + own_pos);
+        for (int i = 0; i < n_chains; ++i) {
+            std::fill(own + blk[i], own + blk[i + 1], i);
+            std::fill(own + n_blk + jblk[i], own + n_blk + jblk[i + 1], i);
+            std::fill(own + n_blk + n_jblk + sblk[i], own + n_blk + n_jblk + sblk[i + 1], i);
+        }
         HIP_TRY(hipMemcpyAsync(t->dev, host.data(), need, hipMemcpyHostToDevice, stream));
         HIP_TRY(hipStreamSynchronize(stream));
         unsigned char *d = static_cast<unsigned char *>(t->dev);
+        t->batch.only = chains[0]->d_desc;
+        t->batch.blk_chain = reinterpret_cast<const int32_t *>(d + own_pos);
+        t->batch.jblk_chain = t->batch.blk_chain + n_blk;
+        t->batch.scan_chain = t->batch.jblk_chain + n_jblk;
         t->batch.atom_chain = reinterpret_cast<const int32_t *>(d + map_pos);
         t->batch.atom_chain_shift = shift;
         t->batch.table = reinterpret_cast<ChainDev *const *>(d);
@@ -1188,6 +1205,7 @@ kcm_status noalloc_table(NoallocDevice &d, kcm_chain *const *chains, int n_chain
     if (e != hipSuccess) return fail(KCM_E_DEVICE, "kcm_step_noalloc: copy of the batch table failed");
     Batch &b = d.batch;
     b.table = reinterpret_cast<ChainDev *const *>(d.ptr);
+    b.only = chains[0]->d_desc;
     b.atom_off = reinterpret_cast<const int32_t *>(d.ptr + kNaTab);
     b.blk_off = reinterpret_cast<const int32_t *>(d.ptr + kNaTab + kNaOff);
     b.jblk_off = reinterpret_cast<const int32_t *>(d.ptr + kNaTab + 2 * kNaOff);

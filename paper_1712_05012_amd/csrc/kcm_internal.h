@@ -130,6 +130,8 @@ constexpr int GRID_OFFSET = STATS_OFFSET + (sizeof(ChainStats) + 255) / 256 * 25
 constexpr int ATOM_BLOCK = 256;
 struct Batch {
     ChainDev *const *table;
+    ChainDev *only;           // table[0] where there is one chain: no look-up
+    const int32_t *blk_chain, *jblk_chain, *scan_chain;  // chain of each workgroup of those launches, or null
     const int32_t *atom_off;
     const int32_t *blk_off;
     const int32_t *jblk_off;

@@ -334,9 +334,32 @@ __device__ __forceinline__ int find_block_owner(const int32_t *off, int n, int b
     return lo;
 }
 
+// The chain of workgroup b, by the map of the launch's workgroups to chains (or
+// a search where there is none), and its first workgroup.
+struct Owner {
+    ChainDev *cd;
+    int chain, first;
+};
+__device__ __forceinline__ Owner owner_of(const Batch &bt, const int32_t *map, const int32_t *off, int b)
+{
+    if (bt.n_chains == 1) return {bt.only, 0, 0};
+    const int c = map ? map[b] : find_block_owner(off, bt.n_chains, b);
+    return {bt.table[c], c, off[c]};
+}
+// A chain's flags and grid lie at fixed places behind its descriptor: their
+// loads need not wait for its pointers.
+__device__ __forceinline__ ChainStats *stats_of(const ChainDev *cd)
+{
+    return reinterpret_cast<ChainStats *>(reinterpret_cast<char *>(const_cast<ChainDev *>(cd)) + STATS_OFFSET);
+}
+__device__ __forceinline__ Grid *grid_of(const ChainDev *cd)
+{
+    return reinterpret_cast<Grid *>(reinterpret_cast<char *>(const_cast<ChainDev *>(cd)) + GRID_OFFSET);
+}
+
 // The kernels after the step run a chain iff the step kept it running and its
 // grid for this iteration could be sized.
-__device__ __forceinline__ bool running(const ChainStats *st) { return st->run && !st->grid_bad; }
+__device__ __forceinline__ bool running(const ChainStats *st) { return (st->run != 0) & (st->grid_bad == 0); }
 
 __device__ __forceinline__ int cell_of(const Grid &g, const double4 &r)
 {
@@ -588,13 +611,13 @@ __device__ __forceinline__ double stepped_angle(double th, double d)
 // KCM_01-KCM_06.
 __global__ __launch_bounds__(JOINT_BLOCK) void k_tau(Batch bt)
 {
-    const int c = find_block_owner(bt.jblk_off, bt.n_chains, blockIdx.x);
-    const ChainDev *cd = bt.table[c];
-    ChainStats *st = cd->stats;
+    const Owner own = owner_of(bt, bt.jblk_chain, bt.jblk_off, blockIdx.x);
+    const ChainDev *cd = own.cd;
+    ChainStats *st = stats_of(cd);
     if (!st->active || !st->pending_post) return;
     __shared__ double s_red[(JOINT_BLOCK / WAVE) * 6];
     __shared__ double s_S[8][6];
-    const int jb = blockIdx.x - bt.jblk_off[c];
+    const int jb = blockIdx.x - own.first;
     const int tid = threadIdx.x;
     if (jb >= cd->n_bb_blocks) {
         // a block of side-chain joints: k_wrench left each chi torque whole
@@ -677,14 +700,14 @@ __global__ __launch_bounds__(JOINT_BLOCK) void k_tau(Batch bt)
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(JOINT_BLOCK) void k_stepfk(Batch bt, int mode)
 {
-    const int c = find_block_owner(bt.jblk_off, bt.n_chains, blockIdx.x);
-    const ChainDev *cd = bt.table[c];
-    ChainStats *st = cd->stats;
+    const Owner own = owner_of(bt, bt.jblk_chain, bt.jblk_off, blockIdx.x);
+    const ChainDev *cd = own.cd;
+    ChainStats *st = stats_of(cd);
     if (!st->active) return;
     if (mode == MODE_BOOT && !st->need_grid) return;
     __shared__ double s_red[JOINT_BLOCK / WAVE];
     __shared__ double s_x[JOINT_BLOCK / WAVE][12];
-    const int jb = blockIdx.x - bt.jblk_off[c];
+    const int jb = blockIdx.x - own.first;
     const int tid = threadIdx.x, lane = tid & (WAVE - 1), w = tid / WAVE;
     const int J = cd->n_joints;
     // backbone blocks first; the blocks after them hold the side-chain joints,
@@ -792,10 +815,10 @@ __device__ __forceinline__ double4 placed_atom(const ChainDev *cd, int a, double
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(ATOM_BLOCK) void k_place(Batch bt, int mode)
 {
-    const int c = find_block_owner(bt.blk_off, bt.n_chains, blockIdx.x);
-    ChainDev *cd = bt.table[c];
-    ChainStats *st = cd->stats;
-    const int lb = blockIdx.x - bt.blk_off[c];
+    const Owner own = owner_of(bt, bt.blk_chain, bt.blk_off, blockIdx.x);
+    ChainDev *cd = own.cd;
+    ChainStats *st = stats_of(cd);
+    const int lb = blockIdx.x - own.first;
     // the step and torque kernels of this iteration have consumed the pending forces
     if (mode == MODE_ITER && lb == 0 && threadIdx.x == 0) st->pending_post = 0;
     if (mode == MODE_BOOT ? !(st->active && st->need_grid) : !running(st)) return;
@@ -913,7 +936,7 @@ __device__ __forceinline__ Grid wave_grid(const ChainDev *cd, bool *ok)
 __device__ __forceinline__ void store_grid(ChainDev *cd, ChainStats *st, const Grid &g, bool ok)
 {
     if (ok) {
-        *cd->grid = g;
+        *grid_of(cd) = g;
     } else {
         st->status = -4;
         st->grid_bad = 1;
@@ -922,8 +945,8 @@ __device__ __forceinline__ void store_grid(ChainDev *cd, ChainStats *st, const G
 
 __global__ __launch_bounds__(WAVE) void k_grid(Batch bt)
 {
-    ChainDev *cd = bt.table[blockIdx.x];
-    ChainStats *st = cd->stats;
+    ChainDev *cd = bt.n_chains == 1 ? bt.only : bt.table[blockIdx.x];
+    ChainStats *st = stats_of(cd);
     if (!running(st)) return;
     bool ok;
     const Grid g = wave_grid(cd, &ok);
@@ -933,15 +956,15 @@ __global__ __launch_bounds__(WAVE) void k_grid(Batch bt)
 template <bool OWN_GRID>
 __global__ __launch_bounds__(ATOM_BLOCK) void k_cellkey(Batch bt)
 {
-    const int c = find_block_owner(bt.blk_off, bt.n_chains, blockIdx.x);
-    ChainDev *cd = bt.table[c];
-    ChainStats *st = cd->stats;
+    const Owner own = owner_of(bt, bt.blk_chain, bt.blk_off, blockIdx.x);
+    ChainDev *cd = own.cd;
+    ChainStats *st = stats_of(cd);
     // with OWN_GRID, grid_bad is set by this kernel: a workgroup that sees it
     // set by the first one would have found the same failure itself
     if (!running(st)) return;
     __shared__ int s_ok;
     __shared__ Grid s_g;
-    const int lb = blockIdx.x - bt.blk_off[c];
+    const int lb = blockIdx.x - own.first;
     if (OWN_GRID) {
         if (threadIdx.x < WAVE) {
             bool ok;
@@ -955,7 +978,7 @@ __global__ __launch_bounds__(ATOM_BLOCK) void k_cellkey(Batch bt)
         __syncthreads();
         if (!s_ok) return;
     } else if (threadIdx.x == 0) {
-        s_g = *cd->grid;
+        s_g = *grid_of(cd);
     }
     // Atoms of the workgroup that share a cell take one count atomic between
     // them: an LDS table (open addressing on the key, twice as many slots as
@@ -996,12 +1019,12 @@ __global__ __launch_bounds__(ATOM_BLOCK) void k_cellkey(Batch bt)
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(CHAIN_THREADS) void k_gridboot(Batch bt)
 {
-    ChainDev *cd = bt.table[blockIdx.x];
-    ChainStats *st = cd->stats;
+    ChainDev *cd = bt.n_chains == 1 ? bt.only : bt.table[blockIdx.x];
+    ChainStats *st = stats_of(cd);
     if (!st->active || !st->need_grid) return;
     __shared__ double s_red[CHAIN_THREADS / WAVE * 6];
     __shared__ int s_ok;
-    const bool ok = grid_from_parts(cd, cd->grid, s_red, &s_ok);
+    const bool ok = grid_from_parts(cd, grid_of(cd), s_red, &s_ok);
     if (threadIdx.x == 0) {
         st->need_grid = 0;
         if (!ok) {
@@ -1018,7 +1041,7 @@ __global__ void k_finish(Batch bt)
 {
     const int c = blockIdx.x * blockDim.x + threadIdx.x;
     if (c >= bt.n_chains) return;
-    ChainStats *st = bt.table[c]->stats;
+    ChainStats *st = stats_of(bt.table[c]);
     st->pending_post = 0;
     st->active = running(st);
 }
@@ -1039,7 +1062,7 @@ __global__ __launch_bounds__(1024) void k_stats_gather(Batch bt, ChainStats *__r
     constexpr int W = sizeof(ChainStats) / sizeof(double);
     static_assert(W * sizeof(double) == sizeof(ChainStats), "records are whole doubles");
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < (int64_t)W * bt.n_chains; i += (int64_t)gridDim.x * blockDim.x)
-        reinterpret_cast<double *>(out)[i] = reinterpret_cast<const double *>(bt.table[i / W]->stats)[i % W];
+        reinterpret_cast<double *>(out)[i] = reinterpret_cast<const double *>(stats_of(bt.table[i / W]))[i % W];
     if (flag) signal_host(flag, seq);
 }
 
@@ -1070,7 +1093,7 @@ __global__ void k_fold_control(Batch bt, int mode, double tol, int64_t max_iter)
 {
     const int c = blockIdx.x * blockDim.x + threadIdx.x;
     if (c >= bt.n_chains) return;
-    ChainStats *st = bt.table[c]->stats;
+    ChainStats *st = stats_of(bt.table[c]);
     if (mode == FOLD_BEGIN) {
         const int go = st->status == 0 && max_iter > 0 ? 1 : 0;
         st->saved_tol = st->tol;
@@ -1124,11 +1147,11 @@ __device__ __forceinline__ double wrap_angle(double t)
 __global__ __launch_bounds__(JOINT_BLOCK) void k_mc_propose(Batch bt, int mode, const double *__restrict__ delta,
                                                              const int64_t *__restrict__ delta_off, int trial)
 {
-    const int c = find_block_owner(bt.jblk_off, bt.n_chains, blockIdx.x);
-    ChainDev *cd = bt.table[c];
-    ChainStats *st = cd->stats;
+    const Owner own = owner_of(bt, bt.jblk_chain, bt.jblk_off, blockIdx.x);
+    ChainDev *cd = own.cd;
+    ChainStats *st = stats_of(cd);
     if (st->status != 0) return;
-    const int jb = blockIdx.x - bt.jblk_off[c];
+    const int jb = blockIdx.x - own.first;
     if (jb == 0 && threadIdx.x == 0) {
         st->need_grid = 1;
         st->pending_post = 0;
@@ -1143,7 +1166,7 @@ __global__ __launch_bounds__(JOINT_BLOCK) void k_mc_propose(Batch bt, int mode, 
     if (mode != MC_PROPOSE || !joint_of_block(cd, jb, threadIdx.x, &j)) return;
     const int Jt = cd->n_joints + cd->n_chi;
     const double a = cd->mc_theta[j];
-    cd->theta[j] = cd->mask[j] ? wrap_angle(a + delta[delta_off[c] + (int64_t)trial * Jt + j]) : a;
+    cd->theta[j] = cd->mask[j] ? wrap_angle(a + delta[delta_off[own.chain] + (int64_t)trial * Jt + j]) : a;
 }
 
 // One thread per chain, after the torque kernel has reduced the energies of
@@ -1155,7 +1178,7 @@ __global__ void k_mc_decide(Batch bt, int mode, const double *__restrict__ u, in
     const int c = blockIdx.x * blockDim.x + threadIdx.x;
     if (c >= bt.n_chains) return;
     const ChainDev *cd = bt.table[c];
-    ChainStats *st = cd->stats;
+    ChainStats *st = stats_of(cd);
     // the energy of the chain's terms (bits 1 Coulomb, 2 Lennard-Jones, 4 solvation)
     double e = 0.0;
     if (cd->terms & 1) e += st->e_elec;
@@ -1190,11 +1213,11 @@ __global__ void k_mc_decide(Batch bt, int mode, const double *__restrict__ u, in
 // decided; a rejected trial returns the chain to the accepted angles.
 __global__ __launch_bounds__(JOINT_BLOCK) void k_mc_apply(Batch bt)
 {
-    const int c = find_block_owner(bt.jblk_off, bt.n_chains, blockIdx.x);
-    ChainDev *cd = bt.table[c];
-    const ChainStats *st = cd->stats;
+    const Owner own = owner_of(bt, bt.jblk_chain, bt.jblk_off, blockIdx.x);
+    ChainDev *cd = own.cd;
+    const ChainStats *st = stats_of(cd);
     int j;
-    if (!joint_of_block(cd, blockIdx.x - bt.jblk_off[c], threadIdx.x, &j)) return;
+    if (!joint_of_block(cd, blockIdx.x - own.first, threadIdx.x, &j)) return;
     const int Jt = cd->n_joints + cd->n_chi;
     const double p = cd->theta[j];
     if (st->mc_best) cd->mc_theta[Jt + j] = p;
@@ -1208,11 +1231,11 @@ __global__ __launch_bounds__(JOINT_BLOCK) void k_mc_apply(Batch bt)
 __global__ __launch_bounds__(JOINT_BLOCK) void k_set_theta(Batch bt, const double *__restrict__ theta,
                                                             const int64_t *__restrict__ theta_off)
 {
-    const int c = find_block_owner(bt.jblk_off, bt.n_chains, blockIdx.x);
-    ChainDev *cd = bt.table[c];
-    const int jb = blockIdx.x - bt.jblk_off[c];
+    const Owner own = owner_of(bt, bt.jblk_chain, bt.jblk_off, blockIdx.x);
+    ChainDev *cd = own.cd;
+    const int jb = blockIdx.x - own.first;
     if (jb == 0 && threadIdx.x == 0) {
-        ChainStats *st = cd->stats;
+        ChainStats *st = stats_of(cd);
         st->converged = 0;
         st->status = 0;
         st->nbr_overflow = 0;
@@ -1225,7 +1248,7 @@ __global__ __launch_bounds__(JOINT_BLOCK) void k_set_theta(Batch bt, const doubl
     }
     int j;
     if (!joint_of_block(cd, jb, threadIdx.x, &j)) return;
-    cd->theta[j] = wrap_angle(theta[theta_off[c] + j]);
+    cd->theta[j] = wrap_angle(theta[theta_off[own.chain] + j]);
 }
 
 // ---------------------------------------------------------------------------
@@ -1308,11 +1331,11 @@ __device__ __forceinline__ int place_sorted(const ChainDev *cd, const int *ids, 
 __global__ __launch_bounds__(CHAIN_THREADS) void k_cellscan(Batch bt)
 {
     static_assert(SCAN_CHUNK == 4 * CHAIN_THREADS, "four cells per thread");
-    const int c = find_block_owner(bt.scan_off, bt.n_chains, blockIdx.x);
-    const ChainDev *cd = bt.table[c];
-    if (!running(cd->stats)) return;
-    const int b = blockIdx.x - bt.scan_off[c];
-    const int nc = cd->grid->n_cells, c0 = b * SCAN_CHUNK;
+    const Owner own = owner_of(bt, bt.scan_chain, bt.scan_off, blockIdx.x);
+    const ChainDev *cd = own.cd;
+    if (!running(stats_of(cd))) return;
+    const int b = blockIdx.x - own.first;
+    const int nc = grid_of(cd)->n_cells, c0 = b * SCAN_CHUNK;
     if (c0 >= nc) return;
     __shared__ int s_int[CHAIN_THREADS / WAVE];
     const int m = min(SCAN_CHUNK, nc - c0), i0 = 4 * (int)threadIdx.x;
@@ -1343,11 +1366,11 @@ __global__ __launch_bounds__(ATOM_BLOCK) void k_scatter(Batch bt)
 {
     extern __shared__ int s_off[];
     __shared__ int s_int[ATOM_BLOCK / WAVE];
-    const int c = find_block_owner(bt.blk_off, bt.n_chains, blockIdx.x);
-    const ChainDev *cd = bt.table[c];
-    if (!running(cd->stats)) return;
-    chunk_offsets(cd, cd->grid->n_cells, s_off, s_int);
-    const int a = (blockIdx.x - bt.blk_off[c]) * ATOM_BLOCK + threadIdx.x;
+    const Owner own = owner_of(bt, bt.blk_chain, bt.blk_off, blockIdx.x);
+    const ChainDev *cd = own.cd;
+    if (!running(stats_of(cd))) return;
+    chunk_offsets(cd, grid_of(cd)->n_cells, s_off, s_int);
+    const int a = (blockIdx.x - own.first) * ATOM_BLOCK + threadIdx.x;
     if (a >= cd->n_atoms) return;
     const int key = cd->cell_key[a];
     const int start = cd->cell_local[key] + s_off[key / SCAN_CHUNK];
@@ -1358,13 +1381,13 @@ __global__ __launch_bounds__(ATOM_BLOCK) void k_rank(Batch bt)
 {
     extern __shared__ int s_off[];
     __shared__ int s_int[ATOM_BLOCK / WAVE];
-    const int c = find_block_owner(bt.blk_off, bt.n_chains, blockIdx.x);
-    const ChainDev *cd = bt.table[c];
-    if (!running(cd->stats)) return;
-    const int nc = cd->grid->n_cells, nb = (nc + SCAN_CHUNK - 1) / SCAN_CHUNK;
+    const Owner own = owner_of(bt, bt.blk_chain, bt.blk_off, blockIdx.x);
+    const ChainDev *cd = own.cd;
+    if (!running(stats_of(cd))) return;
+    const int nc = grid_of(cd)->n_cells, nb = (nc + SCAN_CHUNK - 1) / SCAN_CHUNK;
     chunk_offsets(cd, nc, s_off, s_int);
     // the final cell starts (nc + 1 of them), a slice per workgroup of the chain
-    const int lb = blockIdx.x - bt.blk_off[c], nblk = bt.blk_off[c + 1] - bt.blk_off[c];
+    const int lb = blockIdx.x - own.first, nblk = (cd->n_atoms + ATOM_BLOCK - 1) / ATOM_BLOCK;
     const int per = (nc + 1 + nblk - 1) / nblk, i1 = min(nc + 1, (lb + 1) * per);
     {
         // four cells per thread per step, the loads issued before the stores
@@ -1426,8 +1449,8 @@ __global__ __launch_bounds__(NT) void k_chain(Batch bt, int mode)
     __shared__ int s_flag;
     __shared__ Grid s_g;
 
-    ChainDev *cd = bt.table[blockIdx.x];
-    ChainStats *st = cd->stats;
+    ChainDev *cd = bt.n_chains == 1 ? bt.only : bt.table[blockIdx.x];
+    ChainStats *st = stats_of(cd);
     const int tid = threadIdx.x, lane = tid & (WAVE - 1), w = tid / WAVE;
     const int grp = tid / ATOM_BLOCK, gt = tid & (ATOM_BLOCK - 1), w0 = w & ~(WPB - 1);  // block in the pass, its first wave
     const bool lead = tid == 0;
@@ -1700,7 +1723,7 @@ __global__ __launch_bounds__(NT) void k_chain(Batch bt, int mode)
         s_flag = ok;
         if (ok) {
             s_g = g;
-            *cd->grid = g;
+            *grid_of(cd) = g;
         } else {
             // a conformation that never had a grid stops the chain before its
             // first iteration
@@ -2279,17 +2302,19 @@ __global__ __launch_bounds__(WAVE, sizeof(Real) == 4 ? 6 : 4) void k_force(Batch
     // the atom's chain: from the map of the batch, the chain of the first atom
     // of each group and a step per chain border in it (two dependent loads
     // where a binary search over 256 chains takes nine)
-    int c = 0;
+    CDev cd = glob((const ChainDev *)bt.only);
+    int si = atom;
     if (bt.n_chains > 1) {
+        int c = 0;
         if (bt.atom_chain) {
             c = bt.atom_chain[atom >> bt.atom_chain_shift];
             while (bt.atom_off[c + 1] <= atom) ++c;
         } else {
             c = find_block_owner(bt.atom_off, bt.n_chains, atom);
         }
+        cd = glob(glob(bt.table)[c]);
+        si = atom - bt.atom_off[c];
     }
-    const CDev cd = glob(glob(bt.table)[c]);
-    const int si = atom - bt.atom_off[c];
     const int lane = threadIdx.x;
 
     // flags and grid lie at fixed places behind the descriptor, and their loads
@@ -2835,10 +2860,10 @@ __global__ __launch_bounds__(WAVE, sizeof(Real) == 4 ? 6 : 4) void k_force(Batch
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(ATOM_BLOCK) void k_wrench(Batch bt)
 {
-    const int c = find_block_owner(bt.blk_off, bt.n_chains, blockIdx.x);
-    ChainDev *cd = bt.table[c];
-    ChainStats *st = cd->stats;
-    const int lb = blockIdx.x - bt.blk_off[c];
+    const Owner own = owner_of(bt, bt.blk_chain, bt.blk_off, blockIdx.x);
+    ChainDev *cd = own.cd;
+    ChainStats *st = stats_of(cd);
+    const int lb = blockIdx.x - own.first;
     if (lb == 0 && threadIdx.x == 0) {
         // end of the iteration: the chain stays active iff it ran, and its
         // forces await the post phase
