@@ -46,6 +46,19 @@ constexpr double PI_D = 3.14159265358979323846;
 // FP32 error of the tested quantity stays below ~5e-6 A for offsets < 16 A.
 constexpr float MIXED_BAND = 4.0e-5f;
 
+// Loads, stores and atomics through a pointer of unknown address space are
+// flat instructions, which count against the LDS counter as well as the
+// vector-memory one: every LDS wait then also waits for them.  The device
+// arrays of the force kernel are all in global memory, and it reaches them
+// through these global-address-space views (plain pointers in the host
+// pass, which only checks the device code).
+#if defined(__HIP_DEVICE_COMPILE__)
+template <typename T> using gptr = __attribute__((address_space(1))) T *;
+#else
+template <typename T> using gptr = T *;
+#endif
+template <typename T> __device__ __forceinline__ gptr<T> glob(T *p) { return (gptr<T>)p; }
+
 // ---------------------------------------------------------------------------
 // moves between the lanes of a wave
 // ---------------------------------------------------------------------------
@@ -61,7 +74,7 @@ template <int CTRL> __device__ __forceinline__ double dpp(double x)
     return __hiloint2double(dpp<CTRL>(__double2hiint(x)), dpp<CTRL>(__double2loint(x)));
 }
 constexpr int DPP_WAVE_SHL1 = 0x130, DPP_WAVE_SHR1 = 0x138, DPP_ROW_ROR = 0x120, DPP_ROW_SHL = 0x100, DPP_ROW_SHR = 0x110;
-constexpr int DPP_QUAD_XOR1 = 0xb1, DPP_QUAD_XOR2 = 0x4e, DPP_HALF_MIRROR = 0x141, DPP_MIRROR = 0x140;
+constexpr int DPP_QUAD_XOR1 = 0xb1, DPP_QUAD_XOR2 = 0x4e;
 // the lower half of the wave in both halves (UPPER: the upper one), and the
 // even rows of 16 in both rows of each half (UPPER: the odd ones)
 template <bool UPPER> __device__ __forceinline__ int both_halves(int x)
@@ -186,6 +199,77 @@ __device__ __forceinline__ int wave_sum4_i(int a, int b, int c, int d)
     return p + dpp<DPP_ROW_ROR + 1>(p);
 }
 
+// The smaller and the larger of two numbers.  The library's calls first quiet
+// signalling NaNs, one more instruction per argument that went between lanes.
+#if defined(__HIP_DEVICE_COMPILE__)
+__device__ __forceinline__ double min_num(double a, double b)
+{
+    double r;
+    asm("v_min_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+__device__ __forceinline__ double max_num(double a, double b)
+{
+    double r;
+    asm("v_max_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+#else
+__device__ double min_num(double a, double b);
+__device__ double max_num(double a, double b);
+#endif
+__device__ __forceinline__ double lane_value(double x, int l)
+{
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), l), __builtin_amdgcn_readlane(__double2loint(x), l));
+}
+// The box [lo, hi] over the wave, the same in every lane: minima of the six
+// numbers lo and -hi, reduced together as in wave_sum5 (60 instructions in
+// place of 280 for six butterflies).
+__device__ __forceinline__ void wave_box(double (&lo)[3], double (&hi)[3])
+{
+    auto halves = [](double a, double b) {
+        int ah = __double2hiint(a), al = __double2loint(a), bh = __double2hiint(b), bl = __double2loint(b);
+        swap_halves(ah, bh);
+        swap_halves(al, bl);
+        return min_num(__hiloint2double(ah, al), __hiloint2double(bh, bl));
+    };
+    auto rows = [](double a, double b) {
+        int ah = __double2hiint(a), al = __double2loint(a), bh = __double2hiint(b), bl = __double2loint(b);
+        swap_rows(ah, bh);
+        swap_rows(al, bl);
+        return min_num(__hiloint2double(ah, al), __hiloint2double(bh, bl));
+    };
+    const double p = rows(halves(lo[0], lo[1]), halves(lo[2], -hi[0]));
+    double v = halves(-hi[1], -hi[2]);
+    v = min_num(both_rows<false>(v), both_rows<true>(v));
+    const bool up = threadIdx.x & 8;
+    double z = min_num(up ? v : p, dpp<DPP_ROW_ROR + 8>(up ? p : v));
+    z = min_num(z, __hiloint2double(from_xor4(__double2hiint(z)), from_xor4(__double2loint(z))));
+    z = min_num(z, dpp<DPP_QUAD_XOR2>(z));
+    z = min_num(z, dpp<DPP_QUAD_XOR1>(z));
+    lo[0] = lane_value(z, 0);
+    lo[1] = lane_value(z, 32);
+    lo[2] = lane_value(z, 16);
+    hi[0] = -lane_value(z, 48);
+    hi[1] = -lane_value(z, 8);
+    hi[2] = -lane_value(z, 40);
+}
+
+// Inside a condition on the lane: the compiler then runs the branch under the
+// execution mask, where it would compute for all lanes and select each word of
+// each result (two instructions per double).
+__device__ __forceinline__ void masked_branch() { asm volatile(""); }
+
+// A barrier for what the workgroup shares in LDS.  __syncthreads() also waits
+// for every load and store under way to global memory, a thousand cycles where
+// a store has just gone out.
+__device__ __forceinline__ void lds_barrier()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
 // ---------------------------------------------------------------------------
 // rigid transforms (rotation R row-major, translation t): x -> R x + t
 // ---------------------------------------------------------------------------
@@ -260,11 +344,11 @@ __device__ __forceinline__ double wave_sum(double v)
 }
 __device__ __forceinline__ double wave_max(double v)
 {
-    return wave_all(v, [](double a, double b) { return fmax(a, b); });
+    return wave_all(v, [](double a, double b) { return max_num(a, b); });
 }
 __device__ __forceinline__ double wave_min(double v)
 {
-    return wave_all(v, [](double a, double b) { return fmin(a, b); });
+    return wave_all(v, [](double a, double b) { return min_num(a, b); });
 }
 __device__ __forceinline__ int wave_sum_i(int v)
 {
@@ -391,8 +475,8 @@ __device__ __forceinline__ Xf xf_shfl_idx(const Xf &x, int src)
 }
 
 // The current axis (u_j, p_j) of joint j from the transform G of link j + 1.
-__device__ __forceinline__ void fk_emit(const Xf &G, int j, const double4 &u0, const double4 &p0,
-                                        double4 *__restrict__ jcur)
+template <typename P>
+__device__ __forceinline__ void fk_emit(const Xf &G, int j, const double4 &u0, const double4 &p0, P jcur)
 {
     double4 u, p;
     u.x = G.r[0] * u0.x + G.r[1] * u0.y + G.r[2] * u0.z;
@@ -428,34 +512,52 @@ __device__ __forceinline__ Xf joint_xf_of(const double4 &u, const double4 &p, do
 // grows until the grid fits the chain's cell capacity.  Block-wide (any block
 // size); returns false (and a one-cell grid) when the box is not finite or
 // cannot be covered.  s_red: [nw * 6].
-// The grid for the bounding box [lo, hi] of the placed atoms, plus a margin
-// (one thread); *ok stays true iff it could be sized within the capacity.
-__device__ Grid size_grid(const ChainDev *cd, const double lo[3], const double hi[3], bool *ok)
+// The grid for the bounding box [lo, hi] of the placed atoms, plus a margin, by
+// a whole wave: lane k < 3 brings axis k's bounds, the others axis 2's, and all
+// get the grid; ok stays true iff it could be sized within the capacity.
+struct GridRule {
+    double reach_len, cell, inv_cell;  // interaction reach, first cell edge
+    int cap_cells;
+};
+template <typename Chain>
+__device__ __forceinline__ GridRule grid_rule(const Chain *cd)
 {
-    double L3[3], H3[3];
-    for (int k = 0; k < 3; ++k) {
-        L3[k] = lo[k] - GRID_MARGIN;
-        H3[k] = hi[k] + GRID_MARGIN;
-        *ok = *ok && isfinite(L3[k]) && isfinite(H3[k]) && H3[k] >= L3[k] && (H3[k] - L3[k]) < 1e7;
-    }
     const double reach_len = fmax(cd->cutoff, 2.0 * cd->roff_max + cd->delta_r) + 1e-7;
-    double cell = fmax(cd->cell_min, reach_len / MAX_REACH);
-    long long dims[3] = {1, 1, 1};
-    for (int it = 0; *ok && it < 200; ++it) {
-        for (int k = 0; k < 3; ++k) dims[k] = (long long)floor((H3[k] - L3[k]) / cell) + 1;
-        if (dims[0] * dims[1] * dims[2] <= cd->cap_cells) break;
-        cell *= 1.2599210498948732;
-    }
-    *ok = *ok && dims[0] * dims[1] * dims[2] <= cd->cap_cells;
+    const double cell = fmax(cd->cell_min, reach_len / MAX_REACH);
+    return {reach_len, cell, 1.0 / cell, cd->cap_cells};
+}
+__device__ __forceinline__ Grid size_grid(const GridRule &rule, double lo, double hi, bool &ok)
+{
+    const double L = lo - GRID_MARGIN, H = hi + GRID_MARGIN, ext = H - L;
+    ok = !__any(!(ok && isfinite(L) && isfinite(H) && H >= L && ext < 1e7));
     Grid g;
-    for (int k = 0; k < 3; ++k) { g.origin[k] = *ok ? L3[k] : 0.0; g.dims[k] = *ok ? (int)dims[k] : 1; }
-    g.cell = cell;
-    g.inv_cell = 1.0 / cell;
-    g.reach = max(1, (int)ceil(reach_len / cell - 1e-9));
-    g.reach_len = reach_len;
-    g.n_cells = *ok ? (int)(dims[0] * dims[1] * dims[2]) : 1;
+    g.reach_len = rule.reach_len;
+    g.cell = rule.cell;
+    g.inv_cell = rule.inv_cell;
+    long long dims[3] = {1, 1, 1};
+    for (int it = 0; ok && it < 200; ++it) {
+        const long long d = (long long)floor(ext / g.cell) + 1;
+        const int d_lo = (int)d, d_hi = (int)(d >> 32);
+#pragma unroll
+        for (int k = 0; k < 3; ++k)
+            dims[k] = ((long long)__builtin_amdgcn_readlane(d_hi, k) << 32) | (unsigned)__builtin_amdgcn_readlane(d_lo, k);
+        if (dims[0] * dims[1] * dims[2] <= rule.cap_cells) break;
+        g.cell *= 1.2599210498948732;
+        g.inv_cell = 1.0 / g.cell;
+    }
+    ok = ok && dims[0] * dims[1] * dims[2] <= rule.cap_cells;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) { g.origin[k] = ok ? lane_value(L, k) : 0.0; g.dims[k] = ok ? (int)dims[k] : 1; }
+    g.reach = max(1, (int)ceil(g.reach_len / g.cell - 1e-9));
+    g.n_cells = ok ? (int)(dims[0] * dims[1] * dims[2]) : 1;
     g.pad = 0;
     return g;
+}
+// lane k < 3: v[k], the others: v[2]
+__device__ __forceinline__ double axis_of_lane(const double (&v)[3])
+{
+    const int lane = threadIdx.x & (WAVE - 1);
+    return lane == 0 ? v[0] : lane == 1 ? v[1] : v[2];
 }
 
 __device__ bool grid_from_parts(const ChainDev *cd, Grid *out, double *s_red, int *s_ok)
@@ -473,8 +575,7 @@ __device__ bool grid_from_parts(const ChainDev *cd, Grid *out, double *s_red, in
             lo[k] = fmin(lo[k], l);
             hi[k] = fmax(hi[k], h);
         }
-#pragma unroll
-    for (int k = 0; k < 3; ++k) { lo[k] = wave_min(lo[k]); hi[k] = wave_max(hi[k]); }
+    wave_box(lo, hi);
     const bool bad_w = __any(!fin);
     if (tid == 0) *s_ok = 1;
     __syncthreads();
@@ -487,14 +588,16 @@ __device__ bool grid_from_parts(const ChainDev *cd, Grid *out, double *s_red, in
         // wave 0 reduces the wave partials, lane i holding wave i's
 #pragma unroll
         for (int k = 0; k < 3; ++k) {
-            lo[k] = wave_min(lane < nw ? s_red[lane * 6 + k] : DBL_MAX);
-            hi[k] = wave_max(lane < nw ? s_red[lane * 6 + 3 + k] : -DBL_MAX);
+            lo[k] = lane < nw ? s_red[lane * 6 + k] : DBL_MAX;
+            hi[k] = lane < nw ? s_red[lane * 6 + 3 + k] : -DBL_MAX;
         }
-    }
-    if (tid == 0) {
+        wave_box(lo, hi);
         bool ok = *s_ok != 0;
-        *out = size_grid(cd, lo, hi, &ok);
-        *s_ok = ok ? 1 : 0;
+        const Grid g = size_grid(grid_rule(cd), axis_of_lane(lo), axis_of_lane(hi), ok);
+        if (lane == 0) {
+            *out = g;
+            *s_ok = ok ? 1 : 0;
+        }
     }
     __syncthreads();
     return *s_ok != 0;
@@ -508,64 +611,84 @@ __device__ __forceinline__ double axis_torque(const double4 &u, const double4 &p
     const double mz = S[5] - (p.x * S[1] - p.y * S[0]);
     return u.x * mx + u.y * my + u.z * mz;
 }
-__device__ __forceinline__ double joint_torque(const ChainDev *cd, int j, const double *S)
+template <typename Chain>
+__device__ __forceinline__ double joint_torque(const Chain *cd, int j, const double *S)
 {
     return axis_torque(cd->jcur[2 * j], cd->jcur[2 * j + 1], S);
 }
 
-// The sum over the wave as a tree of neighbours, ((v0 + v1) + (v2 + v3)) + ...
-__device__ __forceinline__ double wave_tree_sum(double v)
+// Four sums over the wave, each as a tree of neighbours, ((v0 + v1) + (v2 +
+// v3)) + ..., in lane 0.  The first two levels leave sum k in the lanes l with
+// l mod 4 = k: 40 instructions in place of 104 for four sums in all lanes.
+__device__ __forceinline__ void wave_tree_sum4(double *v)
 {
-    v += dpp<DPP_QUAD_XOR1>(v);
-    v += dpp<DPP_QUAD_XOR2>(v);
-    v += dpp<DPP_HALF_MIRROR>(v);
-    v += dpp<DPP_MIRROR>(v);
-    v = both_rows<false>(v) + both_rows<true>(v);
-    return both_halves<false>(v) + both_halves<true>(v);
+    static_assert(WPART == 10, "four sums behind the wrench");
+    const bool odd = threadIdx.x & 1, up = threadIdx.x & 2;
+    const double a = (odd ? v[1] : v[0]) + dpp<DPP_QUAD_XOR1>(odd ? v[0] : v[1]);
+    const double b = (odd ? v[3] : v[2]) + dpp<DPP_QUAD_XOR1>(odd ? v[2] : v[3]);
+    double z = (up ? b : a) + dpp<DPP_QUAD_XOR2>(up ? a : b);
+    z += __hiloint2double(from_xor4(__double2hiint(z)), from_xor4(__double2loint(z)));
+    z += dpp<DPP_ROW_ROR + 8>(z);
+    z = both_rows<false>(z) + both_rows<true>(z);
+    z = both_halves<false>(z) + both_halves<true>(z);
+    v[0] = z;
+    v[1] = dpp<DPP_WAVE_SHL1>(z);
+    v[2] = dpp<DPP_WAVE_SHL1>(v[1]);
+    v[3] = dpp<DPP_WAVE_SHL1>(v[2]);
 }
 
-// Wrench (F, r x F), energies and failure flag of atom a at r (zeros past the chain's end).
-__device__ __forceinline__ void atom_wrench(const ChainDev *cd, int a, double4 &r, double (&v)[WPART])
+// Wrench (F, r x F), energies and failure flag of atom a at r (zeros past the
+// chain's end), in two parts: the loads, and what is made of them.
+struct AtomForce {
+    double4 f, r, e;
+    long long c[3];
+};
+template <typename Chain> __device__ __forceinline__ AtomForce load_force(const Chain *cd, int a)
+{
+    return {cd->f_pair[a], cd->r[a], cd->e_atom[a], {cd->f_cav[3 * a], cd->f_cav[3 * a + 1], cd->f_cav[3 * a + 2]}};
+}
+__device__ __forceinline__ void wrench_of(const AtomForce &in, bool valid, double4 &r, double (&v)[WPART])
 {
 #pragma unroll
     for (int k = 0; k < WPART; ++k) v[k] = 0.0;
     r = make_double4(0, 0, 0, 0);
-    if (a < cd->n_atoms) {
+    if (valid) {
         const double inv_fix = 1.0 / FIX_SCALE;
-        const double4 fp = cd->f_pair[a];
-        const double Fx = fp.x + (double)cd->f_cav[3 * a] * inv_fix;
-        const double Fy = fp.y + (double)cd->f_cav[3 * a + 1] * inv_fix;
-        const double Fz = fp.z + (double)cd->f_cav[3 * a + 2] * inv_fix;
-        r = cd->r[a];
+        const double Fx = in.f.x + (double)in.c[0] * inv_fix;
+        const double Fy = in.f.y + (double)in.c[1] * inv_fix;
+        const double Fz = in.f.z + (double)in.c[2] * inv_fix;
+        r = in.r;
         v[0] = Fx; v[1] = Fy; v[2] = Fz;
         v[3] = r.y * Fz - r.z * Fy; v[4] = r.z * Fx - r.x * Fz; v[5] = r.x * Fy - r.y * Fx;
-        const double4 e = cd->e_atom[a];
-        v[6] = e.x; v[7] = e.y; v[8] = e.z;
+        v[6] = in.e.x; v[7] = in.e.y; v[8] = in.e.z;
         v[9] = (isfinite(Fx) && isfinite(Fy) && isfinite(Fz)) ? 0.0 : 1.0;
     }
 }
 
 // Over the wave: entries 0-5 (the wrench) become the inclusive suffix, this
-// atom and every later one; entries 6-9 (energies, flag) the sum, in every
-// lane, in the order in which lane 0 of such a suffix adds.
+// atom and every later one; entries 6-9 (energies, flag) in lane 0 the sum, in
+// the order in which lane 0 of such a suffix adds.
 __device__ __forceinline__ void wave_suffix(double (&S)[WPART])
 {
     const int lane = threadIdx.x & (WAVE - 1);
 #pragma unroll
     for (int d = 1; d < WAVE; d <<= 1) {
+        double y[6];
 #pragma unroll
-        for (int k = 0; k < 6; ++k) {
-            const double y = from_above(S[k], d);
-            if (lane + d < WAVE) S[k] += y;
+        for (int k = 0; k < 6; ++k) y[k] = from_above(S[k], d);
+        if (lane + d < WAVE) {
+            masked_branch();
+#pragma unroll
+            for (int k = 0; k < 6; ++k) S[k] += y[k];
         }
     }
-#pragma unroll
-    for (int k = 6; k < WPART; ++k) S[k] = wave_tree_sum(S[k]);
+    wave_tree_sum4(S + 6);
 }
 
 // Side-chain torque of the residue whose CB is atom a at r: the whole torque,
 // over HB1..HB3 (atoms a+1 .. a+3), about the CA->CB axis through CA.
-__device__ __forceinline__ double chi_torque(const ChainDev *cd, int a, const double4 &r)
+template <typename Chain>
+__device__ __forceinline__ double chi_torque(const Chain *cd, int a, const double4 &r)
 {
     const double inv_fix = 1.0 / FIX_SCALE;
     const double4 ca = cd->r[a - 2];
@@ -586,7 +709,8 @@ __device__ __forceinline__ double chi_torque(const ChainDev *cd, int a, const do
 }
 
 // The compliance step of eq KCM_07 for the largest torque tm: dtheta = scale tau.
-__device__ __forceinline__ double step_scale(const ChainDev *cd, double tm)
+template <typename Chain>
+__device__ __forceinline__ double step_scale(const Chain *cd, double tm)
 {
     const double kappa = cd->kappa, smax = cd->max_step;
     if (cd->step_rule == 1) return tm > 0.0 ? smax / tm : 0.0;
@@ -767,7 +891,10 @@ __global__ __launch_bounds__(JOINT_BLOCK) void k_stepfk(Batch bt, int mode)
 #pragma unroll
     for (int d = 1; d < WAVE; d <<= 1) {
         Xf y = xf_from_below(x, d);
-        if (lane >= d) x = xf_mul(y, x);
+        if (lane >= d) {
+                    masked_branch();
+                    x = xf_mul(y, x);
+                }
     }
     if (lane == WAVE - 1) xf_store(s_x[w], x);
     __syncthreads();
@@ -781,7 +908,8 @@ __global__ __launch_bounds__(JOINT_BLOCK) void k_stepfk(Batch bt, int mode)
 }
 
 // Position of atom a with zero position q under its link transform L.
-__device__ __forceinline__ double4 placed_atom(const ChainDev *cd, int a, double4 q, const double *L)
+template <typename Chain>
+__device__ __forceinline__ double4 placed_atom(const Chain *cd, int a, double4 q, const double *L)
 {
     const int res = a / APR, slot = a - res * APR;
     if (cd->n_chi && slot >= 5 && slot <= 7) {
@@ -839,7 +967,10 @@ __global__ __launch_bounds__(ATOM_BLOCK) void k_place(Batch bt, int mode)
 #pragma unroll
             for (int d = 1; d < WAVE; d <<= 1) {
                 Xf y = xf_from_below(x, d);
-                if (lane >= d) x = xf_mul(y, x);
+                if (lane >= d) {
+                    masked_branch();
+                    x = xf_mul(y, x);
+                }
             }
             if (base > 0) x = xf_mul(acc, x);
             if (base + lane == jb_lo - 1) xf_store(s_c[0], x);
@@ -911,7 +1042,7 @@ __global__ __launch_bounds__(ATOM_BLOCK) void k_place(Batch bt, int mode)
 // read it; for small ones, where a launch costs more than the redundant work,
 // wave 0 of every key workgroup sizes it and the first one stores it.
 // ---------------------------------------------------------------------------
-// the grid from the chain's bounding-box partials (one wave; lane 0 gets it)
+// the grid from the chain's bounding-box partials (one wave)
 __device__ __forceinline__ Grid wave_grid(const ChainDev *cd, bool *ok)
 {
     const int lane = (int)threadIdx.x & (WAVE - 1), nblk = (cd->n_atoms + ATOM_BLOCK - 1) / ATOM_BLOCK;
@@ -925,12 +1056,9 @@ __device__ __forceinline__ Grid wave_grid(const ChainDev *cd, bool *ok)
             lo[k] = fmin(lo[k], l);
             hi[k] = fmax(hi[k], h);
         }
-#pragma unroll
-    for (int k = 0; k < 3; ++k) { lo[k] = wave_min(lo[k]); hi[k] = wave_max(hi[k]); }
-    *ok = !__any(!fin);
-    Grid g{};
-    if (lane == 0) g = size_grid(cd, lo, hi, ok);
-    return g;
+    wave_box(lo, hi);
+    *ok = fin;
+    return size_grid(grid_rule(cd), axis_of_lane(lo), axis_of_lane(hi), *ok);
 }
 
 __device__ __forceinline__ void store_grid(ChainDev *cd, ChainStats *st, const Grid &g, bool ok)
@@ -1284,7 +1412,8 @@ __device__ void chunk_offsets(const ChainDev *cd, int nc, int *s_off, int *s_int
 // sqrt(eps), R_off) in FP64, or, for a chain of the mixed form, the first three
 // as the FP32 values its pair terms use in the first 16 bytes.  Either way
 // R_off is the last double.
-__device__ __forceinline__ double4 sorted_param(const ChainDev *cd, double4 p)
+template <typename Chain>
+__device__ __forceinline__ double4 sorted_param(const Chain *cd, double4 p)
 {
     if (cd->precision == 1) {
         p.x = __hiloint2double(__float_as_int((float)p.y), __float_as_int((float)p.x));
@@ -1414,6 +1543,30 @@ __global__ __launch_bounds__(ATOM_BLOCK) void k_rank(Batch bt)
     if (place_sorted(cd, cd->s_tmp, a, b, e) == 0) cd->cell_count[key] = 0;
 }
 
+// What k_chain uses of a chain's descriptor, read once at its start while
+// nothing is stored yet: into scalar registers, where a later look would be a
+// vector load (its stores might change the descriptor, for all the compiler
+// knows) with a few hundred cycles of latency each.
+struct ChainView {
+    int n_atoms, n_joints, n_chi, n_bb_blocks, cap_cells, precision, step_rule;
+    double cutoff, kappa, max_step, delta_r, cell_min, roff_max;
+    gptr<double> theta, dtheta, tau;
+    gptr<uint8_t> mask;
+    gptr<double4> joint0, jcur, r0, r, aparam, s_r, s_p, f_pair, e_atom;
+    gptr<int32_t> cell_start, s_idx;
+    gptr<long long> f_cav;
+    __device__ __forceinline__ explicit ChainView(const ChainDev *d)
+        : n_atoms(d->n_atoms), n_joints(d->n_joints), n_chi(d->n_chi), n_bb_blocks(d->n_bb_blocks),
+          cap_cells(d->cap_cells), precision(d->precision), step_rule(d->step_rule), cutoff(d->cutoff),
+          kappa(d->kappa), max_step(d->max_step), delta_r(d->delta_r), cell_min(d->cell_min), roff_max(d->roff_max),
+          theta(glob(d->theta)), dtheta(glob(d->dtheta)), tau(glob(d->tau)), mask(glob(d->mask)),
+          joint0(glob(d->joint0)), jcur(glob(d->jcur)), r0(glob(d->r0)), r(glob(d->r)), aparam(glob(d->aparam)),
+          s_r(glob(d->s_r)), s_p(glob(d->s_p)), f_pair(glob(d->f_pair)), e_atom(glob(d->e_atom)),
+          cell_start(glob(d->cell_start)), s_idx(glob(d->s_idx)), f_cav(glob(d->f_cav))
+    {
+    }
+};
+
 // ---------------------------------------------------------------------------
 // k_chain: everything of an iteration but the force kernel, one workgroup per
 // chain, for calls of short or many chains (set_form in kcm_host.cpp)
@@ -1430,27 +1583,31 @@ __global__ __launch_bounds__(ATOM_BLOCK) void k_rank(Batch bt)
 // ones and ends the call; MODE_TAU leaves torques and energies only.
 // The conditions that end the kernel early are the same for all threads, so
 // every barrier is reached by all of them.
-// What bounds it is latency: of about 34,500 cycles for a chain of 150 atoms
-// the wrenches with the wait for the last forces take 7,000, the transform
-// scan 5,500, the grid 2,600, the sorted arrays 2,800; with LDS permutes for
-// every lane move it took 39,200.  15.3 us in place of 47 us for the eight
-// kernels it replaces, 43 us with them in one graph.  Workgroups of 768
-// threads at most: 1,024 would leave 128 registers and spill 80.
+// What bounds it is latency: one wave per SIMD and a chain of dependent steps,
+// about 26,500 cycles for a chain of 150 atoms, of which the loads at the start
+// take 3,000, the wrenches 5,500, the transform scan 3,800, the sorted arrays
+// 2,600 and the grid 2,400.  11 us in place of 47 us for the eight kernels it
+// replaces (43 us with them in one graph).  What it took before, in that order:
+// 39,200 cycles with LDS permutes for every lane move; 36,200 where every
+// barrier waited for the stores before it, every look at the descriptor was a
+// load and one thread sized the grid (13.9 us).  768-thread form, 256 chains of
+// 500 to 6,000 atoms: 109 us, 123 before.  Workgroups of 768 threads at most:
+// 1,024 would leave 128 registers.
 template <int NT, bool ONE>
 __global__ __launch_bounds__(NT) void k_chain(Batch bt, int mode)
 {
     static_assert(JOINT_BLOCK == ATOM_BLOCK && NT % ATOM_BLOCK == 0, "blocks of one size");
     constexpr int NW = NT / WAVE, WPB = ATOM_BLOCK / WAVE;  // waves, waves per block
+    constexpr bool KEEP_AXIS = ONE && NT <= 512;            // registers left for ua_1, pa_1
     extern __shared__ __align__(16) unsigned char s_dyn[];
     __shared__ double s_red[NW][12];
     __shared__ double s_blk[CHAIN_JBLOCKS][12], s_carry[CHAIN_JBLOCKS][12];
     __shared__ double s_tm[NW];
     __shared__ int s_bad[NW], s_scan[NW];
-    __shared__ int s_flag;
-    __shared__ Grid s_g;
 
-    ChainDev *cd = bt.n_chains == 1 ? bt.only : bt.table[blockIdx.x];
-    ChainStats *st = stats_of(cd);
+    ChainDev *dev = bt.n_chains == 1 ? bt.only : bt.table[blockIdx.x];
+    ChainStats *st = stats_of(dev);
+    const ChainView view(dev), *cd = &view;
     const int tid = threadIdx.x, lane = tid & (WAVE - 1), w = tid / WAVE;
     const int grp = tid / ATOM_BLOCK, gt = tid & (ATOM_BLOCK - 1), w0 = w & ~(WPB - 1);  // block in the pass, its first wave
     const bool lead = tid == 0;
@@ -1463,30 +1620,47 @@ __global__ __launch_bounds__(NT) void k_chain(Batch bt, int mode)
     const int64_t it1 = st->iterations + 1, it_limit = st->iter_limit;
     const int overflow = st->nbr_overflow;
     int go = st->run;
+    asm volatile("" : : "v"(go), "v"(overflow), "v"(tol), "v"(it1), "v"(it_limit), "v"((int)grid_bad), "v"((int)fresh));
     // a thread with one atom and one joint takes what it needs of them now, all
     // loads in flight together, and keeps it
-    double4 r0_1 = {}, ap_1 = {}, u0_1 = {}, p0_1 = {}, uc_1 = {}, pc_1 = {};
+    // (threads beyond the last atom or joint the last one's, and leave it)
+    double4 r0_1, ap_1, u0_1, p0_1, uc_1, pc_1, ua_1, pa_1;  // ua, pa: axis of the joint whose first atom this is
     double th_1 = 0.0;
-    bool free_1 = false;
+    unsigned free_1 = 0;
+    AtomForce in_1;  // stale, and not used, unless pending
     if (ONE) {
-        if (tid < n) {
-            r0_1 = cd->r0[tid];
-            ap_1 = cd->aparam[tid];
+        const int a = min(tid, n - 1), j = min(tid, J - 1), res = a / APR, ja = 2 * res + (a - res * APR == 8 ? 1 : 0);
+        in_1 = load_force(cd, a);
+        if (KEEP_AXIS) {
+            ua_1 = cd->jcur[2 * ja];
+            pa_1 = cd->jcur[2 * ja + 1];
         }
-        if (tid < J) {
-            u0_1 = cd->joint0[2 * tid];
-            p0_1 = cd->joint0[2 * tid + 1];
-            uc_1 = cd->jcur[2 * tid];
-            pc_1 = cd->jcur[2 * tid + 1];
-        }
-        if (tid < J + n_chi) {
-            th_1 = cd->theta[tid];
-            free_1 = cd->mask[tid];
-        }
+        uc_1 = cd->jcur[2 * j];
+        pc_1 = cd->jcur[2 * j + 1];
+        u0_1 = cd->joint0[2 * j];
+        p0_1 = cd->joint0[2 * j + 1];
+        th_1 = cd->theta[min(tid, J + n_chi - 1)];
+        free_1 = cd->mask[min(tid, J + n_chi - 1)];
+        r0_1 = cd->r0[a];
+        ap_1 = cd->aparam[a];
     }
-    __syncthreads();
+    const GridRule rule = grid_rule(cd);
+    unsigned *s_cell = reinterpret_cast<unsigned *>(s_dyn + (ONE ? sizeof(double) * 12 * (J + 1) : 0));
+    if (ONE) {
+        for (int i = tid; i < rule.cap_cells / 8; i += NT) reinterpret_cast<uint4 *>(s_cell)[i] = make_uint4(0, 0, 0, 0);
+        // here all the loads are done: a wait for one behind the stores below
+        // would wait for those too
+        auto done = [](double4 &v) { asm volatile("" : "+v"(v.x), "+v"(v.y), "+v"(v.z)); };
+        done(u0_1); done(p0_1); done(uc_1); done(pc_1); done(r0_1); done(ap_1);
+        if (KEEP_AXIS) { done(ua_1); done(pa_1); }
+        asm volatile("" : "+v"(ap_1.w), "+v"(th_1), "+v"(free_1));
+    }
+    // Before the first thread of the workgroup changes a flag a barrier follows
+    // the reads above.  Barriers are of LDS only, as nothing else goes between
+    // threads, but for the side-chain angles.
     if (mode == MODE_TAU && !pending) return;
     if (!active) {
+        lds_barrier();
         if (lead) {
             st->pending_post = 0;
             if (mode == MODE_FINAL) st->active = running(st);
@@ -1504,25 +1678,29 @@ __global__ __launch_bounds__(NT) void k_chain(Batch bt, int mode)
             const int lb = lb0 + grp, a = lb * ATOM_BLOCK + gt;
             double4 r;
             double S[WPART];
-            atom_wrench(cd, a, r, S);
+            wrench_of(ONE ? in_1 : load_force(cd, min(a, n - 1)), a < n, r, S);
             wave_suffix(S);
-            if (!ONE) __syncthreads();  // the last pass has read s_red
+            if (!ONE) lds_barrier();  // the last pass has read s_red
             if (lane == 0)
 #pragma unroll
                 for (int k = 0; k < WPART; ++k) s_red[w][k] = S[k];
-            __syncthreads();
+            lds_barrier();
+            double later[6] = {0, 0, 0, 0, 0, 0};  // the waves of the block after this one
 #pragma unroll
-            for (int k = 0; k < 6; ++k) {
-                double t = 0.0;
-                for (int i = w + 1; i < w0 + WPB; ++i) t += s_red[i][k];
-                S[k] += t;
-            }
+            for (int i = 1; i < WPB; ++i)
+#pragma unroll
+                for (int k = 0; k < 6; ++k) {
+                    const double t = s_red[w0 + i][k];
+                    later[k] = w0 + i > w ? later[k] + t : later[k];
+                }
+#pragma unroll
+            for (int k = 0; k < 6; ++k) S[k] += later[k];
             if (a < n) {
                 const int res = a / APR, slot = a - res * APR;
                 if (slot == 4 && n_chi) s_tau[J + res] = chi_torque(cd, a, r);
                 if (slot == 2 || slot == 8) {
                     const int j = 2 * res + (slot == 8 ? 1 : 0);
-                    s_tau[j] = joint_torque(cd, j, S);
+                    s_tau[j] = KEEP_AXIS ? axis_torque(ua_1, pa_1, S) : joint_torque(cd, j, S);
                 }
             }
             if (gt < WPART && lb < nblk) {
@@ -1532,7 +1710,7 @@ __global__ __launch_bounds__(NT) void k_chain(Batch bt, int mode)
                 s_part[lb][gt] = t;
             }
         }
-        __syncthreads();
+        lds_barrier();
         int bad = 0;
         for (int j0 = 0; j0 < J; j0 += NT) {
             const int j = j0 + tid, jlo = j - gt;
@@ -1568,12 +1746,12 @@ __global__ __launch_bounds__(NT) void k_chain(Batch bt, int mode)
         tm = wave_max(tm);
         if (lane == 0) s_tm[w] = tm;
         bad = __any(bad);
-        if (w == 0) {
-            // energies and the non-finite force flag of the pending forces
+        if (w == NW - 1) {
+            // (the last wave has the fewest joints) energies and the non-finite force flag of the pending forces
             double E[4];
 #pragma unroll
             for (int k = 0; k < 4; ++k) E[k] = wave_sum(lane < nblk ? s_part[lane][6 + k] : 0.0);
-            if (lead) {
+            if (lane == 0) {
                 st->e_elec = E[0];
                 st->e_vdw = E[1];
                 st->e_cav = E[2];
@@ -1582,7 +1760,7 @@ __global__ __launch_bounds__(NT) void k_chain(Batch bt, int mode)
             bad = bad || E[3] > 0.0;
         }
         if (lane == 0) s_bad[w] = bad;
-        __syncthreads();
+        lds_barrier();
         if (mode == MODE_TAU) return;
         bad = 0;
 #pragma unroll
@@ -1618,6 +1796,7 @@ __global__ __launch_bounds__(NT) void k_chain(Batch bt, int mode)
         }
     } else if (mode == MODE_ITER) {
         go = 1;
+        lds_barrier();
         if (lead) st->run = 1;
     }
     const bool on = go && !grid_bad;
@@ -1628,7 +1807,8 @@ __global__ __launch_bounds__(NT) void k_chain(Batch bt, int mode)
         }
         return;
     }
-    __syncthreads();  // s_tau is read, the angles are written
+    if (n_chi) __syncthreads();  // the side-chain angles are written
+    else lds_barrier();          // s_tau is read
 
     // forward kinematics: s_G[j + 1] = T_jlo o ... o T_j inside each joint
     // block, then the products of the earlier blocks in front
@@ -1646,27 +1826,37 @@ __global__ __launch_bounds__(NT) void k_chain(Batch bt, int mode)
                 }
                 x = joint_xf_of(u0_1, p0_1, th_1);
             }
+            const int held = J - (j - lane);  // joints in the wave
 #pragma unroll
-            for (int d = 1; d < WAVE; d <<= 1) {
-                Xf y = xf_from_below(x, d);
-                if (lane >= d) x = xf_mul(y, x);
-            }
+            for (int d = 1; d < WAVE; d <<= 1)
+                if (d < held) {  // else there is nothing below to take
+                    const Xf y = xf_from_below(x, d);
+                    if (lane >= d) {
+                        masked_branch();
+                        x = xf_mul(y, x);
+                    }
+                }
             if (lane == WAVE - 1) xf_store(s_red[w], x);
         }
-        __syncthreads();
+        lds_barrier();
         if (holds) {
             if (w > w0) {
                 Xf pre = xf_load(s_red[w0]);
                 for (int i = w0 + 1; i < w; ++i) pre = xf_mul(pre, xf_load(s_red[i]));
                 x = xf_mul(pre, x);
             }
-            if (j < J) xf_store(s_G[j + 1], x);
-            if (j == min(J, (jb + 1) * JOINT_BLOCK) - 1) xf_store(s_blk[jb], x);
+            if (ONE) x = xf_mul(xf_identity(), x);  // nothing in front of the one block (the product keeps its zeros' signs)
+            if (j < J) {
+                xf_store(s_G[j + 1], x);
+                if (ONE) fk_emit(x, j, u0_1, p0_1, cd->jcur);
+            }
+            if (!ONE && j == min(J, (jb + 1) * JOINT_BLOCK) - 1) xf_store(s_blk[jb], x);
         }
-        if (!ONE) __syncthreads();
+        if (!ONE) lds_barrier();
     }
-    __syncthreads();
-    if (w == 0) {
+    if (lead) xf_store(s_G[0], xf_identity());
+    lds_barrier();
+    if (!ONE && w == 0) {
         if (lane == 0) xf_store(s_carry[0], xf_identity());
         if (njb > 1) {
             Xf x = lane < njb - 1 ? xf_load(s_blk[lane]) : xf_identity();
@@ -1674,19 +1864,23 @@ __global__ __launch_bounds__(NT) void k_chain(Batch bt, int mode)
 #pragma unroll
             for (int d = 1; d < 8; d <<= 1) {
                 Xf y = xf_from_below(x, d);
-                if (lane >= d) x = xf_mul(y, x);
+                if (lane >= d) {
+                    masked_branch();
+                    x = xf_mul(y, x);
+                }
             }
             if (lane < njb - 1) xf_store(s_carry[lane + 1], x);
         }
     }
-    if (lead) xf_store(s_G[0], xf_identity());
-    __syncthreads();
-    for (int j = tid; j < J; j += NT) {
-        const Xf G = xf_mul(xf_load(s_carry[j / JOINT_BLOCK]), xf_load(s_G[j + 1]));
-        xf_store(s_G[j + 1], G);
-        fk_emit(G, j, ONE ? u0_1 : cd->joint0[2 * j], ONE ? p0_1 : cd->joint0[2 * j + 1], cd->jcur);
+    if (!ONE) {
+        lds_barrier();
+        for (int j = tid; j < J; j += NT) {
+            const Xf G = xf_mul(xf_load(s_carry[j / JOINT_BLOCK]), xf_load(s_G[j + 1]));
+            xf_store(s_G[j + 1], G);
+            fk_emit(G, j, cd->joint0[2 * j], cd->joint0[2 * j + 1], cd->jcur);
+        }
+        lds_barrier();
     }
-    __syncthreads();
 
     // positions and bounding box
     double lo[3] = {DBL_MAX, DBL_MAX, DBL_MAX}, hi[3] = {-DBL_MAX, -DBL_MAX, -DBL_MAX};
@@ -1703,51 +1897,54 @@ __global__ __launch_bounds__(NT) void k_chain(Batch bt, int mode)
         lo[0] = fmin(lo[0], r.x); lo[1] = fmin(lo[1], r.y); lo[2] = fmin(lo[2], r.z);
         hi[0] = fmax(hi[0], r.x); hi[1] = fmax(hi[1], r.y); hi[2] = fmax(hi[2], r.z);
     }
-#pragma unroll
-    for (int k = 0; k < 3; ++k) { lo[k] = wave_min(lo[k]); hi[k] = wave_max(hi[k]); }
+    wave_box(lo, hi);
     fin = !__any(!fin);
     if (lane == 0) {
 #pragma unroll
         for (int k = 0; k < 3; ++k) { s_red[w][k] = lo[k]; s_red[w][3 + k] = hi[k]; }
         s_bad[w] = fin ? 0 : 1;
     }
-    __syncthreads();
-    if (lead) {
-        bool ok = true;
-        for (int i = 0; i < NW; ++i) {
+    lds_barrier();
+    // every wave sizes the grid
+    const int ax = min(lane, 2);
+    double lo_a = DBL_MAX, hi_a = -DBL_MAX;
+    bool ok = true;
 #pragma unroll
-            for (int k = 0; k < 3; ++k) { lo[k] = fmin(lo[k], s_red[i][k]); hi[k] = fmax(hi[k], s_red[i][3 + k]); }
-            ok = ok && !s_bad[i];
-        }
-        const Grid g = size_grid(cd, lo, hi, &ok);
-        s_flag = ok;
-        if (ok) {
-            s_g = g;
-            *grid_of(cd) = g;
-        } else {
-            // a conformation that never had a grid stops the chain before its
-            // first iteration
+    for (int i = 0; i < NW; ++i) {
+        lo_a = min_num(lo_a, s_red[i][ax]);
+        hi_a = max_num(hi_a, s_red[i][3 + ax]);
+        ok = ok && !s_bad[i];
+    }
+    const Grid g = size_grid(rule, lo_a, hi_a, ok);
+    if (!ok) {
+        // a conformation that never had a grid stops the chain before its
+        // first iteration
+        if (lead) {
             st->status = -4;
             if (fresh) st->run = 0;
             else st->grid_bad = 1;
+            st->need_grid = 0;
             st->pending_post = 0;
             st->active = 0;
         }
+        return;
+    }
+    if (tid == NT - WAVE) {
+        *grid_of(dev) = g;
         st->need_grid = 0;
     }
-    __syncthreads();
-    if (!s_flag) return;
 
     // cell list: counts and starts two to a word
-    const int nc = s_g.n_cells, nword = (nc + 1) / 2;
-    unsigned *s_cell = reinterpret_cast<unsigned *>(s_dyn);
+    const int nc = g.n_cells, nword = (nc + 1) / 2;
     unsigned short *s_ids = reinterpret_cast<unsigned short *>(s_cell + cd->cap_cells / 2);
     unsigned short *s_key = s_ids + n, *s_arr = s_key + n;  // unless each thread keeps its one atom's
-    for (int i = tid; i < nword; i += NT) s_cell[i] = 0;
-    __syncthreads();
+    if (!ONE) {
+        for (int i = tid; i < nword; i += NT) s_cell[i] = 0;
+        lds_barrier();
+    }
     int key1 = 0, arr1 = 0;
     for (int a = tid; a < n; a += NT) {
-        const int key = cell_of(s_g, ONE ? r1 : cd->r[a]), sh = 16 * (key & 1);
+        const int key = cell_of(g, ONE ? r1 : cd->r[a]), sh = 16 * (key & 1);
         const int arr = (int)((atomicAdd(&s_cell[key >> 1], 1u << sh) >> sh) & 0xffffu);
         if (ONE) {
             key1 = key;
@@ -1757,28 +1954,35 @@ __global__ __launch_bounds__(NT) void k_chain(Batch bt, int mode)
             s_arr[a] = (unsigned short)arr;
         }
     }
-    __syncthreads();
+    lds_barrier();
     {
         const int per = (nword + NT - 1) / NT, i0 = min(tid * per, nword), i1 = min(i0 + per, nword);
-        int sum = 0, total = 0;
+        int sum = 0;
         for (int i = i0; i < i1; ++i) sum += (int)(s_cell[i] & 0xffffu) + (int)(s_cell[i] >> 16);
-        int run = block_excl_scan(sum, s_scan, &total);
+        const int x = wave_scan_i(sum);
+        if (lane == WAVE - 1) s_scan[w] = x;
+        lds_barrier();
+        int run = x - sum;
+#pragma unroll
+        for (int i = 0; i < NW; ++i) run += i < w ? s_scan[i] : 0;
         for (int i = i0; i < i1; ++i) {
             const unsigned v = s_cell[i];
             s_cell[i] = (unsigned)run | ((unsigned)(run + (int)(v & 0xffffu)) << 16);
             run += (int)(v & 0xffffu) + (int)(v >> 16);
         }
     }
-    __syncthreads();
+    lds_barrier();
     auto start_of = [&](int c) -> int { return c < nc ? (int)((s_cell[c >> 1] >> (16 * (c & 1))) & 0xffffu) : n; };
     for (int c = tid; c <= nc; c += NT) cd->cell_start[c] = start_of(c);
     for (int a = tid; a < n; a += NT) s_ids[start_of(ONE ? key1 : s_key[a]) + (ONE ? arr1 : s_arr[a])] = (unsigned short)a;
-    __syncthreads();
+    lds_barrier();
     for (int a = tid; a < n; a += NT) {
         // the stable slot: the members of the cell with a smaller index before it
         const int key = ONE ? key1 : s_key[a], b = start_of(key), e = start_of(key + 1);
         int pos = b;
-        for (int s = b; s < e; ++s) pos += s_ids[s] < a ? 1 : 0;
+        for (int s = b; s < e; s += 4)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) pos += (s + k < e && s_ids[min(s + k, n - 1)] < a) ? 1 : 0;
         const double4 r = ONE ? r1 : cd->r[a];
         cd->s_idx[pos] = a;
         cd->s_r[pos] = make_double4(r.x, r.y, r.z, __longlong_as_double((long long)a | ((long long)(a / APR) << 32)));
@@ -1791,18 +1995,6 @@ __global__ __launch_bounds__(NT) void k_chain(Batch bt, int mode)
     }
 }
 
-// Loads, stores and atomics through a pointer of unknown address space are
-// flat instructions, which count against the LDS counter as well as the
-// vector-memory one: every LDS wait then also waits for them.  The device
-// arrays of the force kernel are all in global memory, and it reaches them
-// through these global-address-space views (plain pointers in the host
-// pass, which only checks the device code).
-#if defined(__HIP_DEVICE_COMPILE__)
-template <typename T> using gptr = __attribute__((address_space(1))) T *;
-#else
-template <typename T> using gptr = T *;
-#endif
-template <typename T> __device__ __forceinline__ gptr<T> glob(T *p) { return (gptr<T>)p; }
 using CDev = gptr<const ChainDev>;
 // fixed-point accumulation of the solvation force
 __device__ __forceinline__ void fix_add(gptr<long long> p, long long v)
@@ -2877,7 +3069,7 @@ __global__ __launch_bounds__(ATOM_BLOCK) void k_wrench(Batch bt)
     const int lane = threadIdx.x & (WAVE - 1), w = threadIdx.x / WAVE, nw = ATOM_BLOCK / WAVE;
     double4 r;
     double S[WPART];
-    atom_wrench(cd, a, r, S);
+    wrench_of(load_force(cd, min(a, cd->n_atoms - 1)), a < cd->n_atoms, r, S);
     wave_suffix(S);
     if (lane == 0)
         for (int k = 0; k < WPART; ++k) s_w[w][k] = S[k];
@@ -2916,9 +3108,11 @@ hipError_t launch_tau(const Batch &b, hipStream_t s)
 template <int NT, bool ONE>
 static hipError_t launch_chain_form(const Batch &b, int mode, hipStream_t s)
 {
-    // the larger of the link transforms and the cell list
+    // the link transforms and the cell list, which starts as zeros where each
+    // has its place (ONE) and follows in the same place where not
     const int n = b.max_atoms, links = 2 * (n / APR) + 1;
-    const size_t lds = std::max(sizeof(double) * 12 * links, sizeof(uint16_t) * (size_t)(cell_capacity(n) + (ONE ? 1 : 3) * n));
+    const size_t xf = sizeof(double) * 12 * links, cells = sizeof(uint16_t) * (size_t)(cell_capacity(n) + (ONE ? 1 : 3) * n);
+    const size_t lds = ONE ? xf + cells : std::max(xf, cells);
     if (lds > 65536) {
         const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_chain<NT, ONE>),
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, CHAIN_LDS);
