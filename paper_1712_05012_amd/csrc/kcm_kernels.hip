@@ -311,7 +311,7 @@ __device__ __forceinline__ Xf xf_from_below(const Xf &x, int d)
     return y;
 }
 
-__device__ __forceinline__ void xf_store(double *p, const Xf &x)
+template <typename P> __device__ __forceinline__ void xf_store(P p, const Xf &x)
 {
 #pragma unroll
     for (int k = 0; k < 9; ++k) p[k] = x.r[k];
@@ -319,7 +319,7 @@ __device__ __forceinline__ void xf_store(double *p, const Xf &x)
     for (int k = 0; k < 3; ++k) p[9 + k] = x.t[k];
 }
 
-__device__ __forceinline__ Xf xf_load(const double *p)
+template <typename P> __device__ __forceinline__ Xf xf_load(P p)
 {
     Xf x;
 #pragma unroll
@@ -363,30 +363,36 @@ __device__ void block_sum(double (&v)[K], double *scratch)
     const int lane = threadIdx.x & (WAVE - 1), w = threadIdx.x / WAVE, nw = blockDim.x / WAVE;
 #pragma unroll
     for (int k = 0; k < K; ++k) v[k] = wave_sum(v[k]);
-    __syncthreads();
+    lds_barrier();
     if (lane == 0)
         for (int k = 0; k < K; ++k) scratch[w * K + k] = v[k];
-    __syncthreads();
+    lds_barrier();
 #pragma unroll
     for (int k = 0; k < K; ++k) {
         double s = 0.0;
         for (int i = 0; i < nw; ++i) s += scratch[i * K + k];
         v[k] = s;
     }
-    __syncthreads();
+    lds_barrier();
 }
 
-__device__ double block_max(double v, double *scratch)
+// The largest v over the block and whether any thread has bad set, in every
+// thread.  scratch, s_bad: one entry per wave, not in use.
+__device__ __forceinline__ double block_max_any(double v, bool &bad, double *scratch, int *s_bad)
 {
     const int lane = threadIdx.x & (WAVE - 1), w = threadIdx.x / WAVE, nw = blockDim.x / WAVE;
     v = wave_max(v);
-    __syncthreads();
-    if (lane == 0) scratch[w] = v;
-    __syncthreads();
-    double m = -DBL_MAX;
-    for (int i = 0; i < nw; ++i) m = fmax(m, scratch[i]);
-    __syncthreads();
-    return m;
+    bad = __any(bad);
+    if (lane == 0) {
+        scratch[w] = v;
+        s_bad[w] = bad;
+    }
+    lds_barrier();
+    for (int i = 0; i < nw; ++i) {
+        v = fmax(v, scratch[i]);
+        bad = bad || s_bad[i];
+    }
+    return v;
 }
 
 // Exclusive prefix sum of one int per thread over the block; *total gets the sum.
@@ -394,15 +400,15 @@ __device__ int block_excl_scan(int v, int *scratch, int *total)
 {
     const int lane = threadIdx.x & (WAVE - 1), w = threadIdx.x / WAVE, nw = blockDim.x / WAVE;
     const int x = wave_scan_i(v);
-    __syncthreads();
+    lds_barrier();
     if (lane == WAVE - 1) scratch[w] = x;
-    __syncthreads();
+    lds_barrier();
     int base = 0, tot = 0;
     for (int i = 0; i < nw; ++i) {
         if (i < w) base += scratch[i];
         tot += scratch[i];
     }
-    __syncthreads();
+    lds_barrier();
     *total = tot;
     return base + x - v;
 }
@@ -478,14 +484,18 @@ __device__ __forceinline__ Xf xf_shfl_idx(const Xf &x, int src)
 template <typename P>
 __device__ __forceinline__ void fk_emit(const Xf &G, int j, const double4 &u0, const double4 &p0, P jcur)
 {
+    // the fused steps written out: every kernel that calls this rounds alike
+    auto row = [&](int k, const double4 &v) {
+        return fma(G.r[k + 2], v.z, fma(G.r[k], v.x, G.r[k + 1] * v.y));
+    };
     double4 u, p;
-    u.x = G.r[0] * u0.x + G.r[1] * u0.y + G.r[2] * u0.z;
-    u.y = G.r[3] * u0.x + G.r[4] * u0.y + G.r[5] * u0.z;
-    u.z = G.r[6] * u0.x + G.r[7] * u0.y + G.r[8] * u0.z;
+    u.x = row(0, u0);
+    u.y = row(3, u0);
+    u.z = row(6, u0);
     u.w = 0.0;
-    p.x = G.r[0] * p0.x + G.r[1] * p0.y + G.r[2] * p0.z + G.t[0];
-    p.y = G.r[3] * p0.x + G.r[4] * p0.y + G.r[5] * p0.z + G.t[1];
-    p.z = G.r[6] * p0.x + G.r[7] * p0.y + G.r[8] * p0.z + G.t[2];
+    p.x = row(0, p0) + G.t[0];
+    p.y = row(3, p0) + G.t[1];
+    p.z = row(6, p0) + G.t[2];
     p.w = 0.0;
     jcur[2 * j] = u;
     jcur[2 * j + 1] = p;
@@ -506,6 +516,43 @@ __device__ __forceinline__ Xf joint_xf_of(const double4 &u, const double4 &p, do
     for (int i = 0; i < 3; ++i) x.t[i] = ((&p.x)[i]) - (x.r[3 * i] * p.x + x.r[3 * i + 1] * p.y + x.r[3 * i + 2] * p.z);
     return x;
 }
+
+// A chain's descriptor as the chain kernels use it, read once at their start
+// while nothing is stored yet: into scalar registers, where a later look would
+// be a vector load (the stores might change the descriptor, for all the
+// compiler knows) with a few hundred cycles of latency each.
+struct ChainView {
+    int n_atoms, n_joints, n_chi, n_bb_blocks, cap_cells, precision, step_rule;
+    double cutoff, kappa, max_step, delta_r, cell_min, roff_max;
+    gptr<double> theta, dtheta, tau, xform_loc, blk_xf, tmax_part, bbox_part, wrench_part;
+    gptr<uint8_t> mask;
+    gptr<double4> joint0, jcur, r0, r, aparam, s_r, s_p, f_pair, e_atom;
+    gptr<int32_t> bad_part, cell_key, cell_count, cell_start, cell_local, scan_part, s_tmp, s_idx;
+    gptr<long long> f_cav;
+    __device__ __forceinline__ explicit ChainView(const ChainDev *d)
+        : n_atoms(d->n_atoms), n_joints(d->n_joints), n_chi(d->n_chi), n_bb_blocks(d->n_bb_blocks),
+          cap_cells(d->cap_cells), precision(d->precision), step_rule(d->step_rule), cutoff(d->cutoff),
+          kappa(d->kappa), max_step(d->max_step), delta_r(d->delta_r), cell_min(d->cell_min), roff_max(d->roff_max),
+          theta(glob(d->theta)), dtheta(glob(d->dtheta)), tau(glob(d->tau)), xform_loc(glob(d->xform_loc)),
+          blk_xf(glob(d->blk_xf)), tmax_part(glob(d->tmax_part)), bbox_part(glob(d->bbox_part)),
+          wrench_part(glob(d->wrench_part)), mask(glob(d->mask)), joint0(glob(d->joint0)), jcur(glob(d->jcur)),
+          r0(glob(d->r0)), r(glob(d->r)), aparam(glob(d->aparam)), s_r(glob(d->s_r)), s_p(glob(d->s_p)),
+          f_pair(glob(d->f_pair)), e_atom(glob(d->e_atom)), bad_part(glob(d->bad_part)), cell_key(glob(d->cell_key)),
+          cell_count(glob(d->cell_count)), cell_start(glob(d->cell_start)), cell_local(glob(d->cell_local)),
+          scan_part(glob(d->scan_part)), s_tmp(glob(d->s_tmp)), s_idx(glob(d->s_idx)), f_cav(glob(d->f_cav))
+    {
+    }
+};
+// Loads that are done where this stands: all those named go out together, ahead
+// of the flags that say whether they are needed (they are of memory that is
+// there either way), in place of one latency after the other.
+// (The eight small kernels of an iteration, which are bound by such latencies:
+// 43.4 us before, 38.8 us with these and LDS barriers, for 10,000 atoms.)
+__device__ __forceinline__ void loaded_one(double v) { asm volatile("" : : "v"(v)); }
+__device__ __forceinline__ void loaded_one(long long v) { asm volatile("" : : "v"(v)); }
+__device__ __forceinline__ void loaded_one(int v) { asm volatile("" : : "v"(v)); }
+__device__ __forceinline__ void loaded_one(const double4 &v) { asm volatile("" : : "v"(v.x), "v"(v.y), "v"(v.z)); }
+template <typename... T> __device__ __forceinline__ void loaded(const T &...v) { (loaded_one(v), ...); }
 
 // Grid of Sec. 3.2 from the per-workgroup bounding boxes of the placed atoms,
 // plus a margin; the cell edge starts at max(cell_min, reach / MAX_REACH) and
@@ -736,75 +783,71 @@ __device__ __forceinline__ double stepped_angle(double th, double d)
 __global__ __launch_bounds__(JOINT_BLOCK) void k_tau(Batch bt)
 {
     const Owner own = owner_of(bt, bt.jblk_chain, bt.jblk_off, blockIdx.x);
-    const ChainDev *cd = own.cd;
-    ChainStats *st = stats_of(cd);
-    if (!st->active || !st->pending_post) return;
+    ChainStats *st = stats_of(own.cd);
+    const ChainView view(own.cd), *cd = &view;
     __shared__ double s_red[(JOINT_BLOCK / WAVE) * 6];
+    __shared__ double s_max[JOINT_BLOCK / WAVE];
+    __shared__ int s_bad[JOINT_BLOCK / WAVE];
     __shared__ double s_S[8][6];
     const int jb = blockIdx.x - own.first;
     const int tid = threadIdx.x;
-    if (jb >= cd->n_bb_blocks) {
-        // a block of side-chain joints: k_wrench left each chi torque whole
-        const int jc = (jb - cd->n_bb_blocks) * JOINT_BLOCK + tid, j = cd->n_joints + jc;
-        double tabs = 0.0, bad = 0.0;
-        if (jc < cd->n_chi) {
-            const double t = cd->tau[j];
-            if (!isfinite(t)) bad = 1.0;
-            if (cd->mask[j]) tabs = fabs(t);
-        }
-        const double tmax = block_max(tabs, s_red);
-        const double anybad = block_max(bad, s_red);
-        if (tid == 0) {
-            cd->tmax_part[jb] = tmax;
-            cd->bad_part[jb] = anybad > 0.0 ? 1 : 0;
-        }
-        return;
-    }
     const int J = cd->n_joints, n = cd->n_atoms;
+    // the blocks of side-chain joints come last; k_wrench left each chi torque whole
+    const bool chi = jb >= cd->n_bb_blocks;
+    const int j = chi ? J + (jb - cd->n_bb_blocks) * JOINT_BLOCK + tid : jb * JOINT_BLOCK + tid;
+    const int end = chi ? J + cd->n_chi : J, jc = min(j, end - 1), ja = min(jc, J - 1);
+    double t = cd->tau[jc];
+    const int moves = cd->mask[jc];
+    const double4 u = cd->jcur[2 * ja], p = cd->jcur[2 * ja + 1];
     const int nblk = (n + ATOM_BLOCK - 1) / ATOM_BLOCK;
-    const double *__restrict__ part = cd->wrench_part;
+    const auto part = cd->wrench_part;
     // the joints of this workgroup take their later-workgroup wrench after
     // atom workgroups blo..bhi (at most 6 of them)
-    const int jlo = jb * JOINT_BLOCK, jhi = min(J, jlo + JOINT_BLOCK) - 1;
+    const int jlo = min(jb * JOINT_BLOCK, J - 1), jhi = min(J, jlo + JOINT_BLOCK) - 1;
     const int blo = first_atom_of_joint(jlo) / ATOM_BLOCK, bhi = first_atom_of_joint(jhi) / ATOM_BLOCK;
     __shared__ double s_P[8][6];
-    if (tid < 6 * (bhi - blo + 1)) s_P[tid / 6][tid % 6] = part[WPART * (blo + tid / 6) + tid % 6];
-    double v[6] = {0, 0, 0, 0, 0, 0};
-    for (int b = bhi + 1 + tid; b < nblk; b += JOINT_BLOCK)
+    const double P = part[WPART * min(blo + tid / 6, nblk - 1) + tid % 6];
+    double v[6] = {0, 0, 0, 0, 0, 0}, E[4] = {0, 0, 0, 0};
+    if (!chi)
+        for (int b = bhi + 1 + tid; b < nblk; b += JOINT_BLOCK)
 #pragma unroll
-        for (int k = 0; k < 6; ++k) v[k] += part[WPART * b + k];
-    block_sum<6>(v, s_red);
-    if (tid < 6) {
-        // suffix over the touched workgroups, one wrench component per thread
-        double x = v[tid];
-        for (int b = bhi; b >= blo; --b) {
-            s_S[b - blo][tid] = x;
-            x += s_P[b - blo][tid];
-        }
-    }
-    __syncthreads();
-
-    const int j = jlo + tid;
-    double tabs = 0.0, bad = 0.0;
-    if (j < J) {
-        const double *S = s_S[first_atom_of_joint(j) / ATOM_BLOCK - blo];
-        const double t = cd->tau[j] + joint_torque(cd, j, S);
-        cd->tau[j] = t;
-        if (!isfinite(t)) bad = 1.0;
-        if (cd->mask[j]) tabs = fabs(t);
-    }
-    const double tmax = block_max(tabs, s_red);
-    const double anybad = block_max(bad, s_red);
-    if (tid == 0) {
-        cd->tmax_part[jb] = tmax;
-        cd->bad_part[jb] = anybad > 0.0 ? 1 : 0;
-    }
-    if (jb == 0) {
-        // energies and the non-finite force flag of the pending forces
-        double E[4] = {0, 0, 0, 0};
+            for (int k = 0; k < 6; ++k) v[k] += part[WPART * b + k];
+    if (jb == 0)
         for (int b = tid; b < nblk; b += JOINT_BLOCK)
 #pragma unroll
             for (int k = 0; k < 4; ++k) E[k] += part[WPART * b + 6 + k];
+    loaded(t, moves, u, p, P, v[0], v[1], v[2], v[3], v[4], v[5], E[0], E[1], E[2], E[3]);
+    if (!st->active || !st->pending_post) return;
+    double tabs = 0.0;
+    bool bad = false;
+    if (!chi) {
+        if (tid < 6 * (bhi - blo + 1)) s_P[tid / 6][tid % 6] = P;
+        block_sum<6>(v, s_red);
+        if (tid < 6) {
+            // suffix over the touched workgroups, one wrench component per thread
+            double x = v[tid];
+            for (int b = bhi; b >= blo; --b) {
+                s_S[b - blo][tid] = x;
+                x += s_P[b - blo][tid];
+            }
+        }
+        lds_barrier();
+        if (j < end) {
+            t += axis_torque(u, p, s_S[first_atom_of_joint(j) / ATOM_BLOCK - blo]);
+            cd->tau[j] = t;
+        }
+    }
+    if (j < end) {
+        bad = !isfinite(t);
+        if (moves) tabs = fabs(t);
+    }
+    const double tmax = block_max_any(tabs, bad, s_max, s_bad);
+    if (tid == 0) {
+        cd->tmax_part[jb] = tmax;
+        cd->bad_part[jb] = bad ? 1 : 0;
+    }
+    if (jb == 0) {
+        // energies and the non-finite force flag of the pending forces
         block_sum<4>(E, s_red);
         if (tid == 0) {
             st->e_elec = E[0];
@@ -825,11 +868,10 @@ __global__ __launch_bounds__(JOINT_BLOCK) void k_tau(Batch bt)
 __global__ __launch_bounds__(JOINT_BLOCK) void k_stepfk(Batch bt, int mode)
 {
     const Owner own = owner_of(bt, bt.jblk_chain, bt.jblk_off, blockIdx.x);
-    const ChainDev *cd = own.cd;
-    ChainStats *st = stats_of(cd);
-    if (!st->active) return;
-    if (mode == MODE_BOOT && !st->need_grid) return;
+    ChainStats *st = stats_of(own.cd);
+    const ChainView view(own.cd), *cd = &view;
     __shared__ double s_red[JOINT_BLOCK / WAVE];
+    __shared__ int s_bad[JOINT_BLOCK / WAVE];
     __shared__ double s_x[JOINT_BLOCK / WAVE][12];
     const int jb = blockIdx.x - own.first;
     const int tid = threadIdx.x, lane = tid & (WAVE - 1), w = tid / WAVE;
@@ -837,22 +879,29 @@ __global__ __launch_bounds__(JOINT_BLOCK) void k_stepfk(Batch bt, int mode)
     // backbone blocks first; the blocks after them hold the side-chain joints,
     // which step with the others but are not part of the chain's scan
     const bool chi_block = jb >= cd->n_bb_blocks;
-    if (chi_block && mode == MODE_BOOT) return;
     const int j = chi_block ? J + (jb - cd->n_bb_blocks) * JOINT_BLOCK + tid : jb * JOINT_BLOCK + tid;
     const bool valid = chi_block ? j < J + cd->n_chi : j < J;
-    double th = valid ? cd->theta[j] : 0.0;
+    const int jv = min(j, (chi_block ? J + cd->n_chi : J) - 1), ja = min(jv, J - 1);
+    double th = cd->theta[jv];
+    const double tau = cd->tau[jv];
+    const int moves = cd->mask[jv];
+    const double4 u0 = cd->joint0[2 * ja], p0 = cd->joint0[2 * ja + 1];
+    const int nb = cd->n_bb_blocks + (cd->n_chi + JOINT_BLOCK - 1) / JOINT_BLOCK;
+    double tm = 0.0;
+    int bad_parts = 0;
+    for (int b = tid; b < nb; b += JOINT_BLOCK) {
+        tm = fmax(tm, cd->tmax_part[b]);
+        bad_parts |= cd->bad_part[b];
+    }
+    loaded(th, tau, moves, u0, p0, tm, bad_parts);
+    if (!st->active) return;
+    if (mode == MODE_BOOT && (chi_block || !st->need_grid)) return;
     const bool lead = jb == 0 && tid == 0;
 
     if (mode != MODE_BOOT && st->pending_post) {
-        const int nb = cd->n_bb_blocks + (cd->n_chi + JOINT_BLOCK - 1) / JOINT_BLOCK;
-        double tm = 0.0, bad = 0.0;
-        for (int b = tid; b < nb; b += JOINT_BLOCK) {
-            tm = fmax(tm, cd->tmax_part[b]);
-            if (cd->bad_part[b]) bad = 1.0;
-        }
-        tm = block_max(tm, s_red);
-        bad = block_max(bad, s_red);
-        if (bad > 0.0 || st->post_bad) {
+        bool bad = bad_parts != 0;
+        tm = block_max_any(tm, bad, s_red, s_bad);
+        if (bad || st->post_bad) {
             if (lead) {
                 st->status = -4;
                 st->run = 0;
@@ -861,7 +910,7 @@ __global__ __launch_bounds__(JOINT_BLOCK) void k_stepfk(Batch bt, int mode)
         }
         const double scale = step_scale(cd, tm);
         if (valid) {
-            const double d = cd->mask[j] ? scale * cd->tau[j] : 0.0;
+            const double d = moves ? scale * tau : 0.0;
             cd->dtheta[j] = d;
             th = stepped_angle(th, d);
             cd->theta[j] = th;
@@ -887,17 +936,17 @@ __global__ __launch_bounds__(JOINT_BLOCK) void k_stepfk(Batch bt, int mode)
     if (mode == MODE_FINAL || chi_block) return;
 
     Xf x = xf_identity();
-    if (valid) x = joint_xf_of(cd->joint0[2 * j], cd->joint0[2 * j + 1], th);
+    if (valid) x = joint_xf_of(u0, p0, th);
 #pragma unroll
     for (int d = 1; d < WAVE; d <<= 1) {
         Xf y = xf_from_below(x, d);
         if (lane >= d) {
-                    masked_branch();
-                    x = xf_mul(y, x);
-                }
+            masked_branch();
+            x = xf_mul(y, x);
+        }
     }
     if (lane == WAVE - 1) xf_store(s_x[w], x);
-    __syncthreads();
+    lds_barrier();
     if (w > 0) {
         Xf pre = xf_load(s_x[0]);
         for (int i = 1; i < w; ++i) pre = xf_mul(pre, xf_load(s_x[i]));
@@ -944,12 +993,9 @@ __device__ __forceinline__ double4 placed_atom(const Chain *cd, int a, double4 q
 __global__ __launch_bounds__(ATOM_BLOCK) void k_place(Batch bt, int mode)
 {
     const Owner own = owner_of(bt, bt.blk_chain, bt.blk_off, blockIdx.x);
-    ChainDev *cd = own.cd;
-    ChainStats *st = stats_of(cd);
+    ChainStats *st = stats_of(own.cd);
+    const ChainView view(own.cd), *cd = &view;
     const int lb = blockIdx.x - own.first;
-    // the step and torque kernels of this iteration have consumed the pending forces
-    if (mode == MODE_ITER && lb == 0 && threadIdx.x == 0) st->pending_post = 0;
-    if (mode == MODE_BOOT ? !(st->active && st->need_grid) : !running(st)) return;
     __shared__ double s_G[LINKS_PER_BLOCK][12];
     __shared__ double s_c[2][12];
     __shared__ double s_bb[ATOM_BLOCK / WAVE][6];
@@ -960,6 +1006,17 @@ __global__ __launch_bounds__(ATOM_BLOCK) void k_place(Batch bt, int mode)
     const int l_lo = link_of_atom(a0), l_hi = link_of_atom(a1);
     // link l (>= 1) needs the product of the joint blocks before joint l-1
     const int jb_lo = (max(l_lo, 1) - 1) / JOINT_BLOCK, jb_hi = (max(l_hi, 1) - 1) / JOINT_BLOCK;
+    // zero position of the thread's atom, transform inside its block and joint of its link
+    const int a = a0 + tid, nL = l_hi - l_lo + 1, jl = max(l_lo + min(tid, nL - 1), 1) - 1;
+    const double4 r0 = cd->r0[min(a, n - 1)];
+    const Xf loc = xf_load(cd->xform_loc + 12 * jl);
+    const double4 u0 = cd->joint0[2 * jl], p0 = cd->joint0[2 * jl + 1];
+    static_assert(LINKS_PER_BLOCK <= ATOM_BLOCK, "a thread for each link");
+    if (tid < nL) xf_store(s_G[tid], loc);  // there until it is used: registers decide how many waves fit
+    loaded(r0, u0, p0);
+    // the step and torque kernels of this iteration have consumed the pending forces
+    if (mode == MODE_ITER && lb == 0 && tid == 0) st->pending_post = 0;
+    if (mode == MODE_BOOT ? !(st->active && st->need_grid) : !running(st)) return;
     if (w == 0) {
         Xf acc = xf_identity();
         for (int base = 0; base < jb_hi; base += WAVE) {
@@ -982,26 +1039,27 @@ __global__ __launch_bounds__(ATOM_BLOCK) void k_place(Batch bt, int mode)
             if (jb_hi == 0) xf_store(s_c[1], xf_identity());
         }
     }
-    __syncthreads();
-    const int nL = l_hi - l_lo + 1;
-    for (int t = tid; t < nL; t += ATOM_BLOCK) {
-        const int l = l_lo + t;
+    lds_barrier();
+    if (tid < nL) {
+        const int l = l_lo + tid;
         Xf G = xf_identity();
         if (l > 0) {
-            const int j = l - 1;
-            G = xf_mul(xf_load(s_c[j / JOINT_BLOCK == jb_lo ? 0 : 1]), xf_load(cd->xform_loc + 12 * j));
+            masked_branch();
+            G = xf_mul(xf_load(s_c[jl / JOINT_BLOCK == jb_lo ? 0 : 1]), xf_load(s_G[tid]));
         }
-        xf_store(s_G[t], G);
+        xf_store(s_G[tid], G);
         const int fa = first_atom_of_link(l);
-        if (l > 0 && fa >= a0 && fa <= a1) fk_emit(G, l - 1, cd->joint0[2 * (l - 1)], cd->joint0[2 * (l - 1) + 1], cd->jcur);
+        if (l > 0 && fa >= a0 && fa <= a1) {
+            masked_branch();
+            fk_emit(G, jl, u0, p0, cd->jcur);
+        }
     }
-    __syncthreads();
+    lds_barrier();
 
-    const int a = a0 + tid;
     double lo[3] = {DBL_MAX, DBL_MAX, DBL_MAX}, hi[3] = {-DBL_MAX, -DBL_MAX, -DBL_MAX};
     bool fin = true;
     if (a <= a1) {
-        const double4 r = placed_atom(cd, a, cd->r0[a], s_G[link_of_atom(a) - l_lo]);
+        const double4 r = placed_atom(cd, a, r0, s_G[link_of_atom(a) - l_lo]);
         cd->r[a] = r;
         fin = isfinite(r.x) && isfinite(r.y) && isfinite(r.z);
         if (mode == MODE_ITER) {
@@ -1012,14 +1070,13 @@ __global__ __launch_bounds__(ATOM_BLOCK) void k_place(Batch bt, int mode)
         lo[0] = r.x; lo[1] = r.y; lo[2] = r.z;
         hi[0] = r.x; hi[1] = r.y; hi[2] = r.z;
     }
-#pragma unroll
-    for (int k = 0; k < 3; ++k) { lo[k] = wave_min(lo[k]); hi[k] = wave_max(hi[k]); }
+    wave_box(lo, hi);
     const bool bad_w = __any(!fin);
     if (lane == 0) {
         for (int k = 0; k < 3; ++k) { s_bb[w][k] = lo[k]; s_bb[w][3 + k] = hi[k]; }
         s_bad[w] = bad_w ? 1 : 0;
     }
-    __syncthreads();
+    lds_barrier();
     if (tid < 6) {
         const int k = tid;
         double v = s_bb[0][k];
@@ -1043,7 +1100,7 @@ __global__ __launch_bounds__(ATOM_BLOCK) void k_place(Batch bt, int mode)
 // wave 0 of every key workgroup sizes it and the first one stores it.
 // ---------------------------------------------------------------------------
 // the grid from the chain's bounding-box partials (one wave)
-__device__ __forceinline__ Grid wave_grid(const ChainDev *cd, bool *ok)
+__device__ __forceinline__ Grid wave_grid(const ChainView *cd, bool *ok)
 {
     const int lane = (int)threadIdx.x & (WAVE - 1), nblk = (cd->n_atoms + ATOM_BLOCK - 1) / ATOM_BLOCK;
     double lo[3] = {DBL_MAX, DBL_MAX, DBL_MAX}, hi[3] = {-DBL_MAX, -DBL_MAX, -DBL_MAX};
@@ -1061,10 +1118,10 @@ __device__ __forceinline__ Grid wave_grid(const ChainDev *cd, bool *ok)
     return size_grid(grid_rule(cd), axis_of_lane(lo), axis_of_lane(hi), *ok);
 }
 
-__device__ __forceinline__ void store_grid(ChainDev *cd, ChainStats *st, const Grid &g, bool ok)
+__device__ __forceinline__ void store_grid(Grid *out, ChainStats *st, const Grid &g, bool ok)
 {
     if (ok) {
-        *grid_of(cd) = g;
+        *out = g;
     } else {
         st->status = -4;
         st->grid_bad = 1;
@@ -1073,41 +1130,30 @@ __device__ __forceinline__ void store_grid(ChainDev *cd, ChainStats *st, const G
 
 __global__ __launch_bounds__(WAVE) void k_grid(Batch bt)
 {
-    ChainDev *cd = bt.n_chains == 1 ? bt.only : bt.table[blockIdx.x];
-    ChainStats *st = stats_of(cd);
+    const ChainDev *dev = bt.n_chains == 1 ? bt.only : bt.table[blockIdx.x];
+    ChainStats *st = stats_of(dev);
+    const ChainView view(dev);
     if (!running(st)) return;
     bool ok;
-    const Grid g = wave_grid(cd, &ok);
-    if (threadIdx.x == 0) store_grid(cd, st, g, ok);
+    const Grid g = wave_grid(&view, &ok);
+    if (threadIdx.x == 0) store_grid(grid_of(dev), st, g, ok);
 }
 
 template <bool OWN_GRID>
 __global__ __launch_bounds__(ATOM_BLOCK) void k_cellkey(Batch bt)
 {
     const Owner own = owner_of(bt, bt.blk_chain, bt.blk_off, blockIdx.x);
-    ChainDev *cd = own.cd;
-    ChainStats *st = stats_of(cd);
+    ChainStats *st = stats_of(own.cd);
+    const ChainView view(own.cd), *cd = &view;
+    const int lb = blockIdx.x - own.first, a = lb * ATOM_BLOCK + threadIdx.x;
+    const bool valid = a < cd->n_atoms;
+    const double4 r = cd->r[min(a, cd->n_atoms - 1)];
+    loaded(r);
     // with OWN_GRID, grid_bad is set by this kernel: a workgroup that sees it
     // set by the first one would have found the same failure itself
     if (!running(st)) return;
     __shared__ int s_ok;
     __shared__ Grid s_g;
-    const int lb = blockIdx.x - own.first;
-    if (OWN_GRID) {
-        if (threadIdx.x < WAVE) {
-            bool ok;
-            const Grid g = wave_grid(cd, &ok);
-            if (threadIdx.x == 0) {
-                s_g = g;
-                s_ok = ok ? 1 : 0;
-                if (lb == 0) store_grid(cd, st, g, ok);
-            }
-        }
-        __syncthreads();
-        if (!s_ok) return;
-    } else if (threadIdx.x == 0) {
-        s_g = *grid_of(cd);
-    }
     // Atoms of the workgroup that share a cell take one count atomic between
     // them: an LDS table (open addressing on the key, twice as many slots as
     // atoms, so a probe always ends) gives each atom its rank among them, the
@@ -1119,12 +1165,24 @@ __global__ __launch_bounds__(ATOM_BLOCK) void k_cellkey(Batch bt)
         s_hkey[h] = -1;
         s_hcnt[h] = 0;
     }
-    __syncthreads();
-    const int a = lb * ATOM_BLOCK + threadIdx.x;
-    const bool valid = a < cd->n_atoms;
+    if (OWN_GRID) {
+        if (threadIdx.x < WAVE) {
+            bool ok;
+            const Grid g = wave_grid(cd, &ok);
+            if (threadIdx.x == 0) {
+                s_g = g;
+                s_ok = ok ? 1 : 0;
+                if (lb == 0) store_grid(grid_of(own.cd), st, g, ok);
+            }
+        }
+    } else if (threadIdx.x == 0) {
+        s_g = *grid_of(own.cd);
+    }
+    lds_barrier();
+    if (OWN_GRID && !s_ok) return;
     int key = 0, slot = 0, rank = 0;
     if (valid) {
-        key = cell_of(s_g, cd->r[a]);
+        key = cell_of(s_g, r);
         cd->cell_key[a] = key;
         slot = (int)(((unsigned)key * 2654435761u) >> 23) & (HSLOTS - 1);
         for (;;) {
@@ -1134,9 +1192,9 @@ __global__ __launch_bounds__(ATOM_BLOCK) void k_cellkey(Batch bt)
         }
         rank = atomicAdd(&s_hcnt[slot], 1);
     }
-    __syncthreads();
-    if (valid && rank == 0) s_hbase[slot] = atomicAdd(&cd->cell_count[key], s_hcnt[slot]);
-    __syncthreads();
+    lds_barrier();
+    if (valid && rank == 0) s_hbase[slot] = atomicAdd(&own.cd->cell_count[key], s_hcnt[slot]);
+    lds_barrier();
     // kept for the scatter in the sorted-index array (free until the rank
     // kernel fills it)
     if (valid) cd->s_idx[a] = s_hbase[slot] + rank;
@@ -1386,7 +1444,7 @@ __global__ __launch_bounds__(JOINT_BLOCK) void k_set_theta(Batch bt, const doubl
 // Chunk offsets of the chain's current grid, block-wide: s_off[b] = number of
 // atoms in the cells of the chunks before chunk b, for b = 0 .. nb (s_off[nb]:
 // all atoms).  The cell start of cell c is cell_local[c] + s_off[c / SCAN_CHUNK].
-__device__ void chunk_offsets(const ChainDev *cd, int nc, int *s_off, int *s_int)
+__device__ __forceinline__ void chunk_offsets(const ChainView *cd, int nc, int *s_off, int *s_int)
 {
     const int nb = (nc + SCAN_CHUNK - 1) / SCAN_CHUNK;
     const int tid = threadIdx.x, per = (nb + blockDim.x - 1) / blockDim.x;
@@ -1397,15 +1455,19 @@ __device__ void chunk_offsets(const ChainDev *cd, int nc, int *s_off, int *s_int
     }
     int total = 0;
     int run = block_excl_scan(loc, s_int, &total);
-    for (int k = 0; k < per; ++k) {
-        const int b = tid * per + k;
-        if (b < nb) {
-            s_off[b] = run;
-            run += cd->scan_part[b];
+    if (per == 1) {
+        if (tid < nb) s_off[tid] = run;
+    } else {
+        for (int k = 0; k < per; ++k) {
+            const int b = tid * per + k;
+            if (b < nb) {
+                s_off[b] = run;
+                run += cd->scan_part[b];
+            }
         }
     }
     if (tid == 0) s_off[nb] = total;
-    __syncthreads();
+    lds_barrier();
 }
 
 // Parameters of an atom as the cell-ordered array s_p holds them: (q, R,
@@ -1423,32 +1485,6 @@ __device__ __forceinline__ double4 sorted_param(const Chain *cd, double4 p)
     return p;
 }
 
-// Slot of atom a in the cell-ordered arrays: the counting-sort scatter placed
-// the atoms of a cell in the order of their count atomics; the stable slot is
-// the number of atoms of the cell with a smaller index, so everything
-// downstream is deterministic.  Gathers position and parameters into that
-// slot; w holds the atom index in its low and the atom's residue in its high
-// 32 bits (read as integers only).  Returns the rank.
-__device__ __forceinline__ int place_sorted(const ChainDev *cd, const int *ids, int a, int b, int e)
-{
-    // the cell's members four at a time, every load issued before any is
-    // compared (indices clamped into the cell, which holds a itself, e > b)
-    int rank = 0;
-    for (int s = b; s < e; s += 4) {
-        int v[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) v[k] = ids[min(s + k, e - 1)];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) rank += (s + k < e && v[k] < a) ? 1 : 0;
-    }
-    const int pos = b + rank;
-    const double4 r = cd->r[a];
-    cd->s_idx[pos] = a;
-    cd->s_r[pos] = make_double4(r.x, r.y, r.z, __longlong_as_double((long long)a | ((long long)(a / APR) << 32)));
-    cd->s_p[pos] = sorted_param(cd, cd->aparam[a]);
-    return rank;
-}
-
 // k_cellscan: one workgroup per chunk of SCAN_CHUNK cells of each chain's
 // capacity (chunks past the current grid return at once): the exclusive scan
 // of the counts inside the chunk, and the chunk's total.  Each thread takes
@@ -1461,26 +1497,24 @@ __global__ __launch_bounds__(CHAIN_THREADS) void k_cellscan(Batch bt)
 {
     static_assert(SCAN_CHUNK == 4 * CHAIN_THREADS, "four cells per thread");
     const Owner own = owner_of(bt, bt.scan_chain, bt.scan_off, blockIdx.x);
-    const ChainDev *cd = own.cd;
-    if (!running(stats_of(cd))) return;
-    const int b = blockIdx.x - own.first;
-    const int nc = grid_of(cd)->n_cells, c0 = b * SCAN_CHUNK;
-    if (c0 >= nc) return;
+    const ChainView view(own.cd), *cd = &view;
+    const int b = blockIdx.x - own.first, c0 = b * SCAN_CHUNK, i0 = 4 * (int)threadIdx.x;
+    int4 v = *(const gptr<const int4>)(cd->cell_count + min(c0 + i0, cd->cap_cells - 4));
+    loaded(v.x, v.y, v.z, v.w);
+    const int nc = grid_of(own.cd)->n_cells;
+    if (!running(stats_of(own.cd)) || c0 >= nc) return;
     __shared__ int s_int[CHAIN_THREADS / WAVE];
-    const int m = min(SCAN_CHUNK, nc - c0), i0 = 4 * (int)threadIdx.x;
-    int4 v = make_int4(0, 0, 0, 0);
-    if (i0 < m) {
-        v = *reinterpret_cast<const int4 *>(cd->cell_count + c0 + i0);
-        if (i0 + 1 >= m) v.y = 0;
-        if (i0 + 2 >= m) v.z = 0;
-        if (i0 + 3 >= m) v.w = 0;
-    }
+    const int m = min(SCAN_CHUNK, nc - c0);
+    if (i0 >= m) v.x = 0;
+    if (i0 + 1 >= m) v.y = 0;
+    if (i0 + 2 >= m) v.z = 0;
+    if (i0 + 3 >= m) v.w = 0;
     int total = 0;
     const int run = block_excl_scan(v.x + v.y + v.z + v.w, s_int, &total);
     const int4 o = make_int4(run, run + v.x, run + v.x + v.y, run + v.x + v.y + v.z);
-    int *__restrict__ local = cd->cell_local + c0 + i0;
+    const auto local = cd->cell_local + c0 + i0;
     if (i0 + 3 < m) {
-        *reinterpret_cast<int4 *>(local) = o;
+        *(gptr<int4>)local = o;
     } else if (i0 < m) {
         local[0] = o.x;
         if (i0 + 1 < m) local[1] = o.y;
@@ -1496,76 +1530,71 @@ __global__ __launch_bounds__(ATOM_BLOCK) void k_scatter(Batch bt)
     extern __shared__ int s_off[];
     __shared__ int s_int[ATOM_BLOCK / WAVE];
     const Owner own = owner_of(bt, bt.blk_chain, bt.blk_off, blockIdx.x);
-    const ChainDev *cd = own.cd;
-    if (!running(stats_of(cd))) return;
-    chunk_offsets(cd, grid_of(cd)->n_cells, s_off, s_int);
-    const int a = (blockIdx.x - own.first) * ATOM_BLOCK + threadIdx.x;
-    if (a >= cd->n_atoms) return;
-    const int key = cd->cell_key[a];
-    const int start = cd->cell_local[key] + s_off[key / SCAN_CHUNK];
-    cd->s_tmp[start + cd->s_idx[a]] = a;
+    const ChainView view(own.cd), *cd = &view;
+    const int a = (blockIdx.x - own.first) * ATOM_BLOCK + threadIdx.x, ac = min(a, cd->n_atoms - 1);
+    const int key = cd->cell_key[ac], arrival = cd->s_idx[ac];
+    loaded(key, arrival);
+    const int nc = grid_of(own.cd)->n_cells;
+    if (!running(stats_of(own.cd))) return;
+    const int local = cd->cell_local[key];
+    chunk_offsets(cd, nc, s_off, s_int);
+    if (a < cd->n_atoms) cd->s_tmp[local + s_off[key / SCAN_CHUNK] + arrival] = a;
 }
 
+// The counting-sort scatter placed the atoms of a cell in the order of their
+// count atomics; the stable slot is the number of atoms of the cell with a
+// smaller index, so everything downstream is deterministic.  Gathers position
+// and parameters into that slot; w holds the atom index in its low and the
+// atom's residue in its high 32 bits (read as integers only).
 __global__ __launch_bounds__(ATOM_BLOCK) void k_rank(Batch bt)
 {
     extern __shared__ int s_off[];
     __shared__ int s_int[ATOM_BLOCK / WAVE];
     const Owner own = owner_of(bt, bt.blk_chain, bt.blk_off, blockIdx.x);
-    const ChainDev *cd = own.cd;
-    if (!running(stats_of(cd))) return;
-    const int nc = grid_of(cd)->n_cells, nb = (nc + SCAN_CHUNK - 1) / SCAN_CHUNK;
-    chunk_offsets(cd, nc, s_off, s_int);
-    // the final cell starts (nc + 1 of them), a slice per workgroup of the chain
+    const ChainView view(own.cd), *cd = &view;
     const int lb = blockIdx.x - own.first, nblk = (cd->n_atoms + ATOM_BLOCK - 1) / ATOM_BLOCK;
+    const int a = lb * ATOM_BLOCK + threadIdx.x, ac = min(a, cd->n_atoms - 1);
+    const int key = cd->cell_key[ac];
+    const double4 r = cd->r[ac], ap = cd->aparam[ac];
+    loaded(key, r, ap, ap.w);
+    const int nc = grid_of(own.cd)->n_cells, nb = (nc + SCAN_CHUNK - 1) / SCAN_CHUNK;
+    if (!running(stats_of(own.cd))) return;
+    const int local = cd->cell_local[key], next = cd->cell_local[min(key + 1, nc - 1)];
+    chunk_offsets(cd, nc, s_off, s_int);
+    const int b = local + s_off[key / SCAN_CHUNK];
+    const int e = key + 1 < nc ? next + s_off[(key + 1) / SCAN_CHUNK] : s_off[nb];
+    // the cell's members four at a time, every load issued before any is
+    // compared (indices clamped into the cell, which holds a itself, e > b)
+    int pos = b;
+    for (int s = b; s < e; s += 4) {
+        int v[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) v[k] = cd->s_tmp[min(s + k, e - 1)];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) pos += (s + k < e && v[k] < a) ? 1 : 0;
+    }
+    if (a < cd->n_atoms) {
+        cd->s_idx[pos] = a;
+        cd->s_r[pos] = make_double4(r.x, r.y, r.z, __longlong_as_double((long long)a | ((long long)(a / APR) << 32)));
+        cd->s_p[pos] = sorted_param(cd, ap);
+        // the first atom of each cell returns its count to zero for the next iteration
+        if (pos == b) cd->cell_count[key] = 0;
+    }
+    // the final cell starts (nc + 1 of them), a slice per workgroup of the
+    // chain: four cells per thread per step, the loads issued before the stores
+    // (indices clamped into the grid, which has at least one cell)
     const int per = (nc + 1 + nblk - 1) / nblk, i1 = min(nc + 1, (lb + 1) * per);
-    {
-        // four cells per thread per step, the loads issued before the stores
-        // (indices clamped into the grid, which has at least one cell)
-        const int *__restrict__ loc = cd->cell_local;
-        int *__restrict__ start = cd->cell_start;
-        for (int i = lb * per + (int)threadIdx.x; i < i1; i += 4 * ATOM_BLOCK) {
-            int v[4];
+    for (int i = lb * per + (int)threadIdx.x; i < i1; i += 4 * ATOM_BLOCK) {
+        int v[4];
 #pragma unroll
-            for (int k = 0; k < 4; ++k) v[k] = loc[min(i + k * ATOM_BLOCK, nc - 1)];
+        for (int k = 0; k < 4; ++k) v[k] = cd->cell_local[min(i + k * ATOM_BLOCK, nc - 1)];
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const int j = i + k * ATOM_BLOCK;
-                if (j < i1) start[j] = j < nc ? v[k] + s_off[j / SCAN_CHUNK] : s_off[nb];
-            }
+        for (int k = 0; k < 4; ++k) {
+            const int j = i + k * ATOM_BLOCK;
+            if (j < i1) cd->cell_start[j] = j < nc ? v[k] + s_off[j / SCAN_CHUNK] : s_off[nb];
         }
     }
-    const int a = lb * ATOM_BLOCK + threadIdx.x;
-    if (a >= cd->n_atoms) return;
-    const int key = cd->cell_key[a];
-    const int b = cd->cell_local[key] + s_off[key / SCAN_CHUNK];
-    const int e = key + 1 < nc ? cd->cell_local[key + 1] + s_off[(key + 1) / SCAN_CHUNK] : s_off[nb];
-    // the first atom of each cell returns its count to zero for the next iteration
-    if (place_sorted(cd, cd->s_tmp, a, b, e) == 0) cd->cell_count[key] = 0;
 }
-
-// What k_chain uses of a chain's descriptor, read once at its start while
-// nothing is stored yet: into scalar registers, where a later look would be a
-// vector load (its stores might change the descriptor, for all the compiler
-// knows) with a few hundred cycles of latency each.
-struct ChainView {
-    int n_atoms, n_joints, n_chi, n_bb_blocks, cap_cells, precision, step_rule;
-    double cutoff, kappa, max_step, delta_r, cell_min, roff_max;
-    gptr<double> theta, dtheta, tau;
-    gptr<uint8_t> mask;
-    gptr<double4> joint0, jcur, r0, r, aparam, s_r, s_p, f_pair, e_atom;
-    gptr<int32_t> cell_start, s_idx;
-    gptr<long long> f_cav;
-    __device__ __forceinline__ explicit ChainView(const ChainDev *d)
-        : n_atoms(d->n_atoms), n_joints(d->n_joints), n_chi(d->n_chi), n_bb_blocks(d->n_bb_blocks),
-          cap_cells(d->cap_cells), precision(d->precision), step_rule(d->step_rule), cutoff(d->cutoff),
-          kappa(d->kappa), max_step(d->max_step), delta_r(d->delta_r), cell_min(d->cell_min), roff_max(d->roff_max),
-          theta(glob(d->theta)), dtheta(glob(d->dtheta)), tau(glob(d->tau)), mask(glob(d->mask)),
-          joint0(glob(d->joint0)), jcur(glob(d->jcur)), r0(glob(d->r0)), r(glob(d->r)), aparam(glob(d->aparam)),
-          s_r(glob(d->s_r)), s_p(glob(d->s_p)), f_pair(glob(d->f_pair)), e_atom(glob(d->e_atom)),
-          cell_start(glob(d->cell_start)), s_idx(glob(d->s_idx)), f_cav(glob(d->f_cav))
-    {
-    }
-};
 
 // ---------------------------------------------------------------------------
 // k_chain: everything of an iteration but the force kernel, one workgroup per
@@ -3053,44 +3082,51 @@ __global__ __launch_bounds__(WAVE, sizeof(Real) == 4 ? 6 : 4) void k_force(Batch
 __global__ __launch_bounds__(ATOM_BLOCK) void k_wrench(Batch bt)
 {
     const Owner own = owner_of(bt, bt.blk_chain, bt.blk_off, blockIdx.x);
-    ChainDev *cd = own.cd;
-    ChainStats *st = stats_of(cd);
+    ChainStats *st = stats_of(own.cd);
+    const ChainView view(own.cd), *cd = &view;
     const int lb = blockIdx.x - own.first;
+    __shared__ double s_w[ATOM_BLOCK / WAVE][WPART];
+    constexpr int NW = ATOM_BLOCK / WAVE;
+    const int a = lb * ATOM_BLOCK + threadIdx.x, ac = min(a, cd->n_atoms - 1);
+    const int lane = threadIdx.x & (WAVE - 1), w = threadIdx.x / WAVE;
+    const int res = a / APR, slot = a - res * APR, j = 2 * res + (slot == 8 ? 1 : 0), jc = min(j, cd->n_joints - 1);
+    const AtomForce in = load_force(cd, ac);
+    const double4 u = cd->jcur[2 * jc], p = cd->jcur[2 * jc + 1];
+    loaded(in.f, in.r, in.e, in.c[0], in.c[1], in.c[2], u, p);
+    const bool go = running(st);
     if (lb == 0 && threadIdx.x == 0) {
         // end of the iteration: the chain stays active iff it ran, and its
         // forces await the post phase
-        const int go = running(st);
         st->active = go;
         if (go) st->pending_post = 1;
     }
-    if (!running(st)) return;
-    __shared__ double s_w[ATOM_BLOCK / WAVE][WPART];
-    const int a = lb * ATOM_BLOCK + threadIdx.x;
-    const int lane = threadIdx.x & (WAVE - 1), w = threadIdx.x / WAVE, nw = ATOM_BLOCK / WAVE;
+    if (!go) return;
     double4 r;
     double S[WPART];
-    wrench_of(load_force(cd, min(a, cd->n_atoms - 1)), a < cd->n_atoms, r, S);
+    wrench_of(in, a < cd->n_atoms, r, S);
     wave_suffix(S);
     if (lane == 0)
-        for (int k = 0; k < WPART; ++k) s_w[w][k] = S[k];
-    __syncthreads();
 #pragma unroll
-    for (int k = 0; k < 6; ++k) {
-        double t = 0.0;
-        for (int i = w + 1; i < nw; ++i) t += s_w[i][k];
-        S[k] += t;
-    }
-    if (a < cd->n_atoms) {
-        const int res = a / APR, slot = a - res * APR;
-        if (slot == 4 && cd->n_chi) cd->tau[cd->n_joints + res] = chi_torque(cd, a, r);
-        if (slot == 2 || slot == 8) {
-            const int j = 2 * res + (slot == 8 ? 1 : 0);
-            cd->tau[j] = joint_torque(cd, j, S);
+        for (int k = 0; k < WPART; ++k) s_w[w][k] = S[k];
+    lds_barrier();
+    double later[6] = {0, 0, 0, 0, 0, 0};  // the waves after this one
+#pragma unroll
+    for (int i = 1; i < NW; ++i)
+#pragma unroll
+        for (int k = 0; k < 6; ++k) {
+            const double t = s_w[i][k];
+            later[k] = i > w ? later[k] + t : later[k];
         }
+#pragma unroll
+    for (int k = 0; k < 6; ++k) S[k] += later[k];
+    if (a < cd->n_atoms) {
+        if (slot == 4 && cd->n_chi) cd->tau[cd->n_joints + res] = chi_torque(cd, a, r);
+        if (slot == 2 || slot == 8) cd->tau[j] = axis_torque(u, p, S);
     }
     if (threadIdx.x < WPART) {
         double t = 0.0;
-        for (int i = 0; i < nw; ++i) t += s_w[i][threadIdx.x];
+#pragma unroll
+        for (int i = 0; i < NW; ++i) t += s_w[i][threadIdx.x];
         cd->wrench_part[WPART * lb + threadIdx.x] = t;
     }
 }
