@@ -353,9 +353,10 @@ struct TimedIter {
 // side and win at every length they can hold: 128 chains of 6,400 atoms 2,913
 // against 2,954 us; 32 of them lose, 855 against 785.
 constexpr int CHAIN_ATOMS_ALWAYS = 1536, CHAIN_MANY = 128;
-void set_form(Batch &b, int max_atoms)
+void set_form(Batch &b, int max_atoms, int terms)
 {
     b.max_atoms = max_atoms;
+    b.terms = terms;
     b.fused = max_atoms <= CHAIN_ATOMS_ALWAYS || (b.n_chains >= CHAIN_MANY && max_atoms <= CHAIN_ATOMS) ? 1 : 0;
 }
 
@@ -535,7 +536,7 @@ kcm_status ensure_table(kcm_chain *const *chains, int n_chains, hipStream_t stre
         int32_t *jblk = reinterpret_cast<int32_t *>(host.data() + jblk_pos);
         int32_t *sblk = reinterpret_cast<int32_t *>(host.data() + scan_pos);
         long long total = 0, blocks = 0, jblocks = 0, sblocks = 0;
-        int max_chunks = 1, max_atoms = 0;
+        int max_chunks = 1, max_atoms = 0, terms = 0;
         for (int i = 0; i < n_chains; ++i) {
             tab[i] = chains[i]->d_desc;
             off[i] = (int32_t)total;
@@ -549,6 +550,7 @@ kcm_status ensure_table(kcm_chain *const *chains, int n_chains, hipStream_t stre
             sblocks += chunks;
             max_chunks = std::max(max_chunks, chunks);
             max_atoms = std::max(max_atoms, chains[i]->n);
+            terms |= chains[i]->h.terms;
         }
         if (total > std::numeric_limits<int32_t>::max() || sblocks > std::numeric_limits<int32_t>::max())
             return fail(KCM_E_INVAL, "too many atoms in one call");
@@ -587,7 +589,7 @@ kcm_status ensure_table(kcm_chain *const *chains, int n_chains, hipStream_t stre
         t->batch.total_jblocks = (int)jblocks;
         t->batch.total_scan_blocks = (int)sblocks;
         t->batch.max_scan_chunks = max_chunks;
-        set_form(t->batch, max_atoms);
+        set_form(t->batch, max_atoms, terms);
         t->chains.assign(chains, chains + n_chains);
         if (t->graph) {
             HIP_TRY(hipGraphExecDestroy(t->graph));
@@ -1179,7 +1181,7 @@ kcm_status noalloc_table(NoallocDevice &d, kcm_chain *const *chains, int n_chain
     int32_t *jblk = reinterpret_cast<int32_t *>(g_noalloc_table + kNaTab + 2 * kNaOff);
     int32_t *sblk = reinterpret_cast<int32_t *>(g_noalloc_table + kNaTab + 3 * kNaOff);
     long long total = 0, blocks = 0, jblocks = 0, sblocks = 0;
-    int max_chunks = 1, max_atoms = 0;
+    int max_chunks = 1, max_atoms = 0, terms = 0;
     for (int i = 0; i < n_chains; ++i) {
         tab[i] = chains[i]->d_desc;
         off[i] = (int32_t)total;
@@ -1193,6 +1195,7 @@ kcm_status noalloc_table(NoallocDevice &d, kcm_chain *const *chains, int n_chain
         sblocks += chunks;
         max_chunks = std::max(max_chunks, chunks);
         max_atoms = std::max(max_atoms, chains[i]->n);
+        terms |= chains[i]->h.terms;
     }
     if (total > std::numeric_limits<int32_t>::max() || sblocks > std::numeric_limits<int32_t>::max())
         return fail(KCM_E_INVAL, "too many atoms in one call");
@@ -1216,7 +1219,7 @@ kcm_status noalloc_table(NoallocDevice &d, kcm_chain *const *chains, int n_chain
     b.total_jblocks = (int)jblocks;
     b.total_scan_blocks = (int)sblocks;
     b.max_scan_chunks = max_chunks;
-    set_form(b, max_atoms);
+    set_form(b, max_atoms, terms);
     for (int i = 0; i < n_chains; ++i) d.chains[i] = chains[i];
     d.n_chains = n_chains;
     d.used = true;

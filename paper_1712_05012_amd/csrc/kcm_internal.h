@@ -146,6 +146,7 @@ struct Batch {
     int total_jblocks;
     int total_scan_blocks;
     int max_atoms;            // atoms of the largest chain
+    int terms;                // energy terms that any of the chains has (KCM_TERM_*)
     int fused;                // 1: the iteration runs as k_chain and the force kernel
     int max_scan_chunks;      // most chunks of one chain (sizes the chunk-offset table in LDS)
 };

@@ -2498,17 +2498,23 @@ __device__ __noinline__ ChunkedSasa sasa_chunked(CDev cd, const ChunkArgs c, Nbr
 // hides the latency of the candidate loads and LDS reads better than four
 // waves with room to spare (3.06 against 3.39 ms on the 256-chain batch when
 // measured, with a longer list); seven spill in the hot loops.  The FP64 form:
-// four (127 registers; its 9,600 bytes allow 16 waves per CU).
-template <typename Real, int CPT, int SAT_CHECK, XcdOrder ORDER>
-__global__ __launch_bounds__(WAVE, sizeof(Real) == 4 ? 6 : 4) void k_force(Batch bt)
+// four (127 registers; its 9,600 bytes allow 16 waves per CU).  CAV false: no
+// chain of the batch has the solvation term.  Without its list and tests
+// eight waves fit a SIMD in either form, and the candidates go by without the
+// neighbour test (FP64, 256 chains of 100 to 200 atoms: 27.4 us, 39.0 with the
+// general kernel; the results are the same bit for bit).
+constexpr int force_waves(bool fp32, bool cav) { return cav ? (fp32 ? 6 : 4) : 8; }
+template <typename Real, int CPT, int SAT_CHECK, XcdOrder ORDER, bool CAV>
+__global__ __launch_bounds__(WAVE, force_waves(sizeof(Real) == 4, CAV)) void k_force(Batch bt)
 {
     static_assert(SAT_CHECK * (SAT_CHECK - 1) / 2 < 32 && 32 + SAT_CHECK <= 64, "block code of step 1");
     constexpr bool MIXED = sizeof(Real) == 4;
-    __shared__ NbrEntry<Real> s_nbr[MAX_NBR];
-    __shared__ int s_nbr_a[MAX_NBR];
-    __shared__ __align__(16) unsigned s_word[MAX_NBR + 2 * WAVE];
-    unsigned *const s_ev = s_word;                 // net events of each neighbour in this pass
-    unsigned *const s_pair = s_word + MAX_NBR;     // (sample, neighbour) pairs that await their displaced tests
+    constexpr int LIST = CAV ? MAX_NBR : 1;  // entries of the neighbour list
+    __shared__ NbrEntry<Real> s_nbr[LIST];
+    __shared__ int s_nbr_a[LIST];
+    __shared__ __align__(16) unsigned s_word[CAV ? MAX_NBR + 2 * WAVE : WAVE + 4 * (3 * APR + 1) * sizeof(Real) / 4];
+    unsigned *const s_ev = s_word;              // net events of each neighbour in this pass
+    unsigned *const s_pair = s_word + LIST;     // (sample, neighbour) pairs that await their displaced tests
 
     int atom = blockIdx.x;
     if (ORDER != CELL_ORDER) {
@@ -2606,7 +2612,7 @@ __global__ __launch_bounds__(WAVE, sizeof(Real) == 4 ? 6 : 4) void k_force(Batch
     const int rbase = beg - off;  // candidate number k of row t is sorted atom rbase_t + k
 
     const int terms = cd->terms;
-    const bool do_elec = terms & 1, do_vdw = terms & 2, do_cav = terms & 4;
+    const bool do_elec = terms & 1, do_vdw = terms & 2, do_cav = CAV && (terms & 4);
     const bool do_pair = do_elec || do_vdw;
     const double cut2 = cd->cutoff * cd->cutoff;
     const double roff_i = pi.roff;
@@ -2699,6 +2705,7 @@ __global__ __launch_bounds__(WAVE, sizeof(Real) == 4 ? 6 : 4) void k_force(Batch
             ee += (double)eel;
             evw += (double)elj;
         }
+        if (!CAV) return;
         bool in_cav = false, front = false;
         double c0 = 0.0;
         if (do_cav) {
@@ -3295,15 +3302,21 @@ hipError_t launch_wrench(const Batch &b, hipStream_t s)
     return hipGetLastError();
 }
 
-template <int V>
+template <int V, bool CAV>
 void launch_force_shape(const Batch &b, int precision, hipStream_t s)
 {
     constexpr int C = FORCE_SHAPES[V].cpt, S = FORCE_SHAPES[V].satb;
     constexpr XcdOrder X = FORCE_SHAPES[V].order;
     if (precision == 1)
-        hipLaunchKernelGGL((k_force<float, C, S, X>), dim3(b.total_atoms), dim3(WAVE), 0, s, b);
+        hipLaunchKernelGGL((k_force<float, C, S, X, CAV>), dim3(b.total_atoms), dim3(WAVE), 0, s, b);
     else
-        hipLaunchKernelGGL((k_force<double, C, S, X>), dim3(b.total_atoms), dim3(WAVE), 0, s, b);
+        hipLaunchKernelGGL((k_force<double, C, S, X, CAV>), dim3(b.total_atoms), dim3(WAVE), 0, s, b);
+}
+template <int V>
+void launch_force_shape(const Batch &b, int precision, hipStream_t s)
+{
+    if (b.terms & 4) launch_force_shape<V, true>(b, precision, s);
+    else launch_force_shape<V, false>(b, precision, s);
 }
 
 hipError_t launch_force(const Batch &b, int precision, int shape, hipStream_t s)
