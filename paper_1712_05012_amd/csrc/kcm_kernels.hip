@@ -112,6 +112,11 @@ __device__ __forceinline__ double from_above(double x, int d)
 // the lanes where p holds (from the compare's own mask, where the library's
 // ballot goes through a 0/1 register and a second compare)
 __device__ __forceinline__ unsigned long long ballot(bool p) { return __builtin_amdgcn_ballot_w64(p); }
+// set bits of m in the lanes below this one (the hardware's masked bit count)
+__device__ __forceinline__ int count_below(unsigned long long m)
+{
+    return (int)__builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
+}
 // op over the wave in every lane, as the butterfly over lane distances 32, 16,
 // ..., 1 takes it: below 16 the values repeat with the last distance inside a
 // row, so a rotation by half of it brings the partner's
@@ -730,6 +735,23 @@ __device__ __forceinline__ void wave_suffix(double (&S)[WPART])
         }
     }
     wave_tree_sum4(S + 6);
+}
+
+// Adds to the suffix S of wave w the wrench of the W waves of its block after it;
+// rows: the sums of the block's waves.  Lane k adds up component k, and all
+// lanes take the six from there (33 instructions in place of 100, and three LDS
+// reads in place of nine).
+template <int W, typename Rows> __device__ __forceinline__ void add_later_waves(double (&S)[WPART], Rows rows, int w)
+{
+    const int lane = threadIdx.x & (WAVE - 1);
+    double later = 0.0;
+#pragma unroll
+    for (int i = 1; i < W; ++i) {
+        const double t = rows[i][min(lane, 5)];
+        later = i > w ? later + t : later;
+    }
+#pragma unroll
+    for (int k = 0; k < 6; ++k) S[k] += lane_value(later, k);
 }
 
 // Side-chain torque of the residue whose CB is atom a at r: the whole torque,
@@ -1613,21 +1635,24 @@ __global__ __launch_bounds__(ATOM_BLOCK) void k_rank(Batch bt)
 // The conditions that end the kernel early are the same for all threads, so
 // every barrier is reached by all of them.
 // What bounds it is latency: one wave per SIMD and a chain of dependent steps,
-// about 26,500 cycles for a chain of 150 atoms, of which the loads at the start
-// take 3,000, the wrenches 5,500, the transform scan 3,800, the sorted arrays
-// 2,600 and the grid 2,400.  11 us in place of 47 us for the eight kernels it
-// replaces (43 us with them in one graph).  What it took before, in that order:
-// 39,200 cycles with LDS permutes for every lane move; 36,200 where every
-// barrier waited for the stores before it, every look at the descriptor was a
-// load and one thread sized the grid (13.9 us).  768-thread form, 256 chains of
-// 500 to 6,000 atoms: 109 us, 123 before.  Workgroups of 768 threads at most:
-// 1,024 would leave 128 registers.
+// about 24,000 cycles for a chain of 150 atoms, of which the loads at the start
+// take 3,200, the wrenches and torques 6,000, the step 2,300, the transform
+// scan 4,000, placement and axes 2,800, the grid 2,400 and the cell list 3,000.
+// 10.4 us in place of 47 us for the eight kernels it replaces (43 us with them
+// in one graph).  What it took before: 39,200 cycles with LDS permutes for every
+// lane move; 36,200 where every barrier waited for the stores before it, every
+// look at the descriptor was a load and one thread sized the grid (13.9 us);
+// 26,500 where every atom compared itself with all of its cell (10.9 us).
+// 768-thread form, 256 chains of 500 to 6,000 atoms: 109 us, 123 before the
+// barriers changed.  Workgroups of 768 threads at most: 1,024 would leave 128
+// registers.
 template <int NT, bool ONE>
 __global__ __launch_bounds__(NT) void k_chain(Batch bt, int mode)
 {
     static_assert(JOINT_BLOCK == ATOM_BLOCK && NT % ATOM_BLOCK == 0, "blocks of one size");
     constexpr int NW = NT / WAVE, WPB = ATOM_BLOCK / WAVE;  // waves, waves per block
     constexpr bool KEEP_AXIS = ONE && NT <= 512;            // registers left for ua_1, pa_1
+    constexpr bool MATCH = ONE && NW <= 4;                  // a byte per wave in a cell's word
     extern __shared__ __align__(16) unsigned char s_dyn[];
     __shared__ double s_red[NW][12];
     __shared__ double s_blk[CHAIN_JBLOCKS][12], s_carry[CHAIN_JBLOCKS][12];
@@ -1676,7 +1701,7 @@ __global__ __launch_bounds__(NT) void k_chain(Batch bt, int mode)
     const GridRule rule = grid_rule(cd);
     unsigned *s_cell = reinterpret_cast<unsigned *>(s_dyn + (ONE ? sizeof(double) * 12 * (J + 1) : 0));
     if (ONE) {
-        for (int i = tid; i < rule.cap_cells / 8; i += NT) reinterpret_cast<uint4 *>(s_cell)[i] = make_uint4(0, 0, 0, 0);
+        for (int i = tid; i < rule.cap_cells / (MATCH ? 4 : 8); i += NT) reinterpret_cast<uint4 *>(s_cell)[i] = make_uint4(0, 0, 0, 0);
         // here all the loads are done: a wait for one behind the stores below
         // would wait for those too
         auto done = [](double4 &v) { asm volatile("" : "+v"(v.x), "+v"(v.y), "+v"(v.z)); };
@@ -1714,16 +1739,7 @@ __global__ __launch_bounds__(NT) void k_chain(Batch bt, int mode)
 #pragma unroll
                 for (int k = 0; k < WPART; ++k) s_red[w][k] = S[k];
             lds_barrier();
-            double later[6] = {0, 0, 0, 0, 0, 0};  // the waves of the block after this one
-#pragma unroll
-            for (int i = 1; i < WPB; ++i)
-#pragma unroll
-                for (int k = 0; k < 6; ++k) {
-                    const double t = s_red[w0 + i][k];
-                    later[k] = w0 + i > w ? later[k] + t : later[k];
-                }
-#pragma unroll
-            for (int k = 0; k < 6; ++k) S[k] += later[k];
+            add_later_waves<WPB>(S, s_red + w0, w - w0);
             if (a < n) {
                 const int res = a / APR, slot = a - res * APR;
                 if (slot == 4 && n_chi) s_tau[J + res] = chi_torque(cd, a, r);
@@ -1963,59 +1979,105 @@ __global__ __launch_bounds__(NT) void k_chain(Batch bt, int mode)
         st->need_grid = 0;
     }
 
-    // cell list: counts and starts two to a word
-    const int nc = g.n_cells, nword = (nc + 1) / 2;
-    unsigned short *s_ids = reinterpret_cast<unsigned short *>(s_cell + cd->cap_cells / 2);
-    unsigned short *s_key = s_ids + n, *s_arr = s_key + n;  // unless each thread keeps its one atom's
-    if (!ONE) {
-        for (int i = tid; i < nword; i += NT) s_cell[i] = 0;
-        lds_barrier();
-    }
-    int key1 = 0, arr1 = 0;
-    for (int a = tid; a < n; a += NT) {
-        const int key = cell_of(g, ONE ? r1 : cd->r[a]), sh = 16 * (key & 1);
-        const int arr = (int)((atomicAdd(&s_cell[key >> 1], 1u << sh) >> sh) & 0xffffu);
-        if (ONE) {
-            key1 = key;
-            arr1 = arr;
-        } else {
-            s_key[a] = (unsigned short)key;
-            s_arr[a] = (unsigned short)arr;
+    if (MATCH) {
+        // Cell list of at most 256 atoms, one to a thread: the lanes of a wave
+        // that share a cell by ballots over the bits of the key, one byte of
+        // the cell's word for the count of each wave.  A slot is then the
+        // cell's start, the counts of the waves before and the lanes of the
+        // cell below this one, which is the stable order at once, without the
+        // scatter and a look at every member of the cell (3,000 cycles less).
+        const int nc = g.n_cells;
+        unsigned short *s_start = reinterpret_cast<unsigned short *>(s_cell + cd->cap_cells);
+        const bool valid = tid < n;
+        const int key = valid ? cell_of(g, r1) : 0;
+        unsigned long long same = ballot(valid);
+        for (int bit = 1; bit < nc; bit <<= 1) {
+            const unsigned long long ones = ballot(key & bit);
+            same &= key & bit ? ones : ~ones;
         }
-    }
-    lds_barrier();
-    {
-        const int per = (nword + NT - 1) / NT, i0 = min(tid * per, nword), i1 = min(i0 + per, nword);
+        const int rank = count_below(same);
+        if (valid && rank == 0) reinterpret_cast<unsigned char *>(s_cell + key)[w] = (unsigned char)__popcll(same);
+        lds_barrier();
+        const int per = (nc + NT - 1) / NT, i0 = min(tid * per, nc), i1 = min(i0 + per, nc);
         int sum = 0;
-        for (int i = i0; i < i1; ++i) sum += (int)(s_cell[i] & 0xffffu) + (int)(s_cell[i] >> 16);
+#pragma unroll 4
+        for (int i = i0; i < i1; ++i) sum = (int)__builtin_amdgcn_sad_u8(s_cell[i], 0u, (unsigned)sum);
         const int x = wave_scan_i(sum);
         if (lane == WAVE - 1) s_scan[w] = x;
         lds_barrier();
         int run = x - sum;
 #pragma unroll
         for (int i = 0; i < NW; ++i) run += i < w ? s_scan[i] : 0;
+#pragma unroll 4
         for (int i = i0; i < i1; ++i) {
-            const unsigned v = s_cell[i];
-            s_cell[i] = (unsigned)run | ((unsigned)(run + (int)(v & 0xffffu)) << 16);
-            run += (int)(v & 0xffffu) + (int)(v >> 16);
+            s_start[i] = (unsigned short)run;
+            cd->cell_start[i] = run;
+            run = (int)__builtin_amdgcn_sad_u8(s_cell[i], 0u, (unsigned)run);
         }
-    }
-    lds_barrier();
-    auto start_of = [&](int c) -> int { return c < nc ? (int)((s_cell[c >> 1] >> (16 * (c & 1))) & 0xffffu) : n; };
-    for (int c = tid; c <= nc; c += NT) cd->cell_start[c] = start_of(c);
-    for (int a = tid; a < n; a += NT) s_ids[start_of(ONE ? key1 : s_key[a]) + (ONE ? arr1 : s_arr[a])] = (unsigned short)a;
-    lds_barrier();
-    for (int a = tid; a < n; a += NT) {
-        // the stable slot: the members of the cell with a smaller index before it
-        const int key = ONE ? key1 : s_key[a], b = start_of(key), e = start_of(key + 1);
-        int pos = b;
-        for (int s = b; s < e; s += 4)
+        if (lead) cd->cell_start[nc] = n;
+        lds_barrier();
+        if (valid) {
+            const unsigned before = s_cell[key] & ((1u << (8 * w)) - 1u);
+            const int pos = s_start[key] + (int)__builtin_amdgcn_sad_u8(before, 0u, (unsigned)rank);
+            cd->s_idx[pos] = tid;
+            cd->s_r[pos] = make_double4(r1.x, r1.y, r1.z, __longlong_as_double((long long)tid | ((long long)(tid / APR) << 32)));
+            cd->s_p[pos] = sorted_param(cd, ap_1);
+        }
+    } else {
+        // cell list: counts and starts two to a word
+        const int nc = g.n_cells, nword = (nc + 1) / 2;
+        unsigned short *s_ids = reinterpret_cast<unsigned short *>(s_cell + cd->cap_cells / 2);
+        unsigned short *s_key = s_ids + n, *s_arr = s_key + n;  // unless each thread keeps its one atom's
+        if (!ONE) {
+            for (int i = tid; i < nword; i += NT) s_cell[i] = 0;
+            lds_barrier();
+        }
+        int key1 = 0, arr1 = 0;
+        for (int a = tid; a < n; a += NT) {
+            const int key = cell_of(g, ONE ? r1 : cd->r[a]), sh = 16 * (key & 1);
+            const int arr = (int)((atomicAdd(&s_cell[key >> 1], 1u << sh) >> sh) & 0xffffu);
+            if (ONE) {
+                key1 = key;
+                arr1 = arr;
+            } else {
+                s_key[a] = (unsigned short)key;
+                s_arr[a] = (unsigned short)arr;
+            }
+        }
+        lds_barrier();
+        {
+            const int per = (nword + NT - 1) / NT, i0 = min(tid * per, nword), i1 = min(i0 + per, nword);
+            int sum = 0;
+            for (int i = i0; i < i1; ++i) sum += (int)(s_cell[i] & 0xffffu) + (int)(s_cell[i] >> 16);
+            const int x = wave_scan_i(sum);
+            if (lane == WAVE - 1) s_scan[w] = x;
+            lds_barrier();
+            int run = x - sum;
 #pragma unroll
-            for (int k = 0; k < 4; ++k) pos += (s + k < e && s_ids[min(s + k, n - 1)] < a) ? 1 : 0;
-        const double4 r = ONE ? r1 : cd->r[a];
-        cd->s_idx[pos] = a;
-        cd->s_r[pos] = make_double4(r.x, r.y, r.z, __longlong_as_double((long long)a | ((long long)(a / APR) << 32)));
-        cd->s_p[pos] = sorted_param(cd, ONE ? ap_1 : cd->aparam[a]);
+            for (int i = 0; i < NW; ++i) run += i < w ? s_scan[i] : 0;
+            for (int i = i0; i < i1; ++i) {
+                const unsigned v = s_cell[i];
+                s_cell[i] = (unsigned)run | ((unsigned)(run + (int)(v & 0xffffu)) << 16);
+                run += (int)(v & 0xffffu) + (int)(v >> 16);
+            }
+        }
+        lds_barrier();
+        auto start_of = [&](int c) -> int { return c < nc ? (int)((s_cell[c >> 1] >> (16 * (c & 1))) & 0xffffu) : n; };
+        for (int c = tid; c <= nc; c += NT) cd->cell_start[c] = start_of(c);
+        for (int a = tid; a < n; a += NT) s_ids[start_of(ONE ? key1 : s_key[a]) + (ONE ? arr1 : s_arr[a])] = (unsigned short)a;
+        lds_barrier();
+        for (int a = tid; a < n; a += NT) {
+            // the stable slot: the members of the cell with a smaller index before it
+            const int key = ONE ? key1 : s_key[a], b = start_of(key), e = start_of(key + 1);
+            int pos = b;
+            for (int s = b; s < e; s += 4)
+#pragma unroll
+                for (int k = 0; k < 4; ++k) pos += (s + k < e && s_ids[min(s + k, n - 1)] < a) ? 1 : 0;
+            const double4 r = ONE ? r1 : cd->r[a];
+            cd->s_idx[pos] = a;
+            cd->s_r[pos] = make_double4(r.x, r.y, r.z, __longlong_as_double((long long)a | ((long long)(a / APR) << 32)));
+            cd->s_p[pos] = sorted_param(cd, ONE ? ap_1 : cd->aparam[a]);
+        }
     }
     if (lead) {
         // the force kernel follows: its forces await the next post phase
@@ -2067,11 +2129,6 @@ __device__ __forceinline__ double dist2(double dx, double dy, double dz)
 {
 #pragma clang fp contract(off)
     return fma(dz, dz, fma(dy, dy, dx * dx));
-}
-// set bits of m in the lanes below this one (the hardware's masked bit count)
-__device__ __forceinline__ int count_below(unsigned long long m)
-{
-    return (int)__builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
 }
 __device__ __forceinline__ double cap_c0(double roff_i, double d2, double rj, double inv_2roff)
 {
@@ -3116,16 +3173,7 @@ __global__ __launch_bounds__(ATOM_BLOCK) void k_wrench(Batch bt)
 #pragma unroll
         for (int k = 0; k < WPART; ++k) s_w[w][k] = S[k];
     lds_barrier();
-    double later[6] = {0, 0, 0, 0, 0, 0};  // the waves after this one
-#pragma unroll
-    for (int i = 1; i < NW; ++i)
-#pragma unroll
-        for (int k = 0; k < 6; ++k) {
-            const double t = s_w[i][k];
-            later[k] = i > w ? later[k] + t : later[k];
-        }
-#pragma unroll
-    for (int k = 0; k < 6; ++k) S[k] += later[k];
+    add_later_waves<NW>(S, s_w, w);
     if (a < cd->n_atoms) {
         if (slot == 4 && cd->n_chi) cd->tau[cd->n_joints + res] = chi_torque(cd, a, r);
         if (slot == 2 || slot == 8) cd->tau[j] = axis_torque(u, p, S);
@@ -3154,7 +3202,8 @@ static hipError_t launch_chain_form(const Batch &b, int mode, hipStream_t s)
     // the link transforms and the cell list, which starts as zeros where each
     // has its place (ONE) and follows in the same place where not
     const int n = b.max_atoms, links = 2 * (n / APR) + 1;
-    const size_t xf = sizeof(double) * 12 * links, cells = sizeof(uint16_t) * (size_t)(cell_capacity(n) + (ONE ? 1 : 3) * n);
+    const size_t xf = sizeof(double) * 12 * links,
+                 cells = sizeof(uint16_t) * (size_t)(NT == 256 ? 3 * cell_capacity(n) : cell_capacity(n) + (ONE ? 1 : 3) * n);
     const size_t lds = ONE ? xf + cells : std::max(xf, cells);
     if (lds > 65536) {
         const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_chain<NT, ONE>),
