@@ -1650,28 +1650,34 @@ __global__ __launch_bounds__(ATOM_BLOCK) void k_rank(Batch bt)
 // The conditions that end the kernel early are the same for all threads, so
 // every barrier is reached by all of them.
 // What bounds it is latency: one wave per SIMD and a chain of dependent steps,
-// about 24,000 cycles for a chain of 150 atoms, of which the loads at the start
-// take 3,200, the wrenches and torques 6,000, the step 2,300, the transform
-// scan 4,000, placement and axes 2,800, the grid 2,400 and the cell list 3,000.
-// 10.4 us in place of 47 us for the eight kernels it replaces (43 us with them
-// in one graph).  What it took before: 39,200 cycles with LDS permutes for every
-// lane move; 36,200 where every barrier waited for the stores before it, every
-// look at the descriptor was a load and one thread sized the grid (13.9 us);
-// 26,500 where every atom compared itself with all of its cell (10.9 us).
-// 768-thread form, 256 chains of 500 to 6,000 atoms: 109 us, 123 before the
-// barriers changed.  Workgroups of 768 threads at most: 1,024 would leave 128
-// registers.
+// about 21,000 cycles for a chain of 150 atoms, of which the loads at the start
+// take 2,700, the wrenches and torques 5,200, the step 2,000, the angles and the
+// transform scan 4,700, the placement 1,400, the grid 2,400 and the cell list
+// 2,800.  8.8 us in place of 47 us for the eight kernels it replaces (43 us with
+// them in one graph).  What it took before: 39,200 cycles with LDS permutes for
+// every lane move; 36,200 where every barrier waited for the stores before it,
+// every look at the descriptor was a load and one thread sized the grid (13.9
+// us); 26,500 where every atom compared itself with all of its cell (10.9 us);
+// 24,000 where the torques went through LDS to a thread for each joint (10.3
+// us).  768-thread form, 256 chains of 500 to 6,000 atoms: 108 us, 123 before
+// the barriers changed.  Workgroups of 768 threads at most: 1,024 would leave
+// 128 registers.
+// SMALL, the form of at most 256 atoms, has one block of atoms and all joints
+// in one wave: the thread of a joint's first atom has its whole torque, the
+// scan needs no carries and no barrier before it, and another wave writes the
+// axes.
 template <int NT, bool ONE>
 __global__ __launch_bounds__(NT) void k_chain(Batch bt, int mode)
 {
     static_assert(JOINT_BLOCK == ATOM_BLOCK && NT % ATOM_BLOCK == 0, "blocks of one size");
     constexpr int NW = NT / WAVE, WPB = ATOM_BLOCK / WAVE;  // waves, waves per block
     constexpr bool KEEP_AXIS = ONE && NT <= 512;            // registers left for ua_1, pa_1
-    constexpr bool MATCH = ONE && NW <= 4;                  // a byte per wave in a cell's word
+    constexpr bool SMALL = NT == 256;
     extern __shared__ __align__(16) unsigned char s_dyn[];
     __shared__ double s_red[NW][12];
     __shared__ double s_blk[CHAIN_JBLOCKS][12], s_carry[CHAIN_JBLOCKS][12];
     __shared__ double s_tm[NW];
+    __shared__ double s_tau1[SMALL ? 3 * (NT / APR) : 1];
     __shared__ int s_bad[NW], s_scan[NW];
 
     ChainDev *dev = bt.n_chains == 1 ? bt.only : bt.table[blockIdx.x];
@@ -1695,17 +1701,23 @@ __global__ __launch_bounds__(NT) void k_chain(Batch bt, int mode)
     // (threads beyond the last atom or joint the last one's, and leave it)
     double4 r0_1, ap_1, u0_1, p0_1, uc_1, pc_1, ua_1, pa_1;  // ua, pa: axis of the joint whose first atom this is
     double th_1 = 0.0;
-    unsigned free_1 = 0;
+    unsigned free_1 = 0, free_a = 0;  // whether joint tid moves; the joint of atom tid
     AtomForce in_1;  // stale, and not used, unless pending
     if (ONE) {
-        const int a = min(tid, n - 1), j = min(tid, J - 1), res = a / APR, ja = 2 * res + (a - res * APR == 8 ? 1 : 0);
+        // (SMALL: each wave has all joints)
+        const int a = min(tid, n - 1), j = min(SMALL ? lane : tid, J - 1), res = a / APR, slot = a - res * APR;
+        const int ja = 2 * res + (slot == 8 ? 1 : 0);
         in_1 = load_force(cd, a);
         if (KEEP_AXIS) {
             ua_1 = cd->jcur[2 * ja];
             pa_1 = cd->jcur[2 * ja + 1];
         }
-        uc_1 = cd->jcur[2 * j];
-        pc_1 = cd->jcur[2 * j + 1];
+        if (SMALL) {
+            free_a = cd->mask[slot == 4 && n_chi ? J + res : ja];
+        } else {
+            uc_1 = cd->jcur[2 * j];
+            pc_1 = cd->jcur[2 * j + 1];
+        }
         u0_1 = cd->joint0[2 * j];
         p0_1 = cd->joint0[2 * j + 1];
         th_1 = cd->theta[min(tid, J + n_chi - 1)];
@@ -1716,13 +1728,14 @@ __global__ __launch_bounds__(NT) void k_chain(Batch bt, int mode)
     const GridRule rule = grid_rule(cd);
     unsigned *s_cell = reinterpret_cast<unsigned *>(s_dyn + (ONE ? sizeof(double) * 12 * (J + 1) : 0));
     if (ONE) {
-        for (int i = tid; i < rule.cap_cells / (MATCH ? 4 : 8); i += NT) reinterpret_cast<uint4 *>(s_cell)[i] = make_uint4(0, 0, 0, 0);
+        for (int i = tid; i < rule.cap_cells / (SMALL ? 4 : 8); i += NT) reinterpret_cast<uint4 *>(s_cell)[i] = make_uint4(0, 0, 0, 0);
         // here all the loads are done: a wait for one behind the stores below
         // would wait for those too
         auto done = [](double4 &v) { asm volatile("" : "+v"(v.x), "+v"(v.y), "+v"(v.z)); };
-        done(u0_1); done(p0_1); done(uc_1); done(pc_1); done(r0_1); done(ap_1);
+        done(u0_1); done(p0_1); done(r0_1); done(ap_1);
+        if (!SMALL) { done(uc_1); done(pc_1); }
         if (KEEP_AXIS) { done(ua_1); done(pa_1); }
-        asm volatile("" : "+v"(ap_1.w), "+v"(th_1), "+v"(free_1));
+        asm volatile("" : "+v"(ap_1.w), "+v"(th_1), "+v"(free_1), "+v"(free_a));
     }
     // Before the first thread of the workgroup changes a flag a barrier follows
     // the reads above.  Barriers are of LDS only, as nothing else goes between
@@ -1739,88 +1752,130 @@ __global__ __launch_bounds__(NT) void k_chain(Batch bt, int mode)
 
     double tm = 0.0;
     if (pending) {
-        // wrenches and torques: s_tau[j] first holds the part of tau_j from the
-        // atom block of j's first downstream atom, s_part the block sums
-        double *s_tau = reinterpret_cast<double *>(s_dyn);
-        double(*s_part)[WPART] = reinterpret_cast<double(*)[WPART]>(s_tau + J + n_chi);
-        for (int lb0 = 0; lb0 < nblk; lb0 += NT / ATOM_BLOCK) {
-            const int lb = lb0 + grp, a = lb * ATOM_BLOCK + gt;
+        int bad = 0;
+        double *s_tau = SMALL ? s_tau1 : reinterpret_cast<double *>(s_dyn);
+        if (SMALL) {
+            // one block of atoms: the thread of a joint's first atom has its whole torque
             double4 r;
             double S[WPART];
-            wrench_of(ONE ? in_1 : load_force(cd, min(a, n - 1)), a < n, r, S);
+            wrench_of(in_1, tid < n, r, S);
             wave_suffix(S);
-            if (!ONE) lds_barrier();  // the last pass has read s_red
             if (lane == 0)
 #pragma unroll
                 for (int k = 0; k < WPART; ++k) s_red[w][k] = S[k];
             lds_barrier();
-            add_later_waves<WPB>(S, s_red + w0, w - w0);
-            if (a < n) {
-                const int res = a / APR, slot = a - res * APR;
-                if (slot == 4 && n_chi) s_tau[J + res] = chi_torque(cd, a, r);
-                if (slot == 2 || slot == 8) {
-                    const int j = 2 * res + (slot == 8 ? 1 : 0);
-                    s_tau[j] = KEEP_AXIS ? axis_torque(ua_1, pa_1, S) : joint_torque(cd, j, S);
-                }
+            add_later_waves<WPB>(S, s_red, w);
+            const int res = tid / APR, slot = tid - res * APR;
+            const bool axis = slot == 2 || slot == 8;
+            if (tid < n && (axis || (slot == 4 && n_chi))) {
+                const double t = axis ? axis_torque(ua_1, pa_1, S) + 0.0 : chi_torque(cd, tid, r);
+                const int j = axis ? 2 * res + (slot == 8 ? 1 : 0) : J + res;
+                s_tau[j] = t;
+                cd->tau[j] = t;
+                bad = !isfinite(t);
+                if (free_a) tm = fabs(t);
             }
-            if (gt < WPART && lb < nblk) {
-                double t = 0.0;
+            tm = wave_max(tm);
+            bad = __any(bad);
+            if (w == NW - 1) {
+                // (the last wave has the fewest atoms) energies and the
+                // non-finite force flag of the pending forces, one to a lane
+                double e = 0.0;
 #pragma unroll
-                for (int i = 0; i < WPB; ++i) t += s_red[w0 + i][gt];
-                s_part[lb][gt] = t;
+                for (int i = 0; i < NW; ++i) e += s_red[i][6 + (lane & 3)];
+                if (lane == 0) st->e_elec = e;
+                if (lane == 1) st->e_vdw = e;
+                if (lane == 2) st->e_cav = e;
+                if (lane == 3) st->post_bad = e > 0.0 ? 1 : 0;
+                bad = bad || __any(lane == 3 && e > 0.0);
             }
-        }
-        lds_barrier();
-        int bad = 0;
-        for (int j0 = 0; j0 < J; j0 += NT) {
-            const int j = j0 + tid, jlo = j - gt;
-            if (jlo + (w - w0) * WAVE < J) {  // the wave holds a joint
-                const int jhi = min(J, jlo + JOINT_BLOCK) - 1, bhi = first_atom_of_joint(jhi) / ATOM_BLOCK;
-                // wrench of the atom blocks after bhi, then of those down to j's
-                double S[6] = {0, 0, 0, 0, 0, 0};
-                if (bhi + 1 < nblk) {
-                    static_assert(CHAIN_ATOMS <= ATOM_BLOCK * WAVE, "later blocks fit one wave");
-                    const int b = bhi + 1 + lane;
-#pragma unroll
-                    for (int k = 0; k < 6; ++k) S[k] = wave_sum(b < nblk ? s_part[b][k] : 0.0);
-                }
-                if (j < J) {
-                    for (int b = bhi; b > first_atom_of_joint(j) / ATOM_BLOCK; --b)
-#pragma unroll
-                        for (int k = 0; k < 6; ++k) S[k] += s_part[b][k];
-                    const double t = s_tau[j] + (ONE ? axis_torque(uc_1, pc_1, S) : joint_torque(cd, j, S));
-                    s_tau[j] = t;
-                    cd->tau[j] = t;
-                    if (!isfinite(t)) bad = 1;
-                    if (ONE ? free_1 : cd->mask[j]) tm = fmax(tm, fabs(t));
-                }
-            }
-        }
-        for (int j = tid; j < J + n_chi; j += NT) {
-            if (j < J) continue;
-            const double t = s_tau[j];
-            cd->tau[j] = t;
-            if (!isfinite(t)) bad = 1;
-            if (ONE ? free_1 : cd->mask[j]) tm = fmax(tm, fabs(t));
-        }
-        tm = wave_max(tm);
-        if (lane == 0) s_tm[w] = tm;
-        bad = __any(bad);
-        if (w == NW - 1) {
-            // (the last wave has the fewest joints) energies and the non-finite force flag of the pending forces
-            double E[4];
-#pragma unroll
-            for (int k = 0; k < 4; ++k) E[k] = wave_sum(lane < nblk ? s_part[lane][6 + k] : 0.0);
             if (lane == 0) {
-                st->e_elec = E[0];
-                st->e_vdw = E[1];
-                st->e_cav = E[2];
-                st->post_bad = E[3] > 0.0 ? 1 : 0;
+                s_tm[w] = tm;
+                s_bad[w] = bad;
             }
-            bad = bad || E[3] > 0.0;
+            lds_barrier();
+        } else {
+            // wrenches and torques: s_tau[j] first holds the part of tau_j from the
+            // atom block of j's first downstream atom, s_part the block sums
+            double(*s_part)[WPART] = reinterpret_cast<double(*)[WPART]>(s_tau + J + n_chi);
+            for (int lb0 = 0; lb0 < nblk; lb0 += NT / ATOM_BLOCK) {
+                const int lb = lb0 + grp, a = lb * ATOM_BLOCK + gt;
+                double4 r;
+                double S[WPART];
+                wrench_of(ONE ? in_1 : load_force(cd, min(a, n - 1)), a < n, r, S);
+                wave_suffix(S);
+                if (!ONE) lds_barrier();  // the last pass has read s_red
+                if (lane == 0)
+#pragma unroll
+                    for (int k = 0; k < WPART; ++k) s_red[w][k] = S[k];
+                lds_barrier();
+                add_later_waves<WPB>(S, s_red + w0, w - w0);
+                if (a < n) {
+                    const int res = a / APR, slot = a - res * APR;
+                    if (slot == 4 && n_chi) s_tau[J + res] = chi_torque(cd, a, r);
+                    if (slot == 2 || slot == 8) {
+                        const int j = 2 * res + (slot == 8 ? 1 : 0);
+                        s_tau[j] = KEEP_AXIS ? axis_torque(ua_1, pa_1, S) : joint_torque(cd, j, S);
+                    }
+                }
+                if (gt < WPART && lb < nblk) {
+                    double t = 0.0;
+#pragma unroll
+                    for (int i = 0; i < WPB; ++i) t += s_red[w0 + i][gt];
+                    s_part[lb][gt] = t;
+                }
+            }
+            lds_barrier();
+            for (int j0 = 0; j0 < J; j0 += NT) {
+                const int j = j0 + tid, jlo = j - gt;
+                if (jlo + (w - w0) * WAVE < J) {  // the wave holds a joint
+                    const int jhi = min(J, jlo + JOINT_BLOCK) - 1, bhi = first_atom_of_joint(jhi) / ATOM_BLOCK;
+                    // wrench of the atom blocks after bhi, then of those down to j's
+                    double S[6] = {0, 0, 0, 0, 0, 0};
+                    if (bhi + 1 < nblk) {
+                        static_assert(CHAIN_ATOMS <= ATOM_BLOCK * WAVE, "later blocks fit one wave");
+                        const int b = bhi + 1 + lane;
+#pragma unroll
+                        for (int k = 0; k < 6; ++k) S[k] = wave_sum(b < nblk ? s_part[b][k] : 0.0);
+                    }
+                    if (j < J) {
+                        for (int b = bhi; b > first_atom_of_joint(j) / ATOM_BLOCK; --b)
+#pragma unroll
+                            for (int k = 0; k < 6; ++k) S[k] += s_part[b][k];
+                        const double t = s_tau[j] + (ONE ? axis_torque(uc_1, pc_1, S) : joint_torque(cd, j, S));
+                        s_tau[j] = t;
+                        cd->tau[j] = t;
+                        if (!isfinite(t)) bad = 1;
+                        if (ONE ? free_1 : cd->mask[j]) tm = fmax(tm, fabs(t));
+                    }
+                }
+            }
+            for (int j = tid; j < J + n_chi; j += NT) {
+                if (j < J) continue;
+                const double t = s_tau[j];
+                cd->tau[j] = t;
+                if (!isfinite(t)) bad = 1;
+                if (ONE ? free_1 : cd->mask[j]) tm = fmax(tm, fabs(t));
+            }
+            tm = wave_max(tm);
+            if (lane == 0) s_tm[w] = tm;
+            bad = __any(bad);
+            if (w == NW - 1) {
+                // (the last wave has the fewest joints) energies and the non-finite force flag of the pending forces
+                double E[4];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) E[k] = wave_sum(lane < nblk ? s_part[lane][6 + k] : 0.0);
+                if (lane == 0) {
+                    st->e_elec = E[0];
+                    st->e_vdw = E[1];
+                    st->e_cav = E[2];
+                    st->post_bad = E[3] > 0.0 ? 1 : 0;
+                }
+                bad = bad || E[3] > 0.0;
+            }
+            if (lane == 0) s_bad[w] = bad;
+            lds_barrier();
         }
-        if (lane == 0) s_bad[w] = bad;
-        lds_barrier();
         if (mode == MODE_TAU) return;
         bad = 0;
 #pragma unroll
@@ -1867,79 +1922,101 @@ __global__ __launch_bounds__(NT) void k_chain(Batch bt, int mode)
         }
         return;
     }
-    if (n_chi) __syncthreads();  // the side-chain angles are written
-    else lds_barrier();          // s_tau is read
-
     // forward kinematics: s_G[j + 1] = T_jlo o ... o T_j inside each joint
     // block, then the products of the earlier blocks in front
     double(*s_G)[12] = reinterpret_cast<double(*)[12]>(s_dyn);
-    for (int j0 = 0; j0 < J; j0 += NT) {
-        const int j = j0 + tid, jb = j / JOINT_BLOCK;
-        const bool holds = j - lane < J;  // the wave holds a joint
-        Xf x = xf_identity();
-        if (holds) {
-            if (j < J) {
-                if (!ONE) {
-                    u0_1 = cd->joint0[2 * j];
-                    p0_1 = cd->joint0[2 * j + 1];
-                    th_1 = cd->theta[j];
-                }
-                x = joint_xf_of(u0_1, p0_1, th_1);
-            }
-            const int held = J - (j - lane);  // joints in the wave
+    if (SMALL) {
+        static_assert(!SMALL || NT / APR * 2 <= WAVE, "one wave has all joints");
+        if (w == 0) {
+            Xf x = xf_identity();
+            if (lane < J) x = joint_xf_of(u0_1, p0_1, th_1);
 #pragma unroll
             for (int d = 1; d < WAVE; d <<= 1)
-                if (d < held) {  // else there is nothing below to take
+                if (d < J) {  // else there is nothing below to take
                     const Xf y = xf_from_below(x, d);
                     if (lane >= d) {
                         masked_branch();
                         x = xf_mul(y, x);
                     }
                 }
-            if (lane == WAVE - 1) xf_store(s_red[w], x);
+            x = xf_mul(xf_identity(), x);  // no block in front (the product keeps its zeros' signs)
+            if (lane < J) xf_store(s_G[lane + 1], x);
+            if (lead) xf_store(s_G[0], xf_identity());
         }
-        lds_barrier();
-        if (holds) {
-            if (w > w0) {
-                Xf pre = xf_load(s_red[w0]);
-                for (int i = w0 + 1; i < w; ++i) pre = xf_mul(pre, xf_load(s_red[i]));
-                x = xf_mul(pre, x);
-            }
-            if (ONE) x = xf_mul(xf_identity(), x);  // nothing in front of the one block (the product keeps its zeros' signs)
-            if (j < J) {
-                xf_store(s_G[j + 1], x);
-                if (ONE) fk_emit(x, j, u0_1, p0_1, cd->jcur);
-            }
-            if (!ONE && j == min(J, (jb + 1) * JOINT_BLOCK) - 1) xf_store(s_blk[jb], x);
-        }
-        if (!ONE) lds_barrier();
-    }
-    if (lead) xf_store(s_G[0], xf_identity());
-    lds_barrier();
-    if (!ONE && w == 0) {
-        if (lane == 0) xf_store(s_carry[0], xf_identity());
-        if (njb > 1) {
-            Xf x = lane < njb - 1 ? xf_load(s_blk[lane]) : xf_identity();
-            static_assert(CHAIN_JBLOCKS <= 8, "carries of at most eight blocks");
-#pragma unroll
-            for (int d = 1; d < 8; d <<= 1) {
-                Xf y = xf_from_below(x, d);
-                if (lane >= d) {
-                    masked_branch();
-                    x = xf_mul(y, x);
+        if (n_chi) __syncthreads();  // the side-chain angles are written
+        else lds_barrier();
+        if (w == NW - 1 && lane < J) fk_emit(xf_load(s_G[lane + 1]), lane, u0_1, p0_1, cd->jcur);
+    } else {
+        if (n_chi) __syncthreads();  // the side-chain angles are written
+        else lds_barrier();          // s_tau is read
+        for (int j0 = 0; j0 < J; j0 += NT) {
+            const int j = j0 + tid, jb = j / JOINT_BLOCK;
+            const bool holds = j - lane < J;  // the wave holds a joint
+            Xf x = xf_identity();
+            if (holds) {
+                if (j < J) {
+                    if (!ONE) {
+                        u0_1 = cd->joint0[2 * j];
+                        p0_1 = cd->joint0[2 * j + 1];
+                        th_1 = cd->theta[j];
+                    }
+                    x = joint_xf_of(u0_1, p0_1, th_1);
                 }
+                const int held = J - (j - lane);  // joints in the wave
+#pragma unroll
+                for (int d = 1; d < WAVE; d <<= 1)
+                    if (d < held) {  // else there is nothing below to take
+                        const Xf y = xf_from_below(x, d);
+                        if (lane >= d) {
+                            masked_branch();
+                            x = xf_mul(y, x);
+                        }
+                    }
+                if (lane == WAVE - 1) xf_store(s_red[w], x);
             }
-            if (lane < njb - 1) xf_store(s_carry[lane + 1], x);
+            lds_barrier();
+            if (holds) {
+                if (w > w0) {
+                    Xf pre = xf_load(s_red[w0]);
+                    for (int i = w0 + 1; i < w; ++i) pre = xf_mul(pre, xf_load(s_red[i]));
+                    x = xf_mul(pre, x);
+                }
+                if (ONE) x = xf_mul(xf_identity(), x);  // no block in front (the product keeps its zeros' signs)
+                if (j < J) {
+                    xf_store(s_G[j + 1], x);
+                    if (ONE) fk_emit(x, j, u0_1, p0_1, cd->jcur);
+                }
+                if (!ONE && j == min(J, (jb + 1) * JOINT_BLOCK) - 1) xf_store(s_blk[jb], x);
+            }
+            if (!ONE) lds_barrier();
         }
-    }
-    if (!ONE) {
+        if (lead) xf_store(s_G[0], xf_identity());
         lds_barrier();
-        for (int j = tid; j < J; j += NT) {
-            const Xf G = xf_mul(xf_load(s_carry[j / JOINT_BLOCK]), xf_load(s_G[j + 1]));
-            xf_store(s_G[j + 1], G);
-            fk_emit(G, j, cd->joint0[2 * j], cd->joint0[2 * j + 1], cd->jcur);
+        if (!ONE && w == 0) {
+            if (lane == 0) xf_store(s_carry[0], xf_identity());
+            if (njb > 1) {
+                Xf x = lane < njb - 1 ? xf_load(s_blk[lane]) : xf_identity();
+                static_assert(CHAIN_JBLOCKS <= 8, "carries of at most eight blocks");
+#pragma unroll
+                for (int d = 1; d < 8; d <<= 1) {
+                    Xf y = xf_from_below(x, d);
+                    if (lane >= d) {
+                        masked_branch();
+                        x = xf_mul(y, x);
+                    }
+                }
+                if (lane < njb - 1) xf_store(s_carry[lane + 1], x);
+            }
         }
-        lds_barrier();
+        if (!ONE) {
+            lds_barrier();
+            for (int j = tid; j < J; j += NT) {
+                const Xf G = xf_mul(xf_load(s_carry[j / JOINT_BLOCK]), xf_load(s_G[j + 1]));
+                xf_store(s_G[j + 1], G);
+                fk_emit(G, j, cd->joint0[2 * j], cd->joint0[2 * j + 1], cd->jcur);
+            }
+            lds_barrier();
+        }
     }
 
     // positions and bounding box
@@ -1994,7 +2071,7 @@ __global__ __launch_bounds__(NT) void k_chain(Batch bt, int mode)
         st->need_grid = 0;
     }
 
-    if (MATCH) {
+    if (SMALL) {
         // Cell list of at most 256 atoms, one to a thread: the lanes of a wave
         // that share a cell by ballots over the bits of the key, one byte of
         // the cell's word for the count of each wave.  A slot is then the
