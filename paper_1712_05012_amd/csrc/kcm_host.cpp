@@ -344,15 +344,16 @@ struct TimedIter {
 };
 
 // The form of the batch's iterations (the results are the same).  One
-// workgroup per chain replaces eight launches of about 4.5 us by one: of
-// 15 us for chains of at most 256 atoms, and about 20 us more for each 768
-// atoms of the longest.  Measured, a whole iteration in mixed precision,
-// one workgroup against nine launches: one chain of 150 atoms 40 against 63
-// us, of 1,000 atoms 55 against 69, of 2,000 73 against 75, of 3,000 89
-// against 79.  With chains for half of the 256 CUs the workgroups run side by
-// side and win at every length they can hold: 128 chains of 6,400 atoms 2,913
-// against 2,954 us; 32 of them lose, 855 against 785.
-constexpr int CHAIN_ATOMS_ALWAYS = 1536, CHAIN_MANY = 128;
+// workgroup per chain replaces eight launches of about 5 us by one: of 9 us for
+// chains of at most 256 atoms, and about 20 us more for each 768 atoms of the
+// longest.  Measured, a whole iteration in mixed precision, one workgroup
+// against nine launches: one chain of 150 atoms 28 against 50 us, of 1,000
+// atoms 43 against 53, of 2,000 55 against 59, of 2,500 63 against 61; eight of
+// 2,000 92 against 97, of 3,000 122 against 118.  With chains for half of the
+// 256 CUs the workgroups run side by side and win at every length they can
+// hold: 128 chains of 6,400 atoms 2,153 against 2,182 us; 32 of them lose, 642
+// against 584, and 96 are even.
+constexpr int CHAIN_ATOMS_ALWAYS = 2048, CHAIN_MANY = 128;
 void set_form(Batch &b, int max_atoms, int terms)
 {
     b.max_atoms = max_atoms;

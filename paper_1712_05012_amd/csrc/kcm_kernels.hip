@@ -25,11 +25,13 @@
 //               in FP64, Coulomb + LJ (eqs 02-03_9), solvation neighbours in
 //               LDS, and the SASA enumeration of Algorithm 1 with the C-state
 //               rules (Sec. 3.4): coverage counts with four samples per lane,
-//               the displaced tests of critical samples inline and those of
-//               exposed samples with one lane per neighbour.  Solvation
-//               events are scattered as fixed-point integers.
+//               the displaced tests of critical samples and of exposed ones
+//               from a queue of (sample, neighbour) pairs.  Solvation events
+//               are scattered as fixed-point integers.
 //   k_wrench    one thread per atom: wrench (F, r x F), the suffix sum inside
 //               the workgroup and the workgroup-local part of each torque.
+//   k_chain     one workgroup per chain: all of these but k_force, for calls of
+//               short or many chains, whose iterations are then two launches.
 #include "kcm_internal.h"
 
 #include <float.h>
@@ -2241,9 +2243,10 @@ constexpr float CAP_SPLIT = 0.6f;
 // cell-ordered atoms in turn, so that its L2 serves a few regions of space and
 // all XCDs see the same mix of atoms); or XCD-aware by eighths (XCD x takes the
 // x-th contiguous eighth).  Force kernel in shapes 0 to 3: 256-chain batch
-// 2,140, 2,180, 2,175, 2,197 us; 10,000-residue globule 301, 303, 307, 314; 256
-// short chains in vacuum (FP64) 41.9, 46.7, 40.7, 41; sixteen chains of unequal
-// density 171, 174, 215, 220 (one eighth holds most of the work).
+// 2,136, 2,160, 2,114, 2,184 us; 10,000-residue globule 306, 307, 294, 307; 500
+// short chains in water 207, 213, 207, 212; 256 in vacuum (FP64) 31.7, 32.7,
+// 30.1, 31.4; sixteen chains of unequal density 171, 174, 215, 220 (one eighth
+// holds most of the work).
 // Every shape visits the candidates and appends the neighbours in the same
 // order, and takes the same decisions: the results are the same bit for bit.
 enum XcdOrder { CELL_ORDER, XCD_CHUNKS, XCD_EIGHTHS };
