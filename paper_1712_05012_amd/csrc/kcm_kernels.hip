@@ -2933,11 +2933,17 @@ __global__ __launch_bounds__(WAVE, force_waves(sizeof(Real) == 4, CAV)) void k_f
         pv[0] = ps.f[0]; pv[1] = ps.f[1]; pv[2] = ps.f[2]; pv[3] = ps.e[0]; pv[4] = ps.e[1];
     }
     const double sums = wave_sum5(pv[0], pv[1], pv[2], pv[3], pv[4]);
-    // stored now, so that nothing of the pair phase stays live below
+    // stored now, so that nothing of the pair phase stays live below.  Both
+    // pointers are read as scalars and the component comes from a table of four
+    // bits for every eight lanes: the compiler otherwise makes one load at a
+    // lane's own address of the two, and branches of the choices.
+    const gptr<double> energies = (gptr<double>)glob(cd->e_atom) + 4 * (size_t)ai;
     if ((lane & 15) == 0 || lane == 8) {
-        const bool energy = lane == 8 || lane == 48;
-        const gptr<double> to = (gptr<double>)glob(energy ? cd->e_atom : cd->f_pair) + 4 * (size_t)ai;
-        to[energy ? (lane == 8 ? 1 : 0) : (lane == 32 ? 1 : lane >> 3)] = energy ? 0.5 * sums : sums;
+        const gptr<double> forces = (gptr<double>)glob(cd->f_pair) + 4 * (size_t)ai;
+        asm("" : : "s"(forces), "s"(energies));
+        const int k = lane >> 3;
+        const bool energy = 0x42 >> k & 1;  // lanes 8 and 48
+        (energy ? energies : forces)[0x10210 >> 4 * k & 7] = energy ? 0.5 * sums : sums;
     }
 
     double e_cav = 0.0, n_exp = -1.0;
@@ -3231,7 +3237,7 @@ __global__ __launch_bounds__(WAVE, force_waves(sizeof(Real) == 4, CAV)) void k_f
         e_cav = glob(cd->g0)[ai] * (double)(N - tot) / (double)N;  // eq G_cav_patch (lane 0)
         n_exp = (double)(N - tot);
     }
-    if (lane == 0) ((gptr<double2>)&glob(cd->e_atom)[ai])[1] = make_double2(e_cav, n_exp);
+    if (lane == 0) ((gptr<double2>)energies)[1] = make_double2(e_cav, n_exp);
 }
 
 // ---------------------------------------------------------------------------
