@@ -2186,10 +2186,15 @@ __global__ __launch_bounds__(NT) void k_chain(Batch bt, int mode)
 // address arithmetic with it.  256-chain batch 2,052 us, 2,116 without; 500
 // short chains in water 197 and 208, FP64 275 and 291.
 #if defined(__HIP_DEVICE_COMPILE__)
-using CDev = const __attribute__((address_space(4))) ChainDev *;
+template <typename T> using cptr = const __attribute__((address_space(4))) T *;
 #else
-using CDev = const ChainDev *;
+template <typename T> using cptr = const T *;
 #endif
+using CDev = cptr<ChainDev>;
+// (So are the constants of an atom: read as scalars they need not wait for the
+// atomics under way, as a vector load behind those does: 10,000 atoms 40.0 us,
+// 41.2 so, the batch 2,009 and 2,038.)
+template <typename T> __device__ __forceinline__ cptr<T> constant(const T *p) { return (cptr<T>)p; }
 // fixed-point accumulation of the solvation force
 __device__ __forceinline__ void fix_add(gptr<long long> p, long long v)
 {
@@ -2252,10 +2257,10 @@ constexpr float CAP_SPLIT = 0.6f;
 // cell-ordered atoms in turn, so that its L2 serves a few regions of space and
 // all XCDs see the same mix of atoms); or XCD-aware by eighths (XCD x takes the
 // x-th contiguous eighth).  Force kernel in shapes 0 to 3: 256-chain batch
-// 2,136, 2,160, 2,114, 2,184 us; 10,000-residue globule 306, 307, 294, 307; 500
-// short chains in water 207, 213, 207, 212; 256 in vacuum (FP64) 31.7, 32.7,
-// 30.1, 31.4; sixteen chains of unequal density 171, 174, 215, 220 (one eighth
-// holds most of the work).
+// 2,009, 2,046, 1,995, 2,048 us; 10,000-residue globule 288, 276, 275, 280; 500
+// short chains in water 194, 199, 192, 197; 256 in vacuum (FP64) 29.3, 31.1,
+// 28.8, 29.7; sixteen chains of unequal density, with an earlier kernel, 171,
+// 174, 215, 220 (one eighth holds most of the work).
 // Every shape visits the candidates and appends the neighbours in the same
 // order, and takes the same decisions: the results are the same bit for bit.
 enum XcdOrder { CELL_ORDER, XCD_CHUNKS, XCD_EIGHTHS };
@@ -3224,7 +3229,7 @@ __global__ __launch_bounds__(WAVE, force_waves(sizeof(Real) == 4, CAV)) void k_f
                 take_pairs(nq, 0);
                 __syncthreads();
                 // eq F_cav_patch: atom i gains G0_i ev / (N dr) per axis, neighbour j the opposite
-                const long long qf = glob(cd->qfix)[ai];
+                const long long qf = constant(cd->qfix)[ai];
                 for (int ul = lane; ul < nlist; ul += WAVE) {
                     const int u = entry_of(ul);
                     const unsigned w = s_ev[u];
@@ -3243,8 +3248,8 @@ __global__ __launch_bounds__(WAVE, force_waves(sizeof(Real) == 4, CAV)) void k_f
         __syncthreads();
         const int tot = wave_sum4_i(ncov, own0, own1, own2);
         if ((lane & 15) == 0 && lane && tot)
-            fix_add(&glob(cd->f_cav)[3 * ai + (lane == 32 ? 0 : lane == 16 ? 1 : 2)], (long long)tot * glob(cd->qfix)[ai]);
-        e_cav = glob(cd->g0)[ai] * (double)(N - tot) / (double)N;  // eq G_cav_patch (lane 0)
+            fix_add(&glob(cd->f_cav)[3 * ai + (lane == 32 ? 0 : lane == 16 ? 1 : 2)], (long long)tot * constant(cd->qfix)[ai]);
+        e_cav = constant(cd->g0)[ai] * (double)(N - tot) / (double)N;  // eq G_cav_patch (lane 0)
         n_exp = (double)(N - tot);
     }
     if (lane == 0) ((gptr<double2>)energies)[1] = make_double2(e_cav, n_exp);
