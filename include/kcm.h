@@ -251,9 +251,11 @@ kcm_status kcm_mc_minimize(kcm_chain *const *chains, int32_t n_chains, int32_t n
 kcm_status kcm_mc_best_theta(const kcm_chain *chain, void *hip_stream, double *theta);
 
 /* Copy a chain's state to host arrays (any pointer may be NULL); synchronises
- * hip_stream.  theta[J] and dtheta[J] (the angles and the last applied step of
- * eq KCM_07); xyz[n][3] and force[n][3] (total, eqs 02, 03 and F_cav_patch) at
- * the conformation of the last force evaluation; tau[J] (eqs KCM_01-KCM_06).
+ * hip_stream, and where the chain's last work went to another stream every
+ * blocking stream of the device as well.  theta[J] and dtheta[J] (the angles
+ * and the last applied step of eq KCM_07); xyz[n][3] and force[n][3] (total,
+ * eqs 02, 03 and F_cav_patch) at the conformation of the last force evaluation;
+ * tau[J] (eqs KCM_01-KCM_06).
  * The angles are the whole state a chain carries from one iteration to the
  * next: a chain built from them continues bit for bit. */
 kcm_status kcm_get_state(const kcm_chain *chain, void *hip_stream, double *theta, double *xyz,

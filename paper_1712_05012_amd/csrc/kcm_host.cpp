@@ -6,6 +6,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <chrono>
 #include <cmath>
 #include <cstdio>
@@ -465,6 +466,7 @@ struct kcm_chain {
     std::vector<unsigned char> staging;  // host source of the build copies
     bool boot = true;    // the conformation has no grid yet (built, or new angles)
     uint64_t mark = 0;   // the last call that checked it (check_chains)
+    std::atomic<hipStream_t> stream{nullptr};  // where work on it was last queued
 };
 
 namespace {
@@ -497,6 +499,7 @@ kcm_status ensure_table(kcm_chain *const *chains, int n_chains, hipStream_t stre
         t = oldest;
     }
     t->last_use = ++g_table_clock;
+    for (int i = 0; i < n_chains; ++i) chains[i]->stream.store(stream, std::memory_order_relaxed);
     if (!same) {
         t->chains.clear();  // until the new set is in place
         t->mc_off_per = -1;
@@ -830,6 +833,7 @@ kcm_status kcm_build_chain(const kcm_chain_desc *desc, const kcm_params *params,
     c->J = l.Jt;
     c->njb = l.njb;
     c->N = l.N;
+    c->stream.store(stream, std::memory_order_relaxed);
     if (hipGetDevice(&c->device) != hipSuccess) c->device = 0;
     unsigned char *base = static_cast<unsigned char *>(dev_mem);
 
@@ -1253,6 +1257,7 @@ kcm_status kcm_step_noalloc(kcm_chain *const *chains, int n_chains, int n_iter, 
     std::sort(g_noalloc_sorted, g_noalloc_sorted + n_chains);
     if (std::adjacent_find(g_noalloc_sorted, g_noalloc_sorted + n_chains) != g_noalloc_sorted + n_chains)
         return fail(KCM_E_INVAL, "a chain appears twice in one call");
+    for (int i = 0; i < n_chains; ++i) chains[i]->stream.store(stream, std::memory_order_relaxed);
     const int prec = chains[0]->h.precision;
     NoallocDevice *d = nullptr;
     kcm_status s = noalloc_device(dev, &d);
@@ -1428,8 +1433,16 @@ kcm_status kcm_get_state(const kcm_chain *c, void *hip_stream, double *theta, do
     if (dtheta) dst[what.add(c->h.dtheta, c->J)] = dtheta;
     if (xyz) dst[what.add_atoms(c->h.r, nullptr, c->n)] = xyz;
     if (force) dst[what.add_atoms(c->h.f_pair, c->h.f_cav, c->n)] = force;
+    // Work on the chain that another stream may still hold: the read goes over
+    // the null stream, as the copies below do, which waits for every blocking
+    // stream.  (One handle stands for each thread's own default stream.)
+    hipStream_t from = s;
+    if (s != nullptr && (s != c->stream.load(std::memory_order_relaxed) || s == hipStreamPerThread)) {
+        HIP_TRY(hipStreamSynchronize(s));
+        from = nullptr;
+    }
     kcm_status st = KCM_OK;
-    if (what.n_parts > 0 && box_read(c, what, dst, s, &st)) return st;
+    if (what.n_parts > 0 && box_read(c, what, dst, from, &st)) return st;
     HIP_TRY(hipStreamSynchronize(s));
     if (theta) HIP_TRY(hipMemcpy(theta, c->h.theta, 8 * c->J, hipMemcpyDeviceToHost));
     if (tau) HIP_TRY(hipMemcpy(tau, c->h.tau, 8 * c->J, hipMemcpyDeviceToHost));
