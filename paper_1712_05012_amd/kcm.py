@@ -208,8 +208,8 @@ def kcm_build_chain(inputs: ChainInputs, params: kcm_params, dev_ptr: int, nbyte
 def _handles(chains):
     try:
         ptrs = array("Q", [c._ptr for c in chains])  # Chain objects, not freed
-    except (AttributeError, TypeError):
-        ptrs = array("Q", [c.handle.value if isinstance(c, Chain) else c.value for c in chains])
+    except (AttributeError, TypeError):  # bare handles, null ones too: the library refuses those
+        return (C.c_void_p * len(chains))(*[c.handle.value if isinstance(c, Chain) else c.value for c in chains])
     return (C.c_void_p * len(ptrs)).from_buffer(ptrs) if ptrs else (C.c_void_p * 0)()
 
 
