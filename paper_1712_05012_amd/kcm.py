@@ -427,6 +427,15 @@ def kcm_chain_free(handle):
 class Chain:
     """Builds one chain in a torch-allocated device block on the current device."""
 
+    @property
+    def handle(self):
+        return self._handle
+
+    @handle.setter
+    def handle(self, h):
+        self._handle = h
+        self._ptr = None if h is None else h.value  # what batched calls pass on (_handles)
+
     def __init__(self, res_type, residue_types, params: kcm_params | None = None, theta0=None,
                  joint_mask=None, stream=None, device=None, side_chains: bool = False):
         import torch
@@ -438,7 +447,6 @@ class Chain:
         ptr = self.block.data_ptr()
         self.offset = (-ptr) % 256
         self.handle = kcm_build_chain(self.inputs, self.params, ptr + self.offset, self.nbytes, stream)
-        self._ptr = self.handle.value
         self.n_atoms, self.n_joints, self.n_samples, self.precision = kcm_chain_info(self.handle)
 
     def step(self, n_iter=1, stream=None):
@@ -468,7 +476,7 @@ class Chain:
     def free(self):
         if self.handle is not None:
             kcm_chain_free(self.handle)
-            self.handle = self._ptr = None
+            self.handle = None
             self.block = None
 
     def __del__(self):
