@@ -323,10 +323,17 @@ kcm_status kcm_set_timing(int every);
  * captures that many consecutive iterations of a call's chains as one HIP
  * graph (on a private stream, once per batch composition and depth) and
  * replays it on hip_stream, with single-iteration replays for the rest of a
- * call; iterations = 0 launches the kernels directly.  Calls of short or many
- * chains, whose iterations are two launches, are always launched directly.
+ * call; iterations = 0 launches the kernels directly.  Calls whose iterations
+ * are two launches (kcm_iteration_launches) are always launched directly.
  * Every mode gives identical results.  KCM_E_INVAL unless 0 <= iterations <= 64. */
 kcm_status kcm_set_graphs(int iterations);
+
+/* How a call of n_chains chains of n_res[0 .. n_chains-1] residues runs each of
+ * its iterations: as two launches (one workgroup per chain, then the force
+ * kernel) or as nine (*launches = 2 or 9).  The results are the same; the choice
+ * is the faster form by the chains' number and lengths.  Needs no device.
+ * KCM_E_INVAL for a null argument, no chains or an n_res outside 1 .. 524288. */
+kcm_status kcm_iteration_launches(const int32_t *n_res, int32_t n_chains, int32_t *launches);
 
 /* Launch shape of the force kernel (process-wide), for the autotuner:
  * 0 (default): each lane loads one candidate per trip of the candidate loop,

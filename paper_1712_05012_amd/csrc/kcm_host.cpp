@@ -344,22 +344,37 @@ struct TimedIter {
     hipEvent_t it0, f0, f1, it1;
 };
 
-// The form of the batch's iterations (the results are the same).  One
-// workgroup per chain replaces eight launches of about 5 us by one: of 9 us for
-// chains of at most 256 atoms, and about 20 us more for each 768 atoms of the
-// longest.  Measured, a whole iteration in mixed precision, one workgroup
-// against nine launches: one chain of 150 atoms 28 against 50 us, of 1,000
-// atoms 43 against 53, of 2,000 55 against 59, of 2,500 63 against 61; eight of
-// 2,000 92 against 97, of 3,000 122 against 118.  With chains for half of the
-// 256 CUs the workgroups run side by side and win at every length they can
-// hold: 128 chains of 6,400 atoms 2,153 against 2,182 us; 32 of them lose, 642
-// against 584, and 96 are even.
-constexpr int CHAIN_ATOMS_ALWAYS = 2048, CHAIN_MANY = 128;
+// The form of a call's iterations (the results are the same): one workgroup per
+// chain and the force kernel, or nine launches.  Up to 512 atoms the first is
+// always the faster: a workgroup takes 9 to 15 us, several share a CU, and a
+// launch is about 5 us (4,000 chains of 150 atoms 69 us without the force
+// kernel, nine launches 230; 4,000 of 300 atoms 261 and 354).  Above, a
+// workgroup has 768 threads and a CU to itself.  Past 2,048 atoms a call of
+// fewer than 128 chains leaves most CUs idle behind its longest one, and takes
+// nine launches.  Any other call goes by what the two forms take more than each
+// other, in us: the longest chain 11.5 for each 1,000 atoms, which it walks
+// alone, and each chain past the 256 that run at once 0.043; the nine launches
+// 33 at the start, 0.047 for each 1,000 atoms of the call and 0.024 for each
+// chain.  A whole iteration in mixed precision, one workgroup against nine
+// launches: 1 chain of 150 atoms 28 and 50 us, 1 of 2,000 54 and 63, 8 of 2,000
+// 88 and 97, 128 of 2,100 664 and 703, 128 of 6,400 2,031 and 2,057; 127 of 150
+// with one of 3,000 107 and 109, with one of 4,000 124 and 112, with one of
+// 6,400 155 and 119; 255 of 150 with one of 6,400 202 and 170; 64 of 150 with 64
+// of 6,400 1,101 and 1,072; 3,999 of 20 with one of 2,000 429 and 392.
+constexpr int CHAIN_SHARED = 512, CHAIN_ATOMS_ALWAYS = 2048, CHAIN_MANY = 128, CHAIN_SLOTS = 256;
+bool one_workgroup_form(int n_chains, int max_atoms, long long total_atoms)
+{
+    if (max_atoms <= CHAIN_SHARED) return true;
+    if (max_atoms > CHAIN_ATOMS || (max_atoms > CHAIN_ATOMS_ALWAYS && n_chains < CHAIN_MANY)) return false;
+    const double one = 11.5e-3 * max_atoms + 0.043 * std::max(0, n_chains - CHAIN_SLOTS);
+    const double nine = 33.0 + 47e-6 * (double)total_atoms + 0.024 * n_chains;
+    return one <= nine;
+}
 void set_form(Batch &b, int max_atoms, int terms)
 {
     b.max_atoms = max_atoms;
     b.terms = terms;
-    b.fused = max_atoms <= CHAIN_ATOMS_ALWAYS || (b.n_chains >= CHAIN_MANY && max_atoms <= CHAIN_ATOMS) ? 1 : 0;
+    b.fused = one_workgroup_form(b.n_chains, max_atoms, b.total_atoms) ? 1 : 0;
 }
 
 // One iteration; with ti, events bracket the iteration and the force kernel.
@@ -1575,6 +1590,20 @@ kcm_status kcm_get_cells(const kcm_chain *c, void *hip_stream, int32_t *dims, do
         if (cell_start_capacity < g.n_cells + 1) return fail(KCM_E_INVAL, "cell_start_capacity too small");
         HIP_TRY(hipMemcpy(cell_start, c->h.cell_start, 4 * ((size_t)g.n_cells + 1), hipMemcpyDeviceToHost));
     }
+    return KCM_OK;
+}
+
+kcm_status kcm_iteration_launches(const int32_t *n_res, int32_t n_chains, int32_t *launches)
+{
+    if (!n_res || !launches || n_chains < 1) return fail(KCM_E_INVAL, "no chains or null launches");
+    int longest = 0;
+    long long total = 0;
+    for (int i = 0; i < n_chains; ++i) {
+        if (n_res[i] < 1 || n_res[i] > (1 << 19)) return fail(KCM_E_INVAL, "n_res out of range (1 .. 524288)");
+        longest = std::max(longest, APR * n_res[i]);
+        total += APR * n_res[i];
+    }
+    *launches = one_workgroup_form(n_chains, longest, total) ? 2 : 9;
     return KCM_OK;
 }
 

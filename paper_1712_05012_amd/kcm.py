@@ -26,7 +26,7 @@ EXPORTED = ("kcm_default_params", "kcm_chain_bytes", "kcm_build_chain", "kcm_ste
             "kcm_get_state", "kcm_get_forces", "kcm_set_theta", "kcm_get_cells", "kcm_chain_info",
             "kcm_set_timing", "kcm_get_timing", "kcm_chain_free", "kcm_last_error", "kcm_get_atom_terms",
             "kcm_set_limits", "kcm_set_graphs", "kcm_mc_minimize", "kcm_mc_best_theta", "kcm_set_theta_batch",
-            "kcm_step_noalloc", "kcm_set_force_variant")
+            "kcm_step_noalloc", "kcm_set_force_variant", "kcm_iteration_launches")
 KCM_FORCE_VARIANTS = 4
 KCM_NBR_CHUNK = 240
 KCM_NOALLOC_MAX_CHAINS = 1024
@@ -100,6 +100,7 @@ def load_library(path: str = LIB_PATH):
     lib.kcm_set_limits.argtypes = [vp, C.c_double, C.c_int64, vp]
     lib.kcm_set_graphs.argtypes = [C.c_int]
     lib.kcm_set_force_variant.argtypes = [C.c_int]
+    lib.kcm_iteration_launches.argtypes = [vp, C.c_int32, vp]
     lib.kcm_get_cells.argtypes = [vp, vp, vp, vp, vp, vp, vp, vp, C.c_int32]
     lib.kcm_chain_info.argtypes = [vp, vp, vp, vp, vp]
     lib.kcm_set_timing.argtypes = [C.c_int]
@@ -404,6 +405,14 @@ def kcm_set_graphs(iterations):
 def kcm_set_force_variant(variant: int):
     """Launch shape of the force kernel (0 .. KCM_FORCE_VARIANTS-1), process-wide."""
     _check(load_library().kcm_set_force_variant(int(variant)))
+
+
+def kcm_iteration_launches(n_res) -> int:
+    """Launches per iteration, 2 or 9, of a call of chains of these residue counts."""
+    n = np.ascontiguousarray(n_res, dtype=np.int32).reshape(-1)
+    out = C.c_int32()
+    _check(load_library().kcm_iteration_launches(n.ctypes.data, n.size, C.byref(out)))
+    return int(out.value)
 
 
 def kcm_set_timing(every: int):
