@@ -631,6 +631,10 @@ kcm_status write_field(T *dev_field, T value, hipStream_t s)
     return KCM_OK;
 }
 
+// Pinned memory that a kernel stores a flag to while the host polls it has to be
+// coherent, which the environment (HIP_HOST_COHERENT) decides unless it is asked for.
+constexpr unsigned kFlagged = hipHostMallocCoherent;
+
 // Waits until the stream's last kernel has stored seq to the n pinned flags:
 // polls for a while (a hundred microseconds at most; the end of a stream's work
 // is seen some five microseconds sooner so), then synchronises the stream.
@@ -665,7 +669,7 @@ kcm_status gather_stats(Table *t, hipStream_t stream, std::vector<ChainStats> &o
         t->stats_cap = 0;
         const int cap = std::max(2 * n, 64);
         // one record more, for the flag
-        HIP_TRY(hipHostMalloc(&t->stats_host, sizeof(ChainStats) * (cap + 1), hipHostMallocDefault));
+        HIP_TRY(hipHostMalloc(&t->stats_host, sizeof(ChainStats) * (cap + 1), kFlagged));
         std::memset(t->stats_host + cap, 0, sizeof(ChainStats));
         t->stats_cap = cap;
     }
@@ -710,7 +714,7 @@ bool box_read(const kcm_chain *c, const BoxRead &what, double *const (&dst)[BOX_
         if (!lock.owns_lock()) continue;
         if (!b.mem) {
             void *p = nullptr;
-            if (hipHostMalloc(&p, kBoxBytes + 256, hipHostMallocPortable) != hipSuccess) {
+            if (hipHostMalloc(&p, kBoxBytes + 256, hipHostMallocPortable | kFlagged) != hipSuccess) {
                 (void)hipGetLastError();
                 return false;
             }

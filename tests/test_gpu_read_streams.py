@@ -1,7 +1,11 @@
 """A state read on another stream than the chain's work waits for that work
-where the streams are blocking ones (needs an MI355X)."""
+where the streams are blocking ones, and reads work with either default of
+pinned memory (needs an MI355X)."""
 import ctypes as C
+import os
 import re
+import subprocess
+import sys
 
 import numpy as np
 import pytest
@@ -13,6 +17,9 @@ from gpu_common import TYPES, params  # noqa: E402
 from paper_1712_05012_amd import kcm  # noqa: E402
 
 pytestmark = pytest.mark.gpu
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
 
 
 @pytest.fixture(scope="module")
@@ -52,3 +59,31 @@ def test_read_on_another_stream_sees_the_queued_steps(hip, m, n_iter, reader):
         assert hip.hipStreamSynchronize(C.c_void_p(s)) == 0 and hip.hipStreamDestroy(C.c_void_p(s)) == 0
     a.free()
     b.free()
+
+
+def test_reads_do_not_depend_on_the_default_of_pinned_memory():
+    # the records and the boxes are polled: coherent memory, also where the
+    # environment makes pinned memory non-coherent unless asked otherwise
+    code = """
+import sys
+sys.path[:0] = [%r, %r]
+import torch
+import numpy as np
+from gpu_common import TYPES, params
+import synth
+from paper_1712_05012_amd import kcm
+c = kcm.Chain(synth.sequence(30, 61), TYPES, params(kcm.KCM_MIXED), theta0=synth.random_dihedrals(30, 61))
+for k in range(20):
+    rep = c.step(1)
+    st = c.state()
+    f = c.forces()
+    assert rep.iterations == k + 1 and np.abs(st["tau"]).max() == rep.max_tau
+    assert np.array_equal(st["force"], f[0] + f[1]) and np.array_equal(st["theta"], c.theta())
+c.free()
+print("reads agree")
+""" % (ROOT, HERE)
+    for value in ("0", "1"):
+        r = subprocess.run([sys.executable, "-c", code], env=dict(os.environ, HIP_HOST_COHERENT=value), timeout=100,
+                           capture_output=True, text=True)
+        print(f"case=pinned-default HIP_HOST_COHERENT={value} rc={r.returncode}", flush=True)
+        assert r.returncode == 0 and "reads agree" in r.stdout, r.stderr[-2000:]
