@@ -5,10 +5,10 @@ Headline workload: the ragged batch of 256 chains with lengths uniform in
 [50, 600] residues (818,020 atoms), random-coil starts from per-chain seeds,
 10 A cutoff, 250 samples per offset sphere, mixed precision (FP32 pair forces
 and sample tests, FP64 kinematics, torques and step), the cell edge and the
-iterations per replayed HIP graph picked by the autotuner on the same batch
+force kernel's launch shape picked by the autotuner on the same batch
 before timing.  One step is one KCM iteration of every chain of the batch
 (forward kinematics, cell list, Coulomb + LJ + SASA solvation forces,
-torques, compliance step).  Inputs are built and every graph is captured
+torques, compliance step), two launches on this batch.  Inputs are built
 before the timed region, which covers exactly --steps iterations between two
 device synchronisations.  Prints one JSON line.
 
@@ -185,9 +185,10 @@ def batch_workload(n_chains: int = 256):
 
 def run_batch(steps: int, warmup: int, n_chains: int = 256, tune: bool = True, direct: bool = False,
               full_steps: int = 500, setting=None):
-    """Ragged batch in mixed precision: all chains advanced together by replayed
-    HIP graphs, with the cell edge and the iterations per graph picked by the
-    autotuner on the same batch first.  Times `steps` iterations (events on
+    """Ragged batch in mixed precision: all chains advanced together, with the
+    cell edge, the force kernel's launch shape and, where the set's iterations
+    are replayed HIP graphs, their depth picked by the autotuner on the same
+    batch first.  Times `steps` iterations (events on
     sampled ones), then, on fresh chains, the workload's full `full_steps`
     iterations without event samples."""
     import torch
@@ -205,14 +206,16 @@ def run_batch(steps: int, warmup: int, n_chains: int = 256, tune: bool = True, d
     else:
         tuned = autotune.tune(T, items, kcm.KCM_MIXED, stream=stream) if tune and not direct else None
     p = kcm.kcm_default_params(precision=kcm.KCM_MIXED, cell_size=tuned.cell_size if tuned else 0.0)
-    depth = 0 if direct else (tuned.graph_depth if tuned else 1)
+    launches = kcm.kcm_iteration_launches([len(seq) for seq, _ in items])
+    # iterations of two launches are launched directly
+    depth = 0 if direct or launches == 2 else (tuned.graph_depth if tuned else 1)
     chains = [kcm.Chain(seq, T, p, theta0=th) for seq, th in items]
     atoms = sum(c.n_atoms for c in chains)
     n_samples = chains[0].n_samples
     kcm.kcm_set_graphs(depth)
     full = None
     try:
-        # warm-up: captures the one-iteration and the depth-iteration graphs
+        # warm-up: captures the one-iteration and the depth-iteration graphs, if any
         kcm.kcm_step(chains, max(warmup, 1) + depth, stream, report=False)
         torch.cuda.synchronize()
         secs, force_ms, iter_ms, samples = timed_steps(kcm, chains, steps, stream)
@@ -249,6 +252,7 @@ def run_batch(steps: int, warmup: int, n_chains: int = 256, tune: bool = True, d
             c.free()
     out = {"chains": len(items), "atoms": atoms, "steps": steps, "seconds": secs, "ms_per_step": 1e3 * secs / steps,
            "value": atoms * steps / secs, "failed_chains": int(bad), "cell_size": p.cell_size, "graph_depth": depth,
+           "launches_per_iteration": launches,
            "force_variant": tuned.force_variant if tuned else 0,
            "force_ms_mean": force_ms, "iter_ms_mean": iter_ms, "force_samples": samples, "units": units,
            "n_samples": n_samples}
@@ -603,6 +607,7 @@ def main():
                 "cell_size": b["cell_size"],
                 "force_variant": b["force_variant"],
                 "graph_depth": b["graph_depth"],
+                "launches_per_iteration": b["launches_per_iteration"],
             },
             "roofline": roofline(u, b["force_ms_mean"], "mixed", traffic_for("mixed", "batch256")),
             "kernel_ms": {"force": b["force_ms_mean"], "iteration": b["iter_ms_mean"],

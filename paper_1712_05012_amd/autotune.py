@@ -4,14 +4,15 @@ iterations per graph.
 Three settings change the speed of an iteration but not its results beyond
 rounding order: the edge of the cells of the grid (``kcm_params.cell_size``;
 0 picks half the reach), the launch shape of the force kernel
-(``kcm_set_force_variant``: candidates per lane per trip, the block of
-neighbours step 1 reads before its saturation check and the atoms' order
-over the XCDs; identical results) and
-how many iterations one replayed HIP graph holds (``kcm_set_graphs``).
-``tune`` builds trial copies of the chains for every candidate edge, times a
-few iterations at every shape and depth on the device, and returns the
-fastest setting together with the whole table it measured.  The trial chains
-are freed; the caller builds its own with the chosen parameters.
+(``kcm_set_force_variant``: candidates per lane per trip and the atoms' order
+over the XCDs; identical results) and how many iterations one replayed HIP
+graph holds (``kcm_set_graphs``).
+``tune`` builds trial copies of the chains for every candidate edge, times the
+same iterations at every shape and depth on the device, and returns the
+fastest setting together with the whole table it measured.  Calls whose
+iterations are two launches use no graphs (``kcm_iteration_launches``): one
+run then stands for every depth, and the first one is returned.  The trial
+chains are freed; the caller builds its own with the chosen parameters.
 
 The timing runs through the C ABI only (``kcm_step`` on the given stream),
 with one device synchronisation before and after each timed run.
@@ -47,6 +48,8 @@ def tune(residue_types, items, precision, cell_sizes=(0.0, 4.4, 3.6), variants=(
 
     if not items:
         raise ValueError("nothing to tune")
+    graphs = kcm.kcm_iteration_launches([len(seq) for seq, _ in items]) > 2
+    run = iters * max(1, *depths)
     table = []
     try:
         for cs in cell_sizes:
@@ -56,14 +59,15 @@ def tune(residue_types, items, precision, cell_sizes=(0.0, 4.4, 3.6), variants=(
             try:
                 for v in variants:
                     kcm.kcm_set_force_variant(v)
-                    for d in depths:
-                        kcm.kcm_set_graphs(d)
-                        kcm.kcm_step(chains, warmup + d, stream, report=False)  # captures the graphs
-                        torch.cuda.synchronize()
-                        t0 = time.perf_counter()
-                        kcm.kcm_step(chains, iters * d, stream, report=False)
-                        torch.cuda.synchronize()
-                        rate = atoms * iters * d / (time.perf_counter() - t0)
+                    for k, d in enumerate(depths):
+                        if graphs or k == 0:
+                            kcm.kcm_set_graphs(d)
+                            kcm.kcm_step(chains, warmup + d, stream, report=False)  # captures the graphs
+                            torch.cuda.synchronize()
+                            t0 = time.perf_counter()
+                            kcm.kcm_step(chains, run, stream, report=False)
+                            torch.cuda.synchronize()
+                            rate = atoms * run / (time.perf_counter() - t0)
                         table.append((float(cs), int(v), int(d), float(chains[0].cells(stream)["cell"]), rate))
             finally:
                 for c in chains:
