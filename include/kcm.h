@@ -23,15 +23,18 @@
  *    is given and never frees it.  The one exception is per-call bookkeeping:
  *    kcm_step, kcm_fold, kcm_mc_minimize and kcm_set_theta_batch keep, per
  *    (device, stream), device tables of the last four chain sets (descriptor
- *    pointers, offset arrays and a map of atoms to chains, about 28 bytes per
- *    chain and up to 128 KiB), each with the per-chain records (pinned host
- *    memory) and the captured HIP graphs; these are allocated when a set first
- *    arrives, reused while it comes back (graphs are dropped when one of their
- *    chains is freed) and kept until the process ends.  kcm_get_state and
- *    kcm_mc_best_theta share up to four pinned buffers of 1 MiB, allocated when
- *    first needed and
- *    kept until the process ends.  kcm_step_noalloc takes the same
- *    bookkeeping from static device memory and allocates nothing.
+ *    pointers, offset arrays and maps of atoms and workgroups to chains: twice
+ *    the sum of 24 bytes per chain, 64 KiB at most for the map of atoms, and 4
+ *    bytes for every 256 atoms, 256 joints and 4,096 cells of each chain; and 16
+ *    bytes per chain where angles or perturbations were passed), each with the
+ *    per-chain records (pinned host memory, two records per chain and at least
+ *    64) and the captured HIP graphs.  These are allocated when a set first
+ *    arrives, reused while it comes back or by another set in its place (graphs
+ *    are dropped when one of their chains is freed) and kept until the process
+ *    ends.  kcm_get_state and kcm_mc_best_theta share up to four pinned buffers
+ *    of 1 MiB, allocated when first needed and kept until the process ends.
+ *    kcm_step_noalloc takes the same bookkeeping from static device memory and
+ *    allocates nothing.
  *    Host-side handles are owned by the library (kcm_chain_free).  hip_stream
  *    is a hipStream_t (NULL = default stream); work is queued asynchronously
  *    unless a function says it synchronises.

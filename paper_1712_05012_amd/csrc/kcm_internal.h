@@ -16,7 +16,7 @@ constexpr int SCAN_CHUNK = 4096;     // cells per workgroup of the cell-count sc
 constexpr int SCAN_MAX_CHUNKS = 16384; // chunks per chain the scatter's offset table holds
 constexpr int JOINT_BLOCK = 256;     // joints per workgroup of the torque / step / kinematics kernels
 constexpr int MAX_NBR = KCM_NBR_CHUNK; // solvation neighbours of one atom kept in LDS (the list, its atoms
-                                      // and its events, 5,760 bytes in the mixed form, let 24 waves share a CU)
+                                      // its events and the pair queue, 6,272 bytes in the mixed form, let 24 waves share a CU)
 constexpr int SAMPLE_PASS = 256;     // offset-sphere samples the force kernel takes at a time
 constexpr int MAX_REACH = 3;         // cell-stencil half width the force kernel supports (cells >= reach/3)
 constexpr double FIX_SCALE = 4294967296.0;  // fixed-point units per kcal/mol/A (2^32)

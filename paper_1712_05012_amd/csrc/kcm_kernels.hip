@@ -353,10 +353,6 @@ __device__ __forceinline__ double wave_max(double v)
 {
     return wave_all(v, [](double a, double b) { return max_num(a, b); });
 }
-__device__ __forceinline__ double wave_min(double v)
-{
-    return wave_all(v, [](double a, double b) { return min_num(a, b); });
-}
 __device__ __forceinline__ int wave_sum_i(int v)
 {
     return wave_all(v, [](int a, int b) { return a + b; });
@@ -561,14 +557,7 @@ __device__ __forceinline__ void loaded_one(int v) { asm volatile("" : : "v"(v));
 __device__ __forceinline__ void loaded_one(const double4 &v) { asm volatile("" : : "v"(v.x), "v"(v.y), "v"(v.z)); }
 template <typename... T> __device__ __forceinline__ void loaded(const T &...v) { (loaded_one(v), ...); }
 
-// Grid of Sec. 3.2 from the per-workgroup bounding boxes of the placed atoms,
-// plus a margin; the cell edge starts at max(cell_min, reach / MAX_REACH) and
-// grows until the grid fits the chain's cell capacity.  Block-wide (any block
-// size); returns false (and a one-cell grid) when the box is not finite or
-// cannot be covered.  s_red: [nw * 6].
-// The grid for the bounding box [lo, hi] of the placed atoms, plus a margin, by
-// a whole wave: lane k < 3 brings axis k's bounds, the others axis 2's, and all
-// get the grid; ok stays true iff it could be sized within the capacity.
+// What a chain's grid is sized by.
 struct GridRule {
     double reach_len, cell, inv_cell;  // interaction reach, first cell edge
     int cap_cells;
@@ -580,6 +569,11 @@ __device__ __forceinline__ GridRule grid_rule(const Chain *cd)
     const double cell = fmax(cd->cell_min, reach_len / MAX_REACH);
     return {reach_len, cell, 1.0 / cell, cd->cap_cells};
 }
+// The grid of Sec. 3.2 for the bounding box [lo, hi] of the placed atoms, plus a
+// margin, by a whole wave: lane k < 3 brings axis k's bounds, the others axis
+// 2's, and all get the grid; ok stays true iff it could be sized within the
+// capacity.  The cell edge starts at max(cell_min, reach / MAX_REACH) and grows
+// until the grid fits the chain's cell capacity.
 __device__ __forceinline__ Grid size_grid(const GridRule &rule, double lo, double hi, bool &ok)
 {
     const double L = lo - GRID_MARGIN, H = hi + GRID_MARGIN, ext = H - L;
@@ -614,6 +608,9 @@ __device__ __forceinline__ double axis_of_lane(const double (&v)[3])
     return lane == 0 ? v[0] : lane == 1 ? v[1] : v[2];
 }
 
+// The grid from the per-workgroup bounding boxes, block-wide (any block size);
+// returns false (and a one-cell grid) when the box is not finite or cannot be
+// covered.  s_red: [nw * 6].
 __device__ bool grid_from_parts(const ChainDev *cd, Grid *out, double *s_red, int *s_ok)
 {
     const int n = cd->n_atoms;
@@ -1662,8 +1659,8 @@ __global__ __launch_bounds__(ATOM_BLOCK) void k_rank(Batch bt)
 // us); 26,500 where every atom compared itself with all of its cell (10.9 us);
 // 24,000 where the torques went through LDS to a thread for each joint (10.3
 // us).  768-thread form, 256 chains of 500 to 6,000 atoms: 108 us, 123 before
-// the barriers changed.  Workgroups of 768 threads at most: 1,024 would leave
-// 128 registers.
+// the barriers changed.  Workgroups of 768 threads at most: 1,024 leave 128
+// registers, where the form that keeps its loads needs 155 (32 spilled).
 // SMALL, the form of at most 256 atoms, has one block of atoms and all joints
 // in one wave: the thread of a joint's first atom has its whole torque, the
 // scan needs no carries and no barrier before it, and another wave writes the
@@ -2256,11 +2253,14 @@ constexpr float CAP_SPLIT = 0.6f;
 // order; XCD-aware by chunks (each XCD takes chunks of XCD_CHUNK consecutive
 // cell-ordered atoms in turn, so that its L2 serves a few regions of space and
 // all XCDs see the same mix of atoms); or XCD-aware by eighths (XCD x takes the
-// x-th contiguous eighth).  Force kernel in shapes 0 to 3: 256-chain batch
-// 2,009, 2,046, 1,995, 2,048 us; 10,000-residue globule 288, 276, 275, 280; 500
-// short chains in water 194, 199, 192, 197; 256 in vacuum (FP64) 29.3, 31.1,
-// 28.8, 29.7; sixteen chains of unequal density, with an earlier kernel, 171,
-// 174, 215, 220 (one eighth holds most of the work).
+// x-th contiguous eighth).  Force kernel in shapes 0 to 3, us: 256-chain batch
+// 1,958, 1,972, 1,960, 2,012; 10,000-residue globule 260, 260, 259, 268; 500 short
+// chains in water 175, 180, 175, 178; 256 in vacuum (FP64) 28.8, 30.4, 28.4,
+// 28.8; sixteen chains, every fourth compact and the others extended or coils,
+// 335, 340, 282, 342; four compact chains and then twelve extended ones 376,
+// 376, 390, 386, in FP64 538, 534, 558, 547.  Eighths gain where dense and sparse
+// chains alternate and lose where two XCDs get all of the dense ones; chunks are
+// nowhere behind cell order by more than 1 %, and are the default.
 // Every shape visits the candidates and appends the neighbours in the same
 // order, and takes the same decisions: the results are the same bit for bit.
 enum XcdOrder { CELL_ORDER, XCD_CHUNKS, XCD_EIGHTHS };
@@ -2293,8 +2293,8 @@ static_assert((2 * MAX_REACH + 1) * (2 * MAX_REACH + 1) <= WAVE, "stencil rows m
 // in [-256, 256]: the three axes share a word as ten-bit fields biased by 512
 // (no carry or borrow leaves a field), scattered after each pass.  One word
 // instead of two keeps the mixed form's LDS within five of the 1,280-byte
-// granules it is allotted in, 24 waves to a CU: with 6,720 bytes it was six
-// granules and 21 waves, the 256-chain batch 2,419 us against 2,289.
+// granules it is allotted in (6,272 bytes with the pair queue), 24 waves to a CU:
+// with 6,720 bytes it was six granules and 21 waves, the 256-chain batch 2,419 us against 2,289.
 constexpr int EV_BITS = 10, EV_BIAS = 1 << (EV_BITS - 1), EV_MASK = (1 << EV_BITS) - 1;
 constexpr unsigned EV_INIT = EV_BIAS | EV_BIAS << EV_BITS | EV_BIAS << (2 * EV_BITS);
 static_assert(WAVE * SPL < EV_BIAS, "events of a pass fit their field");
@@ -2665,16 +2665,20 @@ __device__ __noinline__ ChunkedSasa sasa_chunked(CDev cd, const ChunkArgs c, Nbr
     return out;
 }
 
-// Mixed form: six waves per SIMD (80 registers, 5,760 bytes of LDS), which
+// Mixed form: six waves per SIMD (80 registers, 6,272 bytes of LDS), which
 // hides the latency of the candidate loads and LDS reads better than four
 // waves with room to spare (3.06 against 3.39 ms on the 256-chain batch when
-// measured, with a longer list); seven spill in the hot loops.  The FP64 form:
-// four (127 registers; its 9,600 bytes allow 16 waves per CU).  CAV false: no
+// measured, with a longer list); a seventh finds no LDS, which holds 25 waves
+// of a CU.  The FP64 form: four (127 registers; its 10,112 bytes allow 16 waves
+// per CU).  CAV false: no
 // chain of the batch has the solvation term.  Without its list and tests
 // eight waves fit a SIMD in either form, and the candidates go by without the
 // neighbour test (FP64, 256 chains of 100 to 200 atoms: 27.4 us, 39.0 with the
 // general kernel; the results are the same bit for bit).
 constexpr int force_waves(bool fp32, bool cav) { return cav ? (fp32 ? 6 : 4) : 8; }
+// LDS of a CU, and of one wave in the granules it is allotted in.
+constexpr int CU_LDS = 160 * 1024, LDS_GRANULE = 1280;
+constexpr int lds_granules(int bytes) { return (bytes + LDS_GRANULE - 1) / LDS_GRANULE * LDS_GRANULE; }
 template <typename Real, int CPT, int SAT_CHECK, XcdOrder ORDER, bool CAV>
 __global__ __launch_bounds__(WAVE, force_waves(sizeof(Real) == 4, CAV)) void k_force(Batch bt)
 {
@@ -2684,6 +2688,8 @@ __global__ __launch_bounds__(WAVE, force_waves(sizeof(Real) == 4, CAV)) void k_f
     __shared__ NbrEntry<Real> s_nbr[LIST];
     __shared__ int s_nbr_a[LIST];
     __shared__ __align__(16) unsigned s_word[CAV ? MAX_NBR + 2 * WAVE : WAVE + 4 * (3 * APR + 1) * sizeof(Real) / 4];
+    static_assert(4 * force_waves(MIXED, CAV) * lds_granules(sizeof(s_nbr) + sizeof(s_nbr_a) + sizeof(s_word)) <= CU_LDS,
+                  "LDS for the waves that the registers allow");
     unsigned *const s_ev = s_word;              // net events of each neighbour in this pass
     unsigned *const s_pair = s_word + LIST;     // (sample, neighbour) pairs that await their displaced tests
 
