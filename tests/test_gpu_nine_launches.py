@@ -282,3 +282,31 @@ def test_more_sets_with_graphs_than_a_stream_keeps():
         kcm.kcm_set_graphs(1)
         for s in sets:
             _free(*s)
+
+
+@pytest.mark.parametrize("sizes,launches", [((12,), 2), ((30, 7, 90), 2), ((LONG, 7), 9)])
+def test_noalloc_step_in_a_callers_graph(sizes, launches):
+    # a caller's own capture of kcm_step_noalloc, replayed with eager work and
+    # synchronisations between, against kcm_step
+    p = params(kcm.KCM_MIXED)
+    a, b = [_chain(m, p, m == 7) for m in sizes], [_chain(m, p, m == 7) for m in sizes]
+    _form(launches, *a)
+    print(f"case=nine-capture sizes={sizes}", flush=True)
+    torch.cuda.synchronize()
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        kcm.kcm_step_noalloc(b, 1, report=False)  # the table of the set is there before the capture
+        torch.cuda.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=s):
+            kcm.kcm_step_noalloc(b, 2, report=False)
+    kcm.kcm_step(a, 1)
+    for k in range(4):
+        with torch.cuda.stream(s):
+            g.replay()
+        torch.cuda.synchronize()
+        assert torch.ones(1000, device="cuda").sum().item() == 1000.0
+        kcm.kcm_step(a, 2)
+        for x, y in zip(a, b):
+            _same(x, y)
+    _free(*a, *b)
