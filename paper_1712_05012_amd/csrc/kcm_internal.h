@@ -54,8 +54,8 @@ struct ChainStats {
 // may change, except grid_bad in the key kernel that sizes the grid in every
 // workgroup: all of them reach the same decision.
 
-// The cell grid of the current iteration (sized at its start from the last
-// bounding box).
+// The cell grid of the current iteration, sized from the bounding box of the
+// conformation it has just placed.
 struct Grid {
     double origin[3];
     double cell, inv_cell;
