@@ -486,6 +486,12 @@ struct kcm_chain {
 
 namespace {
 
+// (after the check of the set) the chains' work goes out on this stream
+void queued_on(kcm_chain *const *chains, int n_chains, hipStream_t stream)
+{
+    for (int i = 0; i < n_chains; ++i) chains[i]->stream.store(stream, std::memory_order_relaxed);
+}
+
 kcm_status ensure_table(kcm_chain *const *chains, int n_chains, hipStream_t stream, Table **out)
 {
     int dev = 0;
@@ -514,7 +520,6 @@ kcm_status ensure_table(kcm_chain *const *chains, int n_chains, hipStream_t stre
         t = oldest;
     }
     t->last_use = ++g_table_clock;
-    for (int i = 0; i < n_chains; ++i) chains[i]->stream.store(stream, std::memory_order_relaxed);
     if (!same) {
         t->chains.clear();  // until the new set is in place
         t->mc_off_per = -1;
@@ -1052,6 +1057,7 @@ kcm_status iterate_locked(Table *t, kcm_chain *const *chains, int n_chains, int 
         t->graph_n_depth = depth;
     }
     if (n_iter > 0) {
+        queued_on(chains, n_chains, stream);
         bool boot = boot_all;
         for (int i = 0; i < n_chains; ++i) boot = boot || chains[i]->boot;
         if (boot) {
@@ -1276,7 +1282,6 @@ kcm_status kcm_step_noalloc(kcm_chain *const *chains, int n_chains, int n_iter, 
     std::sort(g_noalloc_sorted, g_noalloc_sorted + n_chains);
     if (std::adjacent_find(g_noalloc_sorted, g_noalloc_sorted + n_chains) != g_noalloc_sorted + n_chains)
         return fail(KCM_E_INVAL, "a chain appears twice in one call");
-    for (int i = 0; i < n_chains; ++i) chains[i]->stream.store(stream, std::memory_order_relaxed);
     const int prec = chains[0]->h.precision;
     NoallocDevice *d = nullptr;
     kcm_status s = noalloc_device(dev, &d);
@@ -1292,6 +1297,7 @@ kcm_status kcm_step_noalloc(kcm_chain *const *chains, int n_chains, int n_iter, 
     const Batch &bt = d->batch;
     hipError_t e = hipSuccess;
     if (n_iter > 0) {
+        queued_on(chains, n_chains, stream);
         bool boot = false;
         for (int i = 0; i < n_chains; ++i) boot = boot || chains[i]->boot;
         if (boot) {
@@ -1563,6 +1569,7 @@ kcm_status kcm_set_theta_batch(kcm_chain *const *chains, int32_t n_chains, const
     Table *t = nullptr;
     if ((s = ensure_table(chains, n_chains, stream, &t)) != KCM_OK) return s;
     if ((s = upload_joint_offsets(t, chains, n_chains, 1, stream)) != KCM_OK) return s;
+    queued_on(chains, n_chains, stream);
     HIP_TRY(launch_set_theta(t->batch, theta, t->mc_off_dev, stream));
     for (int i = 0; i < n_chains; ++i) chains[i]->boot = true;
     return KCM_OK;

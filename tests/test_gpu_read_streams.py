@@ -61,6 +61,25 @@ def test_read_on_another_stream_sees_the_queued_steps(hip, m, n_iter, reader):
     b.free()
 
 
+def test_a_call_without_iterations_moves_no_work_to_its_stream(hip):
+    work, other = _stream(hip), _stream(hip)
+    seq, th = synth.sequence(15, 62), synth.random_dihedrals(15, 62)
+    a, b = (kcm.Chain(seq, TYPES, params(kcm.KCM_MIXED), theta0=th) for _ in range(2))
+    print("case=read-streams no iterations", flush=True)
+    torch.cuda.synchronize()
+    kcm.kcm_step([a], 2000)
+    want = a.state()
+    kcm.kcm_step([b], 2000, stream=work, report=False)
+    kcm.kcm_step([b], 0, stream=other, report=False)
+    got = kcm.kcm_get_state(b.handle, stream=other)
+    for k in want:
+        assert np.array_equal(got[k], want[k]), k
+    for s in (work, other):
+        assert hip.hipStreamSynchronize(C.c_void_p(s)) == 0 and hip.hipStreamDestroy(C.c_void_p(s)) == 0
+    a.free()
+    b.free()
+
+
 def test_reads_do_not_depend_on_the_default_of_pinned_memory():
     # the records and the boxes are polled: coherent memory, also where the
     # environment makes pinned memory non-coherent unless asked otherwise
