@@ -486,10 +486,23 @@ struct kcm_chain {
 
 namespace {
 
-// (after the check of the set) the chains' work goes out on this stream
-void queued_on(kcm_chain *const *chains, int n_chains, hipStream_t stream)
+// Iterations of these chains go out on the stream: whether one of them needs
+// the boot sequence first.  booted() then says that none does any more.
+bool needs_boot(kcm_chain *const *chains, int n_chains, hipStream_t stream)
 {
-    for (int i = 0; i < n_chains; ++i) chains[i]->stream.store(stream, std::memory_order_relaxed);
+    bool boot = false;
+    for (int i = 0; i < n_chains && !boot; ++i) {
+        boot = chains[i]->boot;
+        chains[i]->stream.store(stream, std::memory_order_relaxed);
+    }
+    return boot;
+}
+void booted(kcm_chain *const *chains, int n_chains, hipStream_t stream)
+{
+    for (int i = 0; i < n_chains; ++i) {
+        chains[i]->boot = false;
+        chains[i]->stream.store(stream, std::memory_order_relaxed);
+    }
 }
 
 kcm_status ensure_table(kcm_chain *const *chains, int n_chains, hipStream_t stream, Table **out)
@@ -1057,12 +1070,9 @@ kcm_status iterate_locked(Table *t, kcm_chain *const *chains, int n_chains, int 
         t->graph_n_depth = depth;
     }
     if (n_iter > 0) {
-        queued_on(chains, n_chains, stream);
-        bool boot = boot_all;
-        for (int i = 0; i < n_chains; ++i) boot = boot || chains[i]->boot;
-        if (boot) {
+        if (needs_boot(chains, n_chains, stream) || boot_all) {
             HIP_TRY(launch_boot(bt, stream));
-            for (int i = 0; i < n_chains; ++i) chains[i]->boot = false;
+            booted(chains, n_chains, stream);
         }
     }
     for (int it = 0; it < n_iter;) {
@@ -1297,12 +1307,9 @@ kcm_status kcm_step_noalloc(kcm_chain *const *chains, int n_chains, int n_iter, 
     const Batch &bt = d->batch;
     hipError_t e = hipSuccess;
     if (n_iter > 0) {
-        queued_on(chains, n_chains, stream);
-        bool boot = false;
-        for (int i = 0; i < n_chains; ++i) boot = boot || chains[i]->boot;
-        if (boot) {
+        if (needs_boot(chains, n_chains, stream)) {
             if ((e = launch_boot(bt, stream)) != hipSuccess) return fail(KCM_E_DEVICE, "kcm_step_noalloc: launch failed");
-            for (int i = 0; i < n_chains; ++i) chains[i]->boot = false;
+            booted(chains, n_chains, stream);
         }
         for (int it = 0; it < n_iter && e == hipSuccess; ++it) e = launch_iteration(bt, prec, stream);
         if (e == hipSuccess) e = launch_final(bt, stream);
@@ -1569,9 +1576,11 @@ kcm_status kcm_set_theta_batch(kcm_chain *const *chains, int32_t n_chains, const
     Table *t = nullptr;
     if ((s = ensure_table(chains, n_chains, stream, &t)) != KCM_OK) return s;
     if ((s = upload_joint_offsets(t, chains, n_chains, 1, stream)) != KCM_OK) return s;
-    queued_on(chains, n_chains, stream);
     HIP_TRY(launch_set_theta(t->batch, theta, t->mc_off_dev, stream));
-    for (int i = 0; i < n_chains; ++i) chains[i]->boot = true;
+    for (int i = 0; i < n_chains; ++i) {
+        chains[i]->boot = true;
+        chains[i]->stream.store(stream, std::memory_order_relaxed);
+    }
     return KCM_OK;
 }
 
